@@ -256,7 +256,9 @@ typedef struct {
     int64_t records;
     int64_t nnz_in, nnz_out;
     int32_t m_out, n_out;
-    /* device time per phase (ms), measured with HIP events on the stream */
+    /* device time per phase (ms): ingest, parallel passes, compaction and the
+     * whole run by HIP events on the stream, the rounds' phases by the device's
+     * clock, read at the start of their kernels */
     double ms_ingest, ms_sweep, ms_decide, ms_parallel, ms_compact, ms_total;
     int64_t sweep_launches;        /* launches of the row-sweep kernel          */
     double sweep_bytes;            /* algorithmic bytes of those launches       */

@@ -219,13 +219,13 @@ static psl_status setup_arena(psl_presolver* p) {
   // one per long-row chunk
   ALLOC(p->cand_cnt, m / 4 + NBINS + (N / PASS_LEN + N / 512 + 2) + 64);
   ALLOC(flags, 1);
-  ALLOC(cnt, m + n + 1);
+  ALLOC(cnt, std::max(m + n + 1, decide_tiles(m, n)));
   ALLOC(off, m + n + 1);
   ALLOC(p->bins_a, m);
   ALLOC(p->bins_s, m);
-  ALLOC(p->sel_dev, 16);
-  ALLOC(p->sel_keep, select_keep_bytes(m));
-  ALLOC(p->sel_cnt, select_count_ints(m));
+  ALLOC(d.super, decide_supers(m, n));
+  ALLOC(d.super_done, decide_supers(m, n));
+  ALLOC(d.super_off, decide_supers(m, n));
   ALLOC(p->bin_counts_dev, NBINS);
   ALLOC(p->lb_in, n);
   ALLOC(p->ub_in, n);
@@ -398,7 +398,6 @@ static psl_status setup_arena(psl_presolver* p) {
     HALLOC(p->h_round, K);
     HALLOC(p->h_ok, K);
     HALLOC(p->h_lpf, K);
-    HALLOC(p->h_lpo, K);
     HALLOC(p->h_lpt, K);
     HALLOC(p->h_desc, K);
     HALLOC(p->h_off_in, K);
@@ -441,13 +440,17 @@ static psl_status setup_arena(psl_presolver* p) {
   d.lrow = lrow;
   d.nlong = 0;
   d.nchunks = 0;
+  d.sel = flags->sel[0];
+  int rate = 0;  // kHz
+  if (hipDeviceGetAttribute(&rate, hipDeviceAttributeWallClockRate, p->s.device) == hipSuccess && rate > 0)
+    p->tick_ms = 1.0 / rate;
   d.K = 1;
   d.row_lp = p->row_lp;
   d.col_lp = p->col_lp;
   d.lp_row0 = p->lp_row0;
   d.lp_col0 = p->lp_col0;
   d.lp_ok = p->lp_ok;
-  d.lp_round = p->lp_round;
+  d.lp_round = d.lp_round_mut = p->lp_round;
   d.lpf = p->lpf;
   d.lpo = p->lpo;
   const psl_settings& s = p->s;
@@ -478,68 +481,37 @@ static psl_status read_flags(psl_presolver* p) {
 }
 
 
-// workgroups per bin from the current bin offsets and chunk count
-static void set_grid(psl_presolver* p) {
-  const Dev& d = p->d;
-  auto cnt = [&](int b) { return d.bin_off[b + 1] - d.bin_off[b]; };
+// workgroups per bin for a launch over `rows` rows of each bin (and chunks)
+static SweepGrid grid_of(const int32_t* rows, int32_t chunks) {
+  SweepGrid g;
+  g.long_base = 0;
   for (int b = 0; b < BIN_LONG; ++b) {
     int per_wg = bin_rows(b) * bin_rep(b);  // rows one workgroup sweeps
-    p->grid.nb[b] = (cnt(b) + per_wg - 1) / per_wg;
+    g.nb[b] = (rows[b] + per_wg - 1) / per_wg;
+    g.long_base += (int64_t)g.nb[b] * cand_region(b);
   }
-  p->grid.nb[BIN_LONG] = d.nchunks;
-  p->grid.long_base = 0;
-  for (int b = 0; b < BIN_LONG; ++b) p->grid.long_base += (int64_t)p->grid.nb[b] * cand_region(b);
+  g.nb[BIN_LONG] = chunks;
+  return g;
 }
 
-// sweep the rows of view v from now on
-static void use_view(psl_presolver* p, const View& v) {
+// launches from now on take every active row of an LP still presolving (the
+// selection is queued; p->grid covers every row of the bins)
+static void use_full_view(psl_presolver* p) {
   Dev& d = p->d;
-  d.bins = v.bins;
-  d.lchunk = v.chunks;
-  for (int b = 0; b <= NBINS; ++b) d.bin_off[b] = v.off[b];
-  d.nchunks = v.nchunks;
-  set_grid(p);
-  p->cur = v;
+  select_all(d, p->thresholds[0], p->thresholds[2], p->bins_a, p->chunks_a, d.flags->sel[0], p->stream);
+  d.bins = p->bins_a;
+  d.lchunk = p->chunks_a;
+  d.sel = d.flags->sel[0];
+  p->grid = grid_of(p->bin_counts, d.nchunks);
 }
 
-// the view described by a selection's device totals (bin offsets, rows,
-// nonzeros, chunks)
-static View view_of(BinEnt* bins, LongChunk* chunks, const int32_t* tot) {
-  View v;
-  v.bins = bins;
-  v.chunks = chunks;
-  for (int b = 0; b <= NBINS; ++b) v.off[b] = tot[b];
-  v.rows = tot[NBINS + 1];
-  v.nnz = tot[NBINS + 2];
-  v.nchunks = tot[NBINS + 3];
-  return v;
-}
-
-// every active row of an LP still presolving (lp_ok), read back at once
-static psl_status full_view(psl_presolver* p, View& dst) {
+// the rows the last round's selection chose
+static void use_round_view(psl_presolver* p) {
   Dev& d = p->d;
-  select_rows(d, nullptr, 0, p->thresholds[0], p->thresholds[2], p->sel_keep, p->sel_cnt, p->bins_a, p->chunks_a,
-              p->sel_dev, p->ws, p->stream);
-  HIPCHK(p, hipMemcpyAsync(p->htot, p->sel_dev, (NBINS + 4) * sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
-  HIPCHK(p, hipStreamSynchronize(p->stream));
-  dst = view_of(p->bins_a, p->chunks_a, p->htot);
-  return PSL_OK;
-}
-
-// sweep every active row from now on
-static psl_status use_full_view(psl_presolver* p) {
-  View v;
-  psl_status e = full_view(p, v);
-  if (e == PSL_OK) use_view(p, v);
-  return e;
-}
-
-// queue the next round's selection with the mode the device decided
-// (d.flags->mode); read with the round's flags
-static void queue_selection(psl_presolver* p) {
-  Dev& d = p->d;
-  select_rows(d, &d.flags->mode, 0, p->thresholds[0], p->thresholds[2], p->sel_keep, p->sel_cnt, p->bins_s,
-              p->chunks_s, d.flags->sel, p->ws, p->stream);
+  d.bins = p->bins_s;
+  d.lchunk = p->chunks_s;
+  d.sel = d.flags->sel[1];
+  p->grid = grid_of(p->bin_counts, d.nchunks);
 }
 
 static std::string error_what(int32_t bits) {
@@ -629,14 +601,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   if (p->htot[0] > p->chunk_cap) return fail(p, PSL_ERR_CAPACITY, "too many long-row chunks");
   d.nchunks = p->htot[0];
   d.colid = nullptr;
-  View mv;
-  mv.bins = bins0;
-  mv.chunks = chunks0;
-  for (int b = 0; b <= NBINS; ++b) mv.off[b] = d.bin_off[b];
-  mv.nchunks = d.nchunks;
-  mv.rows = m;
-  mv.nnz = N;
-  use_view(p, mv);
+  p->grid = grid_of(p->bin_counts, d.nchunks);
   if (p->grid.long_base + (int64_t)p->htot[1] > p->cand_cap)
     return fail(p, PSL_ERR_CAPACITY, "candidate buffer too small for the row bins");
 
@@ -645,6 +610,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   p->cmp.colid = p->colid;
   d.colid = p->colid;
   list_dense_cols(d, st);
+  HIPCHK(p, hipMemcpyAsync(p->htot, d.n_dense, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   if (p->s.enable_doubletons) {
     // the input's transposed copy for the dual postsolve; no column kept yet
     HIPCHK(p, hipMemcpyAsync(p->cp0, d.cp, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
@@ -675,6 +641,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   (void)n;
   HIPCHK(p, hipEventRecord(p->ev[1], st));
   HIPCHK(p, hipStreamSynchronize(st));
+  p->dense = p->htot[0] > 0;
   float ms = 0;
   HIPCHK(p, hipEventElapsedTime(&ms, p->ev[0], p->ev[1]));
   p->ms_ingest = ms;
@@ -933,11 +900,12 @@ static psl_status begin_lp_round(psl_presolver* p) {
   return PSL_OK;
 }
 
-// K > 1: queue the readback of the LPs' flags (and record counts); the next
+// K > 1: queue the readback of the LPs' flags (and round numbers); the next
 // synchronising read completes it
-static psl_status queue_lp_read(psl_presolver* p, bool totals) {
+static psl_status queue_lp_read(psl_presolver* p, bool rounds) {
   if (p->K == 1) return PSL_OK;
-  if (totals) HIPCHK(p, hipMemcpyAsync(p->h_lpo, p->lpo, p->K * sizeof(LpOut), hipMemcpyDeviceToHost, p->stream));
+  if (rounds)
+    HIPCHK(p, hipMemcpyAsync(p->h_round, p->lp_round, p->K * sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipMemcpyAsync(p->h_lpf, p->lpf, p->K * sizeof(LpFlags), hipMemcpyDeviceToHost, p->stream));
   return PSL_OK;
 }
@@ -997,9 +965,6 @@ static bool lp_unb(const psl_presolver* p, int k) {
 static bool lp_merged(const psl_presolver* p, int k) {
   return p->K > 1 ? p->h_lpf[k].merged != 0 : p->hflags->merged != 0;
 }
-static int32_t lp_total(const psl_presolver* p, int k) {
-  return p->K > 1 ? p->h_lpo[k].total : p->hflags->round_total;
-}
 
 // queue the read of the device flags (completed by the unit's wait)
 static psl_status queue_flags(psl_presolver* p) {
@@ -1052,8 +1017,8 @@ static psl_status cycle_start(psl_presolver* p) {
   R.consts_current = false;
   R.r = 0;
   R.unit = U_ROUND;
-  // a cycle's first round sweeps every active row
-  return use_full_view(p);
+  R.own = false;  // a cycle's first round sweeps every active row
+  return PSL_OK;
 }
 
 // after a cycle's rounds: its reduction pass, or the compaction
@@ -1109,50 +1074,71 @@ static psl_status complete_round0(psl_presolver* p) {
   return cycle_start(p);
 }
 
+// Rounds queued before the host looks at the results. Up to RUN_AHEAD_NNZ
+// nonzeros a round takes tens of microseconds and the read and wait after it as
+// much, so several rounds go in one unit, each launched for every row of the
+// bins (workgroups beyond the rows selected return at once). Larger LPs go
+// round by round, with grids of the size of the selection: on the LP of 9.7e7
+// nonzeros rounds queued eight at a time cost 85 ms instead of 82.5, on the
+// power-law LP (1e7) and on one of 9.6e6 they change nothing (5.39 ms; 19.4
+// against 19.9). Units of 4, 8 and 16 rounds give 2.00, 1.88 and 1.92 ms on an
+// LP of 2000 rows (34 rounds) and 1.52, 1.51, 1.60 on one of 31337 (17 rounds,
+// where the rounds queued past the last are launches that return).
+static const int64_t RUN_AHEAD_NNZ = 4000000;
+static const int RUN_AHEAD = 8;
+
 static psl_status launch_round(psl_presolver* p) {
   Dev& d = p->d;
   hipStream_t st = p->stream;
   const psl_settings& s = p->s;
   EngRun& R = p->run;
-  int64_t m = p->m, n = p->n;
-  ++R.round;
-  for (int k = 0; k < p->K; ++k)
-    if (p->lst[k].phase == LP_PROP) {
-      ++p->lst[k].rounds;
-      if (p->K > 1) p->h_round[k] = p->lst[k].rounds;
-    }
-  psl_status e = ensure_capacity(p, m + 3 * n + 16);
-  if (e == PSL_OK) e = begin_lp_round(p);
+  const int64_t need = p->m + 3 * (int64_t)p->n + 16;
+  psl_status e = ensure_capacity(p, need);
   if (e != PSL_OK) return e;
-  HIPCHK(p, hipEventRecord(p->ev[4], st));
-  launch_long_stats(d, MODE_ROUND, st);
-  HIPCHK(p, hipEventRecord(p->ev[7], st));
-  launch_sweep(d, p->grid, p->sweep_mode, st);
-  HIPCHK(p, hipEventRecord(p->ev[5], st));
-  launch_src(d, p->grid, st);
-  launch_decide(d, p->rec_count - p->rec_flushed, R.round, d.cnt, d.off, p->ws, st);
-  // (the candidate regions are free until the next sweep)
-  if (s.enable_free_singletons)
-    launch_free_singletons(d, reinterpret_cast<int32_t*>(d.cand), p->rec_count - p->rec_flushed, R.round, p->ws,
-                           st);
-  HIPCHK(p, hipEventRecord(p->ev[6], st));
-  // The next round's selection is made before the round's one read, in
-  // one pass over the rows. Rows none of whose columns changed since they
-  // were last swept give the same statistics and no qualifying candidate,
-  // so after a round with few column changes only the touched (marked)
-  // rows are swept; and inert rows (their infinite-contribution counts,
-  // kept current as bounds become finite, rule out every outcome) are
-  // never swept. The counts are kept by decrements while few bounds
-  // become finite in a round. After a round with many, no decrement is
-  // made and the next round skips no row: it sweeps, and so recounts,
-  // every row one of whose bounds became finite, while the counts of the
-  // rows it does not sweep are still exact; after it the counts are
-  // exact again. The device takes these decisions from the round's totals
-  // (d.flags->mode); an LP that stopped has left lp_ok already. When the
-  // rounds end here the selection is not used.
-  if (!d.dirty || !d.colid) return fail(p, PSL_ERR_DEVICE, "internal: incremental state not set up");
-  mark_dirty(d, R.r + 1 < s.max_rounds, p->incr_factor, p->count_factor, st);
-  queue_selection(p);
+  if (p->K > 1) {
+    for (int k = 0; k < p->K; ++k)
+      p->h_round[k] = p->lst[k].phase == LP_PROP ? p->lst[k].rounds + 1 : -p->lst[k].rounds;
+    HIPCHK(p, hipMemcpyAsync(p->lp_round, p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, st));
+  }
+  launch_rounds_begin(d, p->rec_count - p->rec_flushed, p->rec_cap, st);
+  const bool ahead = p->nnz <= RUN_AHEAD_NNZ && !p->step_rounds;
+  R.queued = std::min(ahead ? RUN_AHEAD : 1, s.max_rounds - R.r);
+  for (int q = 0; q < R.queued; ++q) {
+    const int seq = ++R.seq, round = R.round + 1 + q;
+    if (R.own) {
+      use_round_view(p);
+      if (R.queued == 1) {  // the counts were read with the round before
+        int32_t rows[NBINS];
+        for (int b = 0; b < NBINS; ++b) rows[b] = p->hflags->sel[1][b].v;
+        p->grid = grid_of(rows, p->hflags->sel[1][SEL_CHUNKS].v);
+      }
+    } else {
+      use_full_view(p);
+    }
+    R.own = true;
+    launch_long_stats(d, MODE_ROUND, p->grid.nb[BIN_LONG], seq, st);
+    launch_sweep(d, p->grid, p->sweep_mode, seq, st);
+    // The next round's selection is made by the device. Rows none of whose
+    // columns changed since they were last swept give the same statistics
+    // and no qualifying candidate, so after a round with few column changes
+    // only the touched (marked) rows are swept; and inert rows (their
+    // infinite-contribution counts, kept current as bounds become finite,
+    // rule out every outcome) are never swept. The counts are kept by
+    // decrements while few bounds become finite in a round. After a round with
+    // many, no decrement is made and the next round skips no row: it sweeps,
+    // and so recounts, every row one of whose bounds became finite, while the
+    // counts of the rows it does not sweep are still exact; after it the
+    // counts are exact again. The device takes these decisions from the
+    // round's totals (d.flags->mode); an LP that stopped has left lp_ok already.
+    // When the rounds end here the selection is not used.
+    RoundMode rm{R.r + q + 1 < s.max_rounds ? 1 : 0, p->incr_factor, p->count_factor};
+    launch_decide(d, p->grid, rm, p->dense, round, seq, d.cnt, st);
+    // (the candidate regions are free until the next sweep)
+    if (s.enable_free_singletons)
+      launch_free_singletons(d, reinterpret_cast<int32_t*>(d.cand), round, seq, p->ws, st);
+    select_next(d, p->thresholds[0], p->thresholds[2], p->bins_s, p->chunks_s, d.flags->sel[1], need,
+                q + 1 == R.queued, seq, st);
+  }
   e = queue_lp_read(p, true);
   if (e != PSL_OK) return e;
   return queue_flags(p);
@@ -1161,57 +1147,50 @@ static psl_status launch_round(psl_presolver* p) {
 static psl_status complete_round(psl_presolver* p) {
   EngRun& R = p->run;
   psl_stats& S = R.S;
-  int64_t m = p->m, n = p->n;
-  int32_t removed = p->hflags->rows_removed;
-  R.long_ms += elapsed(p, 4, 7);
-  R.sweep_ms += elapsed(p, 7, 5);
-  R.decide_ms += elapsed(p, 5, 6);
-  S.sweep_launches += 1;
-  S.sweep_nnz += p->cur.nnz;
-  // algorithmic bytes of the sweep launch: the swept rows' positions
+  const Flags& f = *p->hflags;
+  const int done = f.rounds_done - (int)S.sweep_launches;  // of the rounds queued
+  R.long_ms = (double)f.ticks[0] * p->tick_ms;
+  R.sweep_ms = (double)f.ticks[1] * p->tick_ms;
+  R.decide_ms = (double)f.ticks[2] * p->tick_ms;
+  S.sweep_launches = f.rounds_done;
+  // algorithmic bytes of the sweep launches: the swept rows' positions
   // (12 B a nonzero); per swept row its bin entry, row pointer, sides and
   // statistics (48 B); per column it can touch (at most one per nonzero)
   // the bound read and the new-bound write (32 B)
-  {
-    double sb = 12.0 * p->cur.nnz + 48.0 * p->cur.rows + 32.0 * std::min<int64_t>(n, p->cur.nnz);
-    S.sweep_bytes += sb;
-    // the decisions over every row and column, and the round's records
-    S.alg_bytes += sb + 40.0 * ((double)m + n) + 48.0 * p->hflags->round_total;
-  }
-  p->rec_count += p->hflags->round_total;
-  bool any_done = false;
+  const int64_t recs = p->rec_flushed + f.rec_at - p->rec_count;
+  const double sb = 12.0 * f.sum_nnz + 48.0 * f.sum_rows + 32.0 * f.sum_cols;
+  // the decisions over every row and column, and the rounds' records
+  S.alg_bytes += sb - S.sweep_bytes + 40.0 * done * ((double)p->m + p->n) + 48.0 * recs;
+  if (p->trace)
+    std::fprintf(stderr, "[psl] rounds to %d: swept rows %lld nnz %lld, records %lld, last round: %d, rows removed %d, "
+                 "bounds made finite %d\n", R.round + done, (long long)(f.sum_rows - R.rows_before),
+                 (long long)(f.sum_nnz - S.sweep_nnz), (long long)recs, f.round_total, f.rows_removed, f.fin_cols);
+  R.rows_before = f.sum_rows;
+  S.sweep_bytes = sb;
+  S.sweep_nnz = f.sum_nnz;
+  p->rec_count += recs;
+  R.round += done;
+  R.r += done;
   int nprop = 0;
   for (int k = 0; k < p->K; ++k) {
     LpState& L = p->lst[k];
     if (L.phase != LP_PROP) continue;
+    const bool more = p->K > 1 ? p->h_round[k] > 0 : f.round_total != 0 && !f.infeasible && !f.unbounded;
+    L.rounds = p->K == 1 ? L.rounds + done : more ? p->h_round[k] - 1 : -p->h_round[k];
     if (lp_inf(p, k)) {
       L.phase = LP_DONE;
       L.infeasible = true;
-      any_done = true;
     } else if (lp_unb(p, k)) {
       L.phase = LP_DONE;
       L.unbounded = true;
-      any_done = true;
-    } else if (lp_total(p, k) == 0) {
+    } else if (!more) {
       L.phase = LP_WAIT;
     } else {
       ++nprop;
     }
   }
-  if (p->trace)
-    std::fprintf(stderr, "[psl] round %d: swept rows %lld nnz %lld, records %d, rows removed %d, "
-                 "bounds made finite %d, LPs propagating %d\n", R.round, (long long)p->cur.rows,
-                 (long long)p->cur.nnz, p->hflags->round_total, removed, p->hflags->fin_cols, nprop);
-  if (nprop == 0) {
-    rounds_end(p);
-    return PSL_OK;
-  }
-  if (p->K > 1 && any_done) {
-    psl_status e = drop_done_lps(p);
-    if (e != PSL_OK) return e;
-  }
-  use_view(p, view_of(p->bins_s, p->chunks_s, p->hflags->sel));
-  if (++R.r < p->s.max_rounds) R.unit = U_ROUND;
+  // (an LP found infeasible or unbounded has left lp_ok on the device)
+  if (nprop > 0 && R.r < p->s.max_rounds) R.unit = U_ROUND;
   else rounds_end(p);
   return PSL_OK;
 }
@@ -1230,9 +1209,9 @@ static psl_status launch_pass(psl_presolver* p) {
       ++p->lst[k].rounds;
       if (p->K > 1) p->h_round[k] = p->lst[k].rounds;
     }
-  psl_status e = use_full_view(p);
+  use_full_view(p);
   // row records, then column records (and a substitution pass's)
-  if (e == PSL_OK) e = ensure_capacity(p, pass_records(&s, m, n));
+  psl_status e = ensure_capacity(p, pass_records(&s, m, n));
   if (e == PSL_OK) e = begin_lp_round(p);
   if (e != PSL_OK) return e;
   HIPCHK(p, hipEventRecord(p->ev[4], st));
@@ -1258,8 +1237,8 @@ static psl_status launch_pass(psl_presolver* p) {
   if (s.enable_doubletons) {
     // active lengths and removed-column constants after the parallel
     // passes (row_out), then the substitutions
-    launch_long_stats(d, MODE_COMPACT, st);
-    launch_sweep(d, p->grid, MODE_COMPACT, st);
+    launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, st);
+    launch_sweep(d, p->grid, MODE_COMPACT, 0, st);
     launch_doubletons(d, p->dbl, p->rec_count - p->rec_flushed, R.round, p->ws, st);
   }
   HIPCHK(p, hipEventRecord(p->ev[5], st));
@@ -1283,6 +1262,7 @@ static psl_status complete_pass(psl_presolver* p) {
     p->cmp.colid = p->colid;
     d.colid = p->colid;
     list_dense_cols(d, st);
+    p->dense = true;  // a kept column may have grown
     launch_doubleton_relock(d, p->dbl, st);
     S.alg_bytes += 36.0 * (double)p->nnz;
   }
@@ -1329,12 +1309,11 @@ static psl_status launch_compact(psl_presolver* p) {
     for (int k = 0; k < K; ++k) p->h_ok[k] = !p->lst[k].infeasible && !p->lst[k].unbounded;
     HIPCHK(p, hipMemcpyAsync(p->lp_ok, p->h_ok, K, hipMemcpyHostToDevice, st));
   }
-  psl_status e = use_full_view(p);
-  if (e != PSL_OK) return e;
   HIPCHK(p, hipEventRecord(p->ev[4], st));
   if (!R.consts_current) {
-    launch_long_stats(d, MODE_COMPACT, st);
-    launch_sweep(d, p->grid, MODE_COMPACT, st);
+    use_full_view(p);
+    launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, st);
+    launch_sweep(d, p->grid, MODE_COMPACT, 0, st);
   }
   compact_flags(d, p->cmp, st);
   compact_write(d, p->cmp, p->red, p->obj_offset, st);

@@ -12,6 +12,9 @@
 #include "sweep.h"
 
 using psl::BinEnt;
+using psl::RoundMode;
+using psl::SEL_CHUNKS;
+using psl::SelCnt;
 using psl::CompactScratch;
 using psl::Flags;
 using psl::IngestScratch;
@@ -28,14 +31,6 @@ using psl::Record;
 using psl::Reduced;
 using psl::SweepGrid;
 
-struct View {
-  BinEnt* bins = nullptr;
-  LongChunk* chunks = nullptr;
-  int32_t off[NBINS + 1] = {0};
-  int32_t nchunks = 0;
-  int64_t rows = 0, nnz = 0;
-};
-
 // host state of one LP of a batch
 enum : uint8_t { LP_PROP = 0, LP_WAIT = 1, LP_DONE = 2 };
 struct LpState {
@@ -48,14 +43,19 @@ struct LpState {
 // asynchronous reads of their results, on the engine's stream) and one
 // completion (the wait for those reads, then the host's decisions): round 0,
 // the propagation rounds of each outer cycle, each cycle's reduction pass, the
-// compaction. psl_presolve_run runs them back to back; a stepped server
-// interleaves the units of several batches.
+// compaction. A rounds unit queues several rounds (the device ends them when
+// nothing is left to do). psl_presolve_run runs the units back to back; a
+// stepped server interleaves the units of several batches, a round each.
 enum EngUnit { U_ROUND0 = 0, U_ROUND = 1, U_PASS = 2, U_COMPACT = 3, U_DONE = 4 };
 struct EngRun {
   int unit = U_DONE;               // the unit the next launch starts
   int outer = 0, r = 0, round = 0;  // cycle, round in the cycle, rounds so far
   bool consts_current = false;     // row_out current for the compaction
   bool any_feasible = false;       // the compaction unit has work
+  int queued = 0;                  // rounds of the running unit
+  int64_t rows_before = 0;         // rows swept before the unit
+  int seq = 0;                     // launch number of the last round queued
+  bool own = false;                // the next round takes a round's selection (else every row)
   double sweep_ms = 0.0, decide_ms = 0.0, par_ms = 0.0, long_ms = 0.0, cmp_ms = 0.0;
   psl_stats S{};
 };
@@ -86,7 +86,6 @@ struct psl_presolver {
   int64_t* h_z0 = nullptr;
   uint8_t* h_ok = nullptr;
   LpFlags* h_lpf = nullptr;
-  LpOut* h_lpo = nullptr;
   LpTab* h_lpt = nullptr;
   LpRed* h_lpr = nullptr;
   LpDesc* h_desc = nullptr;
@@ -121,14 +120,14 @@ struct psl_presolver {
   SweepGrid grid{};
   int64_t chunk_cap = 0, long_cap = 0, cand_cap = 0;
   int32_t* cand_cnt = nullptr;
-  // bin views: a full view holds every active row (of an LP still
-  // presolving); a round's selection the rows the device chose for it
+  // selections: the full one holds every active row (of an LP still
+  // presolving), a round's the rows the device chose for it (their counts in
+  // the flag block)
   BinEnt *bins_a = nullptr, *bins_s = nullptr;
   LongChunk *chunks_a = nullptr, *chunks_s = nullptr;
-  uint8_t* sel_keep = nullptr;   // per-row decisions of the row selection
-  int32_t* sel_cnt = nullptr;    // its per-tile counts / offsets
-  int32_t* sel_dev = nullptr;    // [NBINS+1] offsets, rows, nonzeros, chunks of a full view
-  View cur;
+  bool dense = false;            // the LP may have columns of more than MARK_DENSE entries
+  bool step_rounds = false;      // a unit is one round (stepped server)
+  double tick_ms = 1e-5;         // a tick of the device's clock
 
   // records
   Record* rec = nullptr;

@@ -296,29 +296,24 @@ void build_long_chunks(const Dev& d, int npass0, LongChunk* chunks, int32_t* cnt
 // ---------------------------------------------------------------------------
 // row selection: the rows a round sweeps, as bin lists and long-row chunks
 // ---------------------------------------------------------------------------
-// A pass over all rows in tiles of SEL_TILE (SEL_ITEMS a thread, striped so
-// the loads coalesce): a first launch takes each row's decision (one byte:
-// 0, or 1 + its bin) and counts, per tile, the kept rows of every bin, the
-// chunks of the kept long rows and the kept nonzeros; one scan of the counts
-// (bin-major) gives every tile its output offsets; a second launch writes the
-// kept rows in row order into contiguous bins and copies the kept long rows'
-// chunks from the ingest chunk table. The row data of a row is read only
-// when its cheap tests (active; marked, when only marked rows are wanted)
-// pass, so a selection of few marked rows reads about a byte per row.
+// One pass over the rows in tiles, four a thread (striped, so the loads
+// coalesce). A row is kept when it is active, its LP still presolving and, by
+// the mode, marked / not inert; the row data of a row is read only when its
+// cheap tests pass, so a selection of few marked rows reads about a byte per
+// row. A tile's kept rows are counted per bin by ballots and take their place
+// in the bins' lists with one atomic add per bin: a tile's rows stay together
+// and in row order, whose place in the list is of no consequence (candidates
+// fold by maximum and minimum, their sources by the lowest position). A tile
+// is 1024 rows, 4096 from SEL_BIG rows on (fewer adds to each count).
 #define SEL_ITEMS 4
-#define SEL_TILE (PSL_BLOCK * SEL_ITEMS)
-static_assert(SEL_TILE == 1024, "a selection tile is a tile of the marks");
-#define SEL_COUNTS (NBINS + 2)  // rows per bin, long-row chunks, nonzeros
-
-size_t select_keep_bytes(int64_t m) { return (size_t)(m + 2 * SEL_TILE); }
-size_t select_count_ints(int64_t m) { return (size_t)(SEL_COUNTS * ((m + SEL_TILE - 1) / SEL_TILE + 1) + 2); }
+#define SEL_BIG (1 << 20)
 
 struct SelArgs {
-  const int32_t* mode_dev;  // the device's mode (bit 0: marked rows only; bit 1:
-  int mode_host;            // inert rows skipped), or mode_host without one
-  int t_long, t_g8;         // bin thresholds of the ingest
-  uint8_t* keep;            // per row: 0, or 1 + its bin
-  int32_t* cnt;             // SEL_COUNTS * T + 1 counts, scanned in place
+  int mode;             // -1: the device's (bit 0: marked rows only; bit 1: inert rows skipped)
+  int t_long, t_g8;     // bin thresholds of the ingest
+  int64_t need;         // control: records a round may add
+  int last;             // control: no round is queued after this one
+  int seq;              // launch number of the round (control)
 };
 
 // bin of a row of len entries (the bins of the ingest)
@@ -338,358 +333,184 @@ __device__ __forceinline__ int long_row_index(const Dev& d, int row) {
   return lo;
 }
 
-__device__ __forceinline__ int sel_mode(const SelArgs& a) { return a.mode_dev ? *a.mode_dev : a.mode_host; }
-
-__global__ void __launch_bounds__(PSL_BLOCK) k_sel_count(Dev d, SelArgs a, int T) {
-  __shared__ int red[PSL_BLOCK / PSL_WAVE][SEL_COUNTS];
-  int tile = blockIdx.x;
-  int mode = sel_mode(a);
-  int c[SEL_COUNTS];
-#pragma unroll
-  for (int j = 0; j < SEL_COUNTS; ++j) c[j] = 0;
-  // marked rows only: a tile without a mark keeps nothing (its keep bytes
-  // are not read)
-  if ((mode & 1) && tile < T && !d.dirty_tile[tile]) {
-    if (threadIdx.x < SEL_COUNTS) a.cnt[(int64_t)threadIdx.x * T + tile] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.cnt[(int64_t)SEL_COUNTS * T] = 0;
-    return;
-  }
-  if (tile < T) {
-    // level by level for all items, without branches around the loads (a
-    // row that fails the cheap tests reads row 0's data, which is cached)
-    int64_t i[SEL_ITEMS];
-    bool cand[SEL_ITEMS];
-#pragma unroll
-    for (int k = 0; k < SEL_ITEMS; ++k) {
-      i[k] = (int64_t)tile * SEL_TILE + k * PSL_BLOCK + threadIdx.x;
-      int64_t ii = i[k] < d.m ? i[k] : 0;
-      uint8_t on = d.row_on[ii], dt = d.dirty[ii];
-      cand[k] = i[k] < d.m && on != 0 && (!(mode & 1) || dt != 0);
+// The round's control, one workgroup beside the selection's: its records and
+// clock ticks added up, each LP's state after it (d.lp_round: the number of
+// the LP's next round while it propagates, minus its last one once it does
+// not), and the end of the rounds: no LP goes on, or the record buffer might
+// not hold another round.
+__device__ __forceinline__ void round_control(const Dev& d, const SelArgs& a) {
+  __shared__ int go_on;
+  if (threadIdx.x == 0) go_on = 0;
+  __syncthreads();
+  Flags& f = *d.flags;
+  if (d.K == 1) {
+    if (threadIdx.x == 0) go_on = !f.infeasible && !f.unbounded && f.round_total != 0;
+  } else {
+    bool any = false;
+    for (int k = threadIdx.x; k < d.K; k += blockDim.x) {
+      int r = d.lp_round_mut[k];
+      if (r <= 0) continue;
+      bool more = !d.lpf[k].infeasible && !d.lpf[k].unbounded && d.lpo[k].total != 0;
+      d.lpo[k].total = 0;
+      d.lp_round_mut[k] = more ? r + 1 : -r;
+      any = any || more;
     }
-    int r0[SEL_ITEMS], r1[SEL_ITEMS], lpi[SEL_ITEMS];
-    int2 rf[SEL_ITEMS];
-    double lh[SEL_ITEMS], rh[SEL_ITEMS];
-#pragma unroll
-    for (int k = 0; k < SEL_ITEMS; ++k) {
-      int64_t jj = cand[k] ? i[k] : 0;
-      r0[k] = d.rp[jj];
-      r1[k] = d.rp[jj + 1];
-      lpi[k] = d.K > 1 ? d.row_lp[jj] : 0;
-      if (mode & 2) {
-        rf[k] = d.rinf[jj];
-        lh[k] = d.lhs[jj];
-        rh[k] = d.rhs[jj];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < SEL_ITEMS; ++k) {
-      bool keep = cand[k];
-      if (d.K > 1) keep = keep && d.lp_ok[lpi[k]] != 0;
-      if (mode & 2) keep = keep && !row_inert(rf[k], lh[k], rh[k]);
-      uint8_t kb = 0;
-      if (keep) {
-        int len = r1[k] - r0[k];
-        int bin = bin_of_len(len, a.t_long, a.t_g8);
-        kb = (uint8_t)(1 + bin);
-#pragma unroll
-        for (int b = 0; b < NBINS; ++b) c[b] += bin == b;
-        if (bin == BIN_LONG) c[NBINS] += d.lrow[long_row_index(d, (int)i[k])].nchunk;
-        c[NBINS + 1] += len;
-      }
-      a.keep[(int64_t)tile * SEL_TILE + k * PSL_BLOCK + threadIdx.x] = kb;
-    }
-  }
-  int w = threadIdx.x >> 6;
-  // a tile without kept rows (most tiles of a round that sweeps few marked
-  // rows) writes zeros without the reductions
-  if (!__syncthreads_or(c[NBINS + 1] != 0 || c[BIN_G4] + c[BIN_G8] + c[BIN_G16] + c[BIN_W1] + c[BIN_W4] + c[BIN_W8] +
-                                                    c[BIN_LONG] != 0)) {
-    if (threadIdx.x < SEL_COUNTS && tile < T) a.cnt[(int64_t)threadIdx.x * T + tile] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.cnt[(int64_t)SEL_COUNTS * T] = 0;
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < SEL_COUNTS; ++j) {
-    int x = c[j];
-#pragma unroll
-    for (int o = 1; o < PSL_WAVE; o <<= 1) x += __shfl_xor(x, o, PSL_WAVE);
-    if (lane_id() == 0) red[w][j] = x;
+    if (any) go_on = 1;
   }
   __syncthreads();
-  if (threadIdx.x < SEL_COUNTS && tile < T) {
-    int x = 0;
-#pragma unroll
-    for (int v = 0; v < PSL_BLOCK / PSL_WAVE; ++v) x += red[v][threadIdx.x];
-    a.cnt[(int64_t)threadIdx.x * T + tile] = x;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.cnt[(int64_t)SEL_COUNTS * T] = 0;
+  if (threadIdx.x != 0) return;
+  f.rounds_done += 1;
+  f.rec_at += f.round_total;
+  unsigned long long now = wall_clock64();
+  f.ticks[0] += f.stamp[1] - f.stamp[0];
+  f.ticks[1] += f.stamp[2] - f.stamp[1];
+  f.ticks[2] += now - f.stamp[2];
+  if (!go_on || (!a.last && f.rec_at + a.need > f.rec_cap)) f.stop_at = a.seq;
 }
 
-// out: bin lists; cout: chunk list; sel: offsets [0..NBINS], rows, nonzeros,
-// chunks. Kept rows are swept now: their marks are cleared.
-__global__ void __launch_bounds__(PSL_BLOCK) k_sel_scatter(Dev d, SelArgs a, int T, BinEnt* out, LongChunk* cout,
-                                                           int32_t* sel) {
-  __shared__ int wc[SEL_ITEMS][NBINS + 1][PSL_BLOCK / PSL_WAVE];  // per item row, bin (and chunks), wave
-  const int32_t* off = a.cnt;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    int64_t R = (int64_t)NBINS * T, C = (int64_t)(NBINS + 1) * T, Z = (int64_t)(NBINS + 2) * T;
-    for (int b = 0; b < NBINS; ++b) sel[b] = off[(int64_t)b * T];
-    sel[NBINS] = off[R];
-    sel[NBINS + 1] = off[R];
-    sel[NBINS + 2] = off[Z] - off[C];
-    sel[NBINS + 3] = off[C] - off[R];
-  }
-  int tile = blockIdx.x;
-  if (tile >= T) return;
+template <int BS>
+__global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, int T, BinEnt* out, LongChunk* cout, SelCnt* cnt) {
+  constexpr int W = BS / PSL_WAVE;
+  constexpr int MARKS = BS * SEL_ITEMS / 1024;  // tiles of the marks in one of ours
+  __shared__ int wc[SEL_ITEMS][NBINS][W];       // per item row and bin: each wavefront's rows
+  __shared__ int at[NBINS];
+  __shared__ int wz[W];
   __shared__ int marked;
-  if (threadIdx.x == 0) {
-    marked = d.dirty_tile[tile];
-    d.dirty_tile[tile] = 0;  // the tile's marks are taken now (rows not kept keep
-                             // theirs, harmlessly: a change marks them again)
+  const int tile = blockIdx.x;
+  const bool next = a.mode < 0;
+  if (next && round_over(d, a.seq)) return;
+  if (tile == T) {
+    round_control(d, a);
+    return;
+  }
+  const int mode = next ? d.flags->mode : a.mode;
+  if (threadIdx.x == 0) marked = 0;
+  __syncthreads();
+  if (threadIdx.x < MARKS) {
+    int64_t x = (int64_t)tile * MARKS + threadIdx.x;
+    if (x <= d.m / 1024 && d.dirty_tile[x]) {
+      marked = 1;
+      d.dirty_tile[x] = 0;  // the tile's marks are taken now (rows not kept keep
+                            // theirs, harmlessly: a change marks them again)
+    }
   }
   __syncthreads();
-  if ((sel_mode(a) & 1) && !marked) return;
-  int w = threadIdx.x >> 6;
-  int kb[SEL_ITEMS], nch[SEL_ITEMS], pre[SEL_ITEMS], cpre[SEL_ITEMS], r0[SEL_ITEMS], r1[SEL_ITEMS];
-  int64_t row[SEL_ITEMS];
-  bool any = false;
+  if ((mode & 1) && !marked) return;
+  const int w = threadIdx.x >> 6;
+  const int64_t t0 = (int64_t)tile * BS * SEL_ITEMS + threadIdx.x;
+  // level by level for all items, without branches around the loads (a row
+  // that fails the cheap tests reads row 0's data, which is cached)
+  bool keep[SEL_ITEMS];
 #pragma unroll
   for (int k = 0; k < SEL_ITEMS; ++k) {
-    row[k] = (int64_t)tile * SEL_TILE + k * PSL_BLOCK + threadIdx.x;
-    kb[k] = a.keep[row[k]];
-    any |= kb[k] != 0;
+    int64_t i = t0 + k * BS, ii = i < d.m ? i : 0;
+    uint8_t on = d.row_on[ii], dt = d.dirty[ii];
+    keep[k] = i < d.m && on != 0 && (!(mode & 1) || dt != 0);
   }
-  if (!__syncthreads_or(any)) return;  // nothing kept in this tile
+  int r0[SEL_ITEMS], len[SEL_ITEMS], lpi[SEL_ITEMS];
+  int2 rf[SEL_ITEMS];
+  double lh[SEL_ITEMS], rh[SEL_ITEMS];
 #pragma unroll
   for (int k = 0; k < SEL_ITEMS; ++k) {
-    int64_t jj = kb[k] ? row[k] : 0;  // a row not kept reads row 0 (cached)
+    int64_t jj = keep[k] ? t0 + k * BS : 0;
     r0[k] = d.rp[jj];
-    r1[k] = d.rp[jj + 1];
+    len[k] = d.rp[jj + 1] - r0[k];
+    lpi[k] = d.K > 1 ? d.row_lp[jj] : 0;
+    if (mode & 2) {
+      rf[k] = d.rinf[jj];
+      lh[k] = d.lhs[jj];
+      rh[k] = d.rhs[jj];
+    }
   }
+  int bin[SEL_ITEMS], pre[SEL_ITEMS];
+  int z = 0;
 #pragma unroll
   for (int k = 0; k < SEL_ITEMS; ++k) {
-    nch[k] = 0;
-    if (kb[k] == 1 + BIN_LONG) nch[k] = d.lrow[long_row_index(d, (int)row[k])].nchunk;
-    // rank among this wave's lanes of the same bin, and the chunk counts
-    // before this lane in the wave (inclusive scan minus own)
-    int b = kb[k] - 1;
+    if (d.K > 1) keep[k] = keep[k] && d.lp_ok[lpi[k]] != 0;
+    if (mode & 2) keep[k] = keep[k] && !row_inert(rf[k], lh[k], rh[k]);
+    bin[k] = keep[k] ? bin_of_len(len[k], a.t_long, a.t_g8) : -1;
+    z += keep[k] ? len[k] : 0;
     pre[k] = 0;
 #pragma unroll
-    for (int bb = 0; bb < NBINS; ++bb) {
-      unsigned long long bal = __ballot(b == bb);
-      if (b == bb) pre[k] = __popcll(bal & lanemask_lt());
-      if (lane_id() == 0) wc[k][bb][w] = __popcll(bal);
+    for (int b = 0; b < NBINS; ++b) {
+      unsigned long long bal = __ballot(bin[k] == b);
+      if (bin[k] == b) pre[k] = __popcll(bal & lanemask_lt());
+      if (lane_id() == 0) wc[k][b][w] = __popcll(bal);
     }
-    int x = nch[k];
-#pragma unroll
-    for (int o = 1; o < PSL_WAVE; o <<= 1) {
-      int y = __shfl_up(x, o, PSL_WAVE);
-      if (lane_id() >= o) x += y;
-    }
-    cpre[k] = x - nch[k];
-    if (lane_id() == PSL_WAVE - 1) wc[k][NBINS][w] = x;
   }
+#pragma unroll
+  for (int o = 1; o < PSL_WAVE; o <<= 1) z += __shfl_xor(z, o, PSL_WAVE);
+  if (lane_id() == 0) wz[w] = z;
   __syncthreads();
-  // exclusive prefix of every (item row, wave) count in row order, per bin
-  // (and for the chunks): one thread per bin
-  if (threadIdx.x <= NBINS) {
+  // one thread per bin: the exclusive prefix of every (item row, wavefront)
+  // count in row order, then the tile's place in the bin's list
+  if (threadIdx.x < NBINS) {
     int run = 0;
 #pragma unroll
-    for (int kk = 0; kk < SEL_ITEMS; ++kk)
-#pragma unroll
-      for (int v = 0; v < PSL_BLOCK / PSL_WAVE; ++v) {
-        int x = wc[kk][threadIdx.x][v];
-        wc[kk][threadIdx.x][v] = run;
+    for (int k = 0; k < SEL_ITEMS; ++k)
+      for (int v = 0; v < W; ++v) {
+        int x = wc[k][threadIdx.x][v];
+        wc[k][threadIdx.x][v] = run;
         run += x;
       }
+    at[threadIdx.x] = run ? atomicAdd(&cnt[threadIdx.x].v, run) : 0;
+  } else if (threadIdx.x == PSL_WAVE) {
+    int s = 0;
+    for (int v = 0; v < W; ++v) s += wz[v];
+    if (s) atomicAdd(&cnt[SEL_NNZ].v, s);
   }
   __syncthreads();
-  int cbase = off[(int64_t)NBINS * T + tile] - off[(int64_t)NBINS * T];
 #pragma unroll
   for (int k = 0; k < SEL_ITEMS; ++k) {
-    int b = kb[k] - 1;
-    if (b < 0) continue;
-    int64_t i = row[k];
-    int start = r0[k];
-    int len = r1[k] - start;
-    out[off[(int64_t)b * T + tile] + wc[k][b][w] + pre[k]] = BinEnt{(int)i, start, len, 0};
+    if (!keep[k]) continue;
+    const int i = (int)(t0 + k * BS), b = bin[k];
+    out[d.bin_off[b] + at[b] + wc[k][b][w] + pre[k]] = BinEnt{i, r0[k], len[k], 0};
     d.dirty[i] = 0;
-    if (nch[k]) {
-      LongRow lr = d.lrow[long_row_index(d, (int)i)];
-      int cb = wc[k][NBINS][w] + cpre[k];
-      for (int c = 0; c < lr.nchunk; ++c) cout[cbase + cb + c] = d.chunks0[lr.chunk0 + c];
+    if (b == BIN_LONG) {
+      LongRow lr = d.lrow[long_row_index(d, i)];
+      int c0 = atomicAdd(&cnt[SEL_CHUNKS].v, lr.nchunk);
+      for (int c = 0; c < lr.nchunk; ++c) cout[c0 + c] = d.chunks0[lr.chunk0 + c];
     }
   }
 }
 
-void select_rows(const Dev& d, const int32_t* mode_dev, int mode_host, int t_long, int t_g8, uint8_t* keep,
-                 int32_t* cnt, BinEnt* out, LongChunk* cout, int32_t* sel, int32_t* ws, hipStream_t s) {
-  SelArgs a{mode_dev, mode_host, t_long, t_g8, keep, cnt};
-  int T = (int)((d.m + SEL_TILE - 1) / SEL_TILE);
-  unsigned grid = (unsigned)(T > 0 ? T : 1);
-  hipLaunchKernelGGL(k_sel_count, dim3(grid), dim3(PSL_BLOCK), 0, s, d, a, T);
-  scan_excl(cnt, cnt, (int64_t)SEL_COUNTS * T + 1, nullptr, ws, s);
-  hipLaunchKernelGGL(k_sel_scatter, dim3(grid), dim3(PSL_BLOCK), 0, s, d, a, T, out, cout, sel);
-}
-
-// Rows of the columns whose bounds changed (or that were fixed) this round,
-// from the transposed copy; their infinite-contribution counts follow the
-// bounds that became finite. One wavefront per 64 columns walks the entries of
-// its changed columns; columns of more than MARK_DENSE entries (listed once
-// at ingest) are walked by every workgroup of a second launch.
-#define MARK_DENSE 4096
-#define MARK_SHORT 16
-#define MARK_MASK (CC_LB | CC_UB | CC_FIX)
-
-// One entry (q, row i) of a changed column: mark the row (when the next
-// round sweeps dirty rows only), and (with count) lower its infinite-
-// contribution counts when the column's lb / ub became finite.
-__device__ __forceinline__ void mark_entry(const Dev& d, int64_t q, int code, bool mark, bool count) {
-  int i = d.ri[q];
-  if (mark) {
-    d.dirty[i] = 1;
-    d.dirty_tile[i >> 10] = 1;
-  }
-  if (count && (code & (CC_LBFIN | CC_UBFIN))) {
-    bool pos = d.cva[q] > 0;
-    bool lbf = (code & CC_LBFIN) != 0, ubf = (code & CC_UBFIN) != 0;
-    if ((lbf && pos) || (ubf && !pos)) atomicSub(&d.rinf[i].x, 1);  // min contribution now finite
-    if ((lbf && !pos) || (ubf && pos)) atomicSub(&d.rinf[i].y, 1);  // max contribution now finite
+static void launch_select(const Dev& d, const SelArgs& a, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s) {
+  const int extra = a.mode < 0 ? 1 : 0;  // the control's workgroup
+  if (d.m >= SEL_BIG) {
+    int T = (d.m + 1024 * SEL_ITEMS - 1) / (1024 * SEL_ITEMS);
+    hipLaunchKernelGGL(k_select<1024>, dim3(T + extra), dim3(1024), 0, s, d, a, T, out, cout, cnt);
+  } else {
+    int T = (d.m + PSL_BLOCK * SEL_ITEMS - 1) / (PSL_BLOCK * SEL_ITEMS);
+    if (T + extra > 0) hipLaunchKernelGGL(k_select<PSL_BLOCK>, dim3(T + extra), dim3(PSL_BLOCK), 0, s, d, a, T, out, cout, cnt);
   }
 }
 
-// columns the marking pass walks: changed ones when rows are marked, those
-// with a bound that became finite when counts are kept
-__device__ __forceinline__ bool mark_col(int code, int mode) {
-  return ((mode & 1) && (code & MARK_MASK)) || ((mode & 2) && (code & (CC_LBFIN | CC_UBFIN)));
+void select_all(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s) {
+  fill_i32(&cnt[0].v, 0, (int64_t)SEL_N * (sizeof(SelCnt) / sizeof(int32_t)), s);
+  launch_select(d, SelArgs{0, t_long, t_g8, 0, 1, 0}, out, cout, cnt, s);
 }
 
-// The next round's selection mode from this round's totals (bit 0: sweep only
-// the rows touched by a change, when few columns changed and allow is set;
-// bit 1: keep the infinite-contribution counts, when few bounds became finite)
-struct RoundMode {
-  int allow, incr_factor, count_factor;
-};
-
-__device__ __forceinline__ int round_mode(const Dev& d, const RoundMode& rm) {
-  int64_t changed = (int64_t)d.flags->round_total - d.flags->rows_removed;
-  bool incr = rm.allow && changed * rm.incr_factor < (int64_t)d.n;
-  bool counts = (int64_t)d.flags->fin_cols * rm.count_factor < (int64_t)d.n;
-  return (incr ? 1 : 0) | (counts ? 2 : 0);
+void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int64_t need,
+                 bool last, int seq, hipStream_t s) {
+  launch_select(d, SelArgs{-1, t_long, t_g8, need, last ? 1 : 0, seq}, out, cout, cnt, s);
 }
 
-// exclusive prefix (lanes below) and total of per-lane values 0..31 across
-// the wavefront, from one ballot per bit
-__device__ __forceinline__ void wave_scan5(int v, int& pre, int& tot) {
-  unsigned long long below = lanemask_lt();
-  pre = tot = 0;
-#pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    unsigned long long m = __ballot((v >> b) & 1);
-    pre += __popcll(m & below) << b;
-    tot += __popcll(m) << b;
+__global__ void k_rounds_begin(Dev d, int64_t rec_at, int64_t rec_cap) {
+  int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k == 0) {
+    d.flags->rec_at = rec_at;
+    d.flags->rec_cap = rec_cap;
+    d.flags->stop_at = 0x7FFFFFFF;
+  }
+  if (d.K > 1 && k < d.K) {
+    d.lpf[k] = LpFlags{0, 0, 0, 0};
+    d.lpo[k] = LpOut{0, 0};
   }
 }
 
-// A lane reads the codes of MARK_COLS consecutive columns as one word (the
-// code array is 256-byte aligned and padded, so a word starting below n stays
-// inside it); the wavefront's columns to walk are listed in LDS and taken 64
-// at a time, one per lane.
-#define MARK_COLS 4
-#define MARK_TILE (PSL_BLOCK * MARK_COLS)
-
-__global__ void __launch_bounds__(PSL_BLOCK) k_mark_sparse(Dev d, RoundMode rm) {
-  int mode = round_mode(d, rm);
-  if (blockIdx.x == 0 && threadIdx.x == 0) d.flags->mode = mode;
-  if (mode == 0) return;
-  __shared__ int32_t list[MARK_TILE];
-  int lane = lane_id();
-  int32_t* wl = list + (threadIdx.x >> 6) * (PSL_WAVE * MARK_COLS);
-  int64_t j0 = (int64_t)blockIdx.x * MARK_TILE + (int64_t)threadIdx.x * MARK_COLS;
-  uint32_t cw = 0;
-  if (j0 < d.n) {
-    int64_t rem = d.n - j0;
-    cw = reinterpret_cast<const uint32_t*>(d.col_code)[j0 >> 2];
-    if (rem < 4) cw &= (1u << (8 * (int)rem)) - 1u;
-  }
-  int nm = 0;
-#pragma unroll
-  for (int b = 0; b < MARK_COLS; ++b) nm += mark_col((cw >> (8 * b)) & 0xFF, mode);
-  int mpre, mtot;
-  wave_scan5(nm, mpre, mtot);
-#pragma unroll
-  for (int b = 0; b < MARK_COLS; ++b)
-    if (mark_col((cw >> (8 * b)) & 0xFF, mode)) wl[mpre++] = (int32_t)(j0 + b);
-  __syncthreads();
-  for (int c0 = 0; c0 < mtot; c0 += PSL_WAVE) {
-    int q0 = 0, q1 = 0, code = 0;
-    if (c0 + lane < mtot) {
-      int j = wl[c0 + lane];
-      code = d.col_code[j];
-      q0 = d.cp[j];
-      q1 = d.cp[j + 1];
-    }
-    int len = q1 - q0;
-    // short columns: the entries of the lanes' columns, concatenated in
-    // column order, one per lane (a column's entries are contiguous, so the
-    // row-index loads of a step touch a few lines, and no lane walks a
-    // column alone)
-    int sl = len <= MARK_SHORT ? len : 0;
-    int pre, tot;
-    wave_scan5(sl, pre, tot);
-    for (int e0 = 0; e0 < tot; e0 += PSL_WAVE) {
-      int e = e0 + lane;
-      // the entry's column: the last lane whose prefix is <= e
-      int lo = 0, hi = PSL_WAVE - 1;
-#pragma unroll
-      for (int it = 0; it < 6; ++it) {
-        int mid = (lo + hi + 1) >> 1;
-        bool le = __shfl(pre, mid, PSL_WAVE) <= e;
-        lo = le ? mid : lo;
-        hi = le ? hi : mid - 1;
-      }
-      int q = __shfl(q0, lo, PSL_WAVE) + (e - __shfl(pre, lo, PSL_WAVE));
-      int cl = __shfl(code, lo, PSL_WAVE);
-      if (e < tot) mark_entry(d, q, cl, mode & 1, mode & 2);
-    }
-    // longer ones: the wavefront walks them one after another
-    unsigned long long mask = __ballot(len > MARK_SHORT && len <= MARK_DENSE);
-    while (mask) {
-      int l = __ffsll((long long)mask) - 1;
-      mask &= mask - 1;
-      int a = __shfl(q0, l, PSL_WAVE), b = __shfl(q1, l, PSL_WAVE), cl = __shfl(code, l, PSL_WAVE);
-      for (int q = a + lane; q < b; q += PSL_WAVE) mark_entry(d, q, cl, mode & 1, mode & 2);
-    }
-  }
-}
-
-// every workgroup lists the changed dense columns (in slices of 1024, checked
-// in parallel) and walks a grid-strided share of their entries
-__global__ void __launch_bounds__(PSL_BLOCK) k_mark_dense(Dev d, RoundMode rm) {
-  __shared__ int32_t list[1024];
-  __shared__ int32_t cnt;
-  int mode = round_mode(d, rm);
-  if (mode == 0) return;
-  int nd = *d.n_dense;
-  for (int k0 = 0; k0 < nd; k0 += 1024) {
-    if (threadIdx.x == 0) cnt = 0;
-    __syncthreads();
-    for (int k = k0 + threadIdx.x; k < nd && k < k0 + 1024; k += PSL_BLOCK) {
-      int j = d.dense_cols[k];
-      if (mark_col(d.col_code[j], mode)) list[atomicAdd(&cnt, 1)] = j;
-    }
-    __syncthreads();
-    int nc = cnt;
-    for (int c = 0; c < nc; ++c) {
-      int j = list[c];
-      int code = d.col_code[j];
-      int64_t q1 = d.cp[j + 1];
-      for (int64_t q = d.cp[j] + (int64_t)blockIdx.x * PSL_BLOCK + threadIdx.x; q < q1;
-           q += (int64_t)gridDim.x * PSL_BLOCK)
-        mark_entry(d, q, code, mode & 1, mode & 2);
-    }
-    __syncthreads();
-  }
+void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStream_t s) {
+  hipLaunchKernelGGL(k_rounds_begin, dim3((d.K + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d, rec_at,
+                     rec_cap);
 }
 
 // the columns of more than MARK_DENSE entries (order irrelevant)
@@ -705,17 +526,10 @@ void list_dense_cols(const Dev& d, hipStream_t s) {
     hipLaunchKernelGGL(k_dense_cols, dim3((unsigned)((d.n + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d);
 }
 
-void mark_dirty(const Dev& d, bool allow_incremental, int incr_factor, int count_factor, hipStream_t s) {
-  RoundMode rm{allow_incremental ? 1 : 0, incr_factor, count_factor};
-  unsigned blocks = (unsigned)((d.n + MARK_TILE - 1) / MARK_TILE);
-  hipLaunchKernelGGL(k_mark_sparse, dim3(blocks > 0 ? blocks : 1), dim3(PSL_BLOCK), 0, s, d, rm);
-  if (d.nnz > 0 && d.n > 0) hipLaunchKernelGGL(k_mark_dense, dim3(1024), dim3(PSL_BLOCK), 0, s, d, rm);
-}
-
 // ---------------------------------------------------------------------------
 // state initialisation and round 0 (input fixings, crossed bounds / sides)
 // ---------------------------------------------------------------------------
-__global__ void k_init_state(Dev d) {
+__global__ void k_init_state(Dev d, int64_t supers) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < d.m) {
     d.row_on[t] = 1;
@@ -743,7 +557,19 @@ __global__ void k_init_state(Dev d) {
     f.cand_count = f.round_total = f.vlist_count = f.rows_removed = 0;
     f.fin_cols = f.mode = f.lead_count = f.fs_total = f.fs_rows = f.fs_claims = 0;
     f.error_pos = 0x7FFFFFFFFFFFFFFFLL;
+    f.dbl_count = f.dbl_applied = 0;
+    f.stop_at = 0x7FFFFFFF;
+    f.rounds_done = 0;
+    f.rec_at = f.rec_cap = 0;
+    f.sum_rows = f.sum_nnz = f.sum_cols = 0;
+    for (int k = 0; k < 3; ++k) f.stamp[k] = f.ticks[k] = 0;
+    for (int k = 0; k < 2; ++k)
+      for (int b = 0; b < SEL_N; ++b) f.sel[k][b].v = 0;
     *d.flags = f;
+  }
+  if (t < supers) {
+    d.super[t] = 0;
+    d.super_done[t] = 0;
   }
 }
 
@@ -784,8 +610,9 @@ void init_locks(const Dev& d, int32_t* dn, int32_t* up, int32_t* ws, hipStream_t
 
 void launch_init_state(const Dev& d, hipStream_t s) {
   int64_t t = d.m > d.n ? d.m : d.n;
-  if (t < 1) t = 1;
-  hipLaunchKernelGGL(k_init_state, dim3((unsigned)((t + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d);
+  int64_t supers = (int64_t)decide_supers(d.m, d.n);
+  if (t < supers) t = supers;
+  hipLaunchKernelGGL(k_init_state, dim3((unsigned)((t + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d, supers);
 }
 
 __global__ void k_round0_count(Dev d) {

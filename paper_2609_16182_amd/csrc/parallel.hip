@@ -186,7 +186,8 @@ __global__ void k_par_reset(Dev d, ParScratch P) {
 template <int G, int REP>
 __device__ __forceinline__ void hash_groups(const Dev& d, const ParScratch& P, int bin, int lblock0) {
   const int per_block = PSL_BLOCK / G;
-  int count = d.bin_off[bin + 1] - d.bin_off[bin];
+  int count = d.sel[bin].v;
+  if (lblock0 * per_block >= count) return;  // uniform over the workgroup
   int gl = threadIdx.x & (G - 1);
   int row[REP], len[REP];
   int64_t p[REP];
@@ -367,7 +368,7 @@ __device__ __forceinline__ void hash_long_chunk(const Dev& d, const ParScratch& 
 // the wavefront rows of a row block (four per workgroup)
 __device__ __forceinline__ void hash_wave_block(const Dev& d, const ParScratch& P, int bin, int vb) {
   int wid = vb * (PSL_BLOCK / PSL_WAVE) + (threadIdx.x >> 6);
-  if (wid >= d.bin_off[bin + 1] - d.bin_off[bin]) return;
+  if (wid >= d.sel[bin].v) return;
   int row = d.bins[d.bin_off[bin] + wid].row;
   if (bin == BIN_W1) hash_wave_row<1>(d, P, row);
   else if (bin == BIN_W4) hash_wave_row<4>(d, P, row);
@@ -383,7 +384,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, Swe
       continue;
     }
     int rep = bin_rep(bin);
-    int count = d.bin_off[bin + 1] - d.bin_off[bin];
+    int count = d.sel[bin].v;
     if (bin == BIN_G4) hash_groups<4, 4>(d, P, bin, b * rep);
     else if (bin == BIN_G8) hash_groups<8, 4>(d, P, bin, b * rep);
     else if (bin == BIN_G16) hash_groups<16, 4>(d, P, bin, b * rep);
@@ -395,7 +396,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, Swe
       }
     return;
   }
-  if (b < g.nb[BIN_LONG]) hash_long_chunk(d, P, b);
+  if (b < d.sel[SEL_CHUNKS].v) hash_long_chunk(d, P, b);
 }
 
 __global__ void k_par_long_insert(Dev d, ParScratch P) {

@@ -103,21 +103,35 @@ struct LpOut {       // per LP: nonzero when the last round gave it records (cle
   int32_t total, pad;
 };
 
+// A count of a row selection, on a cache line of its own (every workgroup of
+// the selection adds to it).
+struct SelCnt {
+  int32_t v, pad[15];
+};
+// counts of a selection: rows per bin, long-row chunks, nonzeros
+enum { SEL_CHUNKS = NBINS, SEL_NNZ = NBINS + 1, SEL_N = NBINS + 2 };
+
 struct Flags {
   int32_t infeasible, unbounded, error, merged;
   int32_t cand_count, round_total, vlist_count, rows_removed;
   int32_t fin_cols;        // columns of the round with a bound that became finite
   int32_t mode;            // the next round's selection mode (bit 0: touched rows
-                           // only, bit 1: inert rows skipped), set after a round
+                           // only, bit 1: inert rows skipped), set with the decisions
   int64_t error_pos;
-  int32_t sel[NBINS + 4];  // the next round's selection: bin offsets [0..NBINS],
-                           // rows, their nonzeros, long-row chunks
   int32_t lead_count;      // parallel pass: leaders whose merged sides add locks
   int32_t fs_total;        // free singleton eliminations of the round
   int32_t fs_rows;         // chunks of long eliminated rows listed
   int32_t fs_claims;       // chunks of long substituting rows listed
   int32_t dbl_count;       // doubleton-equality candidates listed
   int32_t dbl_applied;     // a doubleton substitution was applied this pass
+  // rounds queued ahead of the host: a round's kernels do nothing when its
+  // number is above stop_at, which the last round's control sets
+  int32_t stop_at, rounds_done;
+  int64_t rec_at, rec_cap;           // next free record; records the buffer holds
+  int64_t sum_rows, sum_nnz, sum_cols;  // swept so far in the run: rows, nonzeros, columns at most
+  uint64_t stamp[3];       // clock at the round's long-row statistics, sweep, decisions
+  uint64_t ticks[3];       // clock ticks of those phases so far in the run
+  SelCnt sel[2][SEL_N];    // counts of the full view / of the rounds' selections
 };
 
 struct Cfg {
@@ -174,13 +188,20 @@ struct Dev {
   Flags *flags;
   int32_t *cnt, *off;
   Record *rec;
+  // the rows a launch takes: lists in fixed places (bin b's from bin_off[b], room
+  // for every row of the bin), their lengths in sel
   const BinEnt *bins;
   int32_t bin_off[NBINS + 1];
+  const SelCnt *sel;
   const LongChunk *lchunk;
   const LongChunk *chunks0;    // chunk table of all long rows (built at ingest)
   LongPart *lpart;
   LongRow *lrow;
-  int32_t nlong, nchunks;
+  int32_t nlong, nchunks;      // long rows and their chunks (of all rows)
+  // the decision tiles' sums: per 64 tiles the records and the columns with a
+  // bound made finite (low / high word), tiles done, and the records before
+  unsigned long long *super;
+  int32_t *super_done, *super_off;
   // batched presolve (K LPs); with K == 1 every row and column is in LP 0
   // and none of these arrays is read
   int32_t K;
@@ -189,6 +210,7 @@ struct Dev {
   uint8_t *lp_ok;                     // [K] LP still presolving (its rows stay in the bins;
                                       // cleared here when the LP stops)
   const int32_t *lp_round;            // [K] the LP's own number of the current round
+  int32_t *lp_round_mut;              // the same, moved on by a round's control
   LpFlags *lpf;                       // [K]
   LpOut *lpo;                         // [K]
   Cfg cfg;
@@ -198,6 +220,8 @@ __device__ __forceinline__ int row_lp_of(const Dev& d, int i) { return d.K > 1 ?
 __device__ __forceinline__ int col_lp_of(const Dev& d, int j) { return d.K > 1 ? d.col_lp[j] : 0; }
 // round number written into a record of LP lp
 __device__ __forceinline__ int round_of(const Dev& d, int lp, int round) { return d.K > 1 ? d.lp_round[lp] : round; }
+// the round with launch number seq is not run: an earlier one ended the rounds
+__device__ __forceinline__ bool round_over(const Dev& d, int seq) { return seq > d.flags->stop_at; }
 // an LP that stops leaves the next selection at once
 __device__ __forceinline__ void flag_infeasible(const Dev& d, int lp) {
   atomicOr(&d.flags->infeasible, 1);

@@ -3,7 +3,8 @@
 // Requests wait in a FIFO queue. A slot (a batch engine with its own arena,
 // stream and, in threaded mode, worker thread) takes every waiting LP from
 // the head of the queue that fits its capacity and whose reduced problem can
-// be reserved in the result heap, presolves them as one batch (every LP gets
+// be reserved in the result heap (after a moment for more, when small LPs come
+// quickly), presolves them as one batch (every LP gets
 // its alone result), then copies each reduced problem into its reserved block
 // with one scatter-copy launch and the records to the host. Slots run
 // concurrently, so requests that arrive while a batch is on the device start
@@ -210,6 +211,10 @@ struct psl_server {
   std::vector<std::unique_ptr<Slot>> slots;
   bool stop = false;
   int running = 0;
+  // the last arrivals' gaps (ms), for the admission of small LPs
+  Clock::time_point last_arrival{};
+  double gaps[8] = {0};
+  uint64_t ngaps = 0;
   size_t arena_bytes = 0;
   std::string err = "no error";
 };
@@ -426,6 +431,29 @@ static void finish_batch(psl_server* sv, Slot& sl, std::vector<Ticket*>& live) {
   }
 }
 
+// How long a free slot lets the queue grow before it takes a batch of less than
+// JOIN_NNZ nonzeros, while requests come quickly (the median of the last 8
+// gaps below JOIN_GAP_MS). The presolve of a small LP is one to two
+// milliseconds of launches whatever the batch holds, so a further LP in it is
+// nearly free, while one of its own takes a slot for as long.
+constexpr auto JOIN_WAIT = std::chrono::microseconds(400);
+constexpr int64_t JOIN_NNZ = 1000000;
+constexpr double JOIN_GAP_MS = 2.5;
+
+// the time to take a batch: at once unless small LPs come quickly (lock held,
+// queue not empty)
+static Clock::time_point admit_at(psl_server* sv) {
+  const Ticket* head = sv->tickets[sv->queue.front()].get();
+  if (sv->ngaps < 8 || (int64_t)sv->queue.size() >= sv->cfg.max_batch_lps) return head->arrival;
+  int64_t z = 0;
+  for (uint64_t id : sv->queue)
+    if ((z += sv->tickets[id]->lp.nnz) >= JOIN_NNZ) return head->arrival;
+  double g[8];
+  std::copy(sv->gaps, sv->gaps + 8, g);
+  std::nth_element(g, g + 4, g + 8);
+  return g[4] < JOIN_GAP_MS ? head->arrival + JOIN_WAIT : head->arrival;
+}
+
 static void worker(psl_server* sv, Slot* sl) {
   (void)hipSetDevice(sv->s.device);
   for (;;) {
@@ -434,6 +462,13 @@ static void worker(psl_server* sv, Slot* sl) {
       std::unique_lock<std::mutex> lk(sv->mu);
       for (;;) {
         if (sv->stop) return;
+        if (!sv->queue.empty()) {
+          Clock::time_point at = admit_at(sv);
+          if (Clock::now() < at) {
+            sv->cv_work.wait_until(lk, at);
+            continue;
+          }
+        }
         b = take_batch(sv);
         if (!b.empty()) break;
         sv->cv_work.wait(lk);
@@ -511,6 +546,7 @@ extern "C" psl_status psl_server_create(const psl_server_config* c, const psl_se
     psl_status st = PSL_OK;
     std::string err;
     sl->eng = engine_new(&es, c->max_batch_rows, c->max_batch_cols, c->max_batch_nnz, c->max_batch_lps, &st, &err);
+    if (sl->eng) sl->eng->step_rounds = !c->threaded;
     sl->seg_cap = 15 * (int64_t)c->max_batch_lps;
     bool ok = sl->eng != nullptr;
     if (ok) ok = hipMalloc((void**)&sl->segs_dev, sl->seg_cap * sizeof(CopySeg)) == hipSuccess;
@@ -561,6 +597,8 @@ extern "C" psl_status psl_server_submit(psl_server* sv, const psl_lp* lp, uint64
   t->lp = *lp;
   t->arrival = Clock::now();
   std::lock_guard<std::mutex> lk(sv->mu);
+  if (sv->next_id > 1) sv->gaps[sv->ngaps++ % 8] = ms_between(sv->last_arrival, t->arrival);
+  sv->last_arrival = t->arrival;
   t->id = sv->next_id++;
   *ticket = t->id;
   sv->queue.push_back(t->id);

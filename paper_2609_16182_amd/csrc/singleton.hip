@@ -51,7 +51,8 @@ __device__ __forceinline__ void fs_offer(const Dev& d, int j, int i) {
 // ones (a dense column down to one row) by the whole wavefront, one after
 // another, 64 positions a step
 #define FS_PICK_SHORT 64
-__global__ void __launch_bounds__(PSL_BLOCK) k_fs_pick(Dev d) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_fs_pick(Dev d, int seq) {
+  if (round_over(d, seq)) return;
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j == 0) d.flags->fs_claims = 0;
   bool want = false;
@@ -120,7 +121,8 @@ __device__ __forceinline__ unsigned long long fs_key(int round, int i) {
 
 // rows whose column has a cost: an infinite preferred side stops the LP;
 // otherwise they claim their columns (long rows through the claim list)
-__global__ void k_fs_claim(Dev d, int32_t* clist, int round) {
+__global__ void k_fs_claim(Dev d, int32_t* clist, int round, int seq) {
+  if (round_over(d, seq)) return;
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= d.m) return;
   int i = (int)t;
@@ -146,7 +148,8 @@ __global__ void k_fs_claim(Dev d, int32_t* clist, int round) {
 // chunks of long claiming rows: MODE 0 claims the columns, MODE 1 marks the
 // row when a lower row holds one of them
 template <int MODE>
-__global__ void __launch_bounds__(PSL_BLOCK) k_fs_claim_long(Dev d, const int32_t* clist, int round) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_fs_claim_long(Dev d, const int32_t* clist, int round, int seq) {
+  if (round_over(d, seq)) return;
   int nc = d.flags->fs_claims;
   for (int k = blockIdx.x; k < nc; k += gridDim.x) {
     int p0 = clist[k];
@@ -174,7 +177,8 @@ __device__ __forceinline__ bool fs_applies(const Dev& d, int i, int j, int round
 
 // applying rows keep their pick, the others drop it; d.cnt gets the count
 // of each tile of PSL_BLOCK rows
-__global__ void __launch_bounds__(PSL_BLOCK) k_fs_count(Dev d, int round) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_fs_count(Dev d, int round, int seq) {
+  if (round_over(d, seq)) return;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) d.flags->fs_rows = 0;
   int k = 0;
@@ -210,7 +214,8 @@ __device__ __forceinline__ void fs_entry(const Dev& d, int jj, double a, double2
 // leaves, its column is set to s / a_ij (0 without a cost); a short row
 // updates and leaves its other columns here, a long one is listed in chunks
 // (and keeps its pick for them)
-__global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int64_t base, int round) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int round, int seq) {
+  if (round_over(d, seq)) return;
   if (d.cnt[blockIdx.x] == 0) return;  // no row of the tile applies
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int j = t < d.m ? d.fs_pick[t] : FS_NONE;
@@ -235,7 +240,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
   rec.v[1] = lhs;
   rec.v[2] = rhs;
   rec.v[3] = cj;
-  d.rec[base + d.flags->round_total + d.off[blockIdx.x] + pre] = rec;
+  d.rec[d.flags->rec_at + d.flags->round_total + d.off[blockIdx.x] + pre] = rec;
   d.row_on[i] = 0;
   d.bnd[j] = make_double2(v, v);
   d.bkey[2 * (int64_t)j] = dkey(v);
@@ -269,7 +274,8 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
 
 // the listed chunks of long applying rows: one workgroup per chunk, a
 // position a thread (the row's own column was set at its emission)
-__global__ void __launch_bounds__(PSL_BLOCK) k_fs_drop(Dev d, const int32_t* list) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_fs_drop(Dev d, const int32_t* list, int seq) {
+  if (round_over(d, seq)) return;
   int nc = d.flags->fs_rows;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     d.flags->round_total += d.flags->fs_total;
@@ -290,7 +296,8 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_drop(Dev d, const int32_t* lis
 }
 
 // the long rows' picks, once all their chunks are done
-__global__ void k_fs_reset(Dev d, const int32_t* list) {
+__global__ void k_fs_reset(Dev d, const int32_t* list, int seq) {
+  if (round_over(d, seq)) return;
   int nc = d.flags->fs_rows;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nc; k += gridDim.x * blockDim.x) {
     int p0 = list[k];
@@ -299,23 +306,23 @@ __global__ void k_fs_reset(Dev d, const int32_t* list) {
   }
 }
 
-void launch_free_singletons(const Dev& d, int32_t* list, int64_t base, int round, int32_t* ws, hipStream_t s) {
+void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, int32_t* ws, hipStream_t s) {
   if (d.m == 0 || d.n == 0) return;
   // the claim chunks follow the room of the drop chunks (at most nnz / FS_SHORT
   // + m of each)
   int32_t* clist = list + (d.nnz / FS_SHORT + d.m + 64);
   unsigned cb = (unsigned)((d.n + PSL_BLOCK - 1) / PSL_BLOCK);
   unsigned rb = (unsigned)((d.m + PSL_BLOCK - 1) / PSL_BLOCK);
-  hipLaunchKernelGGL(k_fs_pick, dim3(cb), dim3(PSL_BLOCK), 0, s, d);
-  hipLaunchKernelGGL(k_fs_claim, dim3(rb), dim3(PSL_BLOCK), 0, s, d, clist, round);
-  hipLaunchKernelGGL((k_fs_claim_long<0>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round);
-  hipLaunchKernelGGL((k_fs_claim_long<1>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round);
-  hipLaunchKernelGGL(k_fs_count, dim3(rb), dim3(PSL_BLOCK), 0, s, d, round);
+  hipLaunchKernelGGL(k_fs_pick, dim3(cb), dim3(PSL_BLOCK), 0, s, d, seq);
+  hipLaunchKernelGGL(k_fs_claim, dim3(rb), dim3(PSL_BLOCK), 0, s, d, clist, round, seq);
+  hipLaunchKernelGGL((k_fs_claim_long<0>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
+  hipLaunchKernelGGL((k_fs_claim_long<1>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
+  hipLaunchKernelGGL(k_fs_count, dim3(rb), dim3(PSL_BLOCK), 0, s, d, round, seq);
   // tile counts (rb <= m entries of d.cnt) scanned
   scan_excl(d.cnt, d.off, rb, &d.flags->fs_total, ws, s);
-  hipLaunchKernelGGL(k_fs_emit, dim3(rb), dim3(PSL_BLOCK), 0, s, d, list, base, round);
-  hipLaunchKernelGGL(k_fs_drop, dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list);
-  hipLaunchKernelGGL(k_fs_reset, dim3(64), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list);
+  hipLaunchKernelGGL(k_fs_emit, dim3(rb), dim3(PSL_BLOCK), 0, s, d, list, round, seq);
+  hipLaunchKernelGGL(k_fs_drop, dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list, seq);
+  hipLaunchKernelGGL(k_fs_reset, dim3(64), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list, seq);
 }
 
 }  // namespace psl

@@ -25,14 +25,26 @@ __host__ __device__ __forceinline__ int64_t cand_region_start(const SweepGrid& g
 }
 
 // sweep.hip
-void launch_long_stats(const Dev& d, int mode, hipStream_t s);
-void launch_sweep(const Dev& d, const SweepGrid& g, int mode, hipStream_t s);
+// (rounds: seq is the round's launch number, see Flags::stop_at)
+void launch_long_stats(const Dev& d, int mode, int chunks, int seq, hipStream_t s);
+void launch_sweep(const Dev& d, const SweepGrid& g, int mode, int seq, hipStream_t s);
 void launch_long_consts(const Dev& d, hipStream_t s);
-void launch_src(const Dev& d, const SweepGrid& g, hipStream_t s);
-// decisions, counts and records of a round (tile_sum / tile_off: one int per
-// 1024 rows and columns, ws: scan workspace)
-void launch_decide(const Dev& d, int64_t base, int round, int32_t* tile_sum, int32_t* tile_off, int32_t* ws,
-                   hipStream_t s);
+// after the sweep: the sources of the final bounds, the decisions and record
+// counts, the records and the marks for the next round (whose mode the
+// decisions' last workgroup sets: d.flags->mode, bit 0 = sweep the touched rows
+// only, allowed with allow_incremental when fewer than n / incr_factor columns
+// changed; bit 1 = keep the infinite-contribution counts, when fewer than n /
+// count_factor bounds became finite)
+#define MARK_DENSE 4096
+struct RoundMode {
+  int allow, incr_factor, count_factor;
+};
+// tile_sum: an int per decision tile (decide_tiles(d)); dense: the LP has
+// columns of more than MARK_DENSE entries
+int64_t decide_tiles(int64_t m, int64_t n);
+size_t decide_supers(int64_t m, int64_t n);
+void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, bool dense, int round, int seq,
+                   int32_t* tile_sum, hipStream_t s);
 int long_max_passes();
 
 // ingest.hip
@@ -55,24 +67,21 @@ const uint32_t* build_csc(const Dev& d, int32_t* cp, int32_t* ri, double* cva, i
 // bins: writes the bin lists and per-bin counts (device counts[NBINS])
 void build_bins(const Dev& d, const int32_t* thresholds, BinEnt* bins, int32_t* counts, IngestScratch& sc,
                 hipStream_t s);
-// The rows a round sweeps: every active row of an LP still presolving (and,
-// by the mode, only the marked ones / none that is inert) as bin lists in row
-// order in out, the kept long rows' chunks (from d.chunks0) in cout, and
-// sel = {bin offsets [0..NBINS], rows, nonzeros, chunks} (device). The mode
-// is *mode_dev (device: bit 0 marked rows only, bit 1 inert rows skipped), or
-// mode_host when mode_dev is null. Kept rows' marks are cleared. keep:
-// select_keep_bytes(m) bytes, cnt: select_count_ints(m) ints.
-size_t select_keep_bytes(int64_t m);
-size_t select_count_ints(int64_t m);
-void select_rows(const Dev& d, const int32_t* mode_dev, int mode_host, int t_long, int t_g8, uint8_t* keep,
-                 int32_t* cnt, BinEnt* out, LongChunk* cout, int32_t* sel, int32_t* ws, hipStream_t s);
-// after a round: decide on the device the next round's mode (d.flags->mode:
-// bit 0 = sweep the touched rows only, allowed with allow_incremental when
-// fewer than n / incr_factor columns changed; bit 1 = keep the infinite-
-// contribution counts, when fewer than n / count_factor bounds became
-// finite); with bit 1, lower the counts of the rows of columns whose bounds
-// became finite; with bit 0, mark the rows of the changed columns dirty
-void mark_dirty(const Dev& d, bool allow_incremental, int incr_factor, int count_factor, hipStream_t s);
+// The rows a launch takes: every active row of an LP still presolving, as bin
+// lists in out (bin b's from d.bin_off[b]), the kept long rows' chunks (from
+// d.chunks0) in cout and the counts in cnt (cleared before). A bin's rows
+// come in row order within each tile of rows, the tiles in any order.
+void select_all(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s);
+// The same for the next round, at the end of a round's launches: by
+// d.flags->mode only the marked rows / none that is inert (marks of kept rows
+// are cleared), and the round's control: its records and swept rows added up,
+// each LP's state, and whether the rounds queued after it run. need: records a
+// round may add (room for them is checked; last: no round is queued after)
+void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int64_t need,
+                 bool last, int seq, hipStream_t s);
+// before rounds are queued: the record buffer's state, no stop, and (K > 1)
+// the LPs' flags cleared
+void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStream_t s);
 // d.dense_cols / d.n_dense from the transposed copy (after build_csc)
 void list_dense_cols(const Dev& d, hipStream_t s);
 // chunk table of the long rows (d.nlong set); total chunks to *total (device)
@@ -103,10 +112,10 @@ size_t par_cols_ws_ints(int64_t n);
 void launch_par_cols(const Dev& d, const ColScratch& P, int64_t base, int round, int32_t* ws, hipStream_t s);
 
 // singleton.hip: zero-cost free column singletons at the end of a round
-// (records from base + the round's record total; list: nnz / 32 + m ints of
+// (records after the round's others; list: nnz / 32 + m ints of
 // scratch; adds its records to d.flags->round_total and its rows to
 // rows_removed)
-void launch_free_singletons(const Dev& d, int32_t* list, int64_t base, int round, int32_t* ws, hipStream_t s);
+void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, int32_t* ws, hipStream_t s);
 
 // parallel.hip
 struct LpTab {        // an LP's slice of the parallel-row table

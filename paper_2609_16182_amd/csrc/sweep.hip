@@ -291,6 +291,7 @@ __device__ __forceinline__ void commit_cands(const Dev& d, const CandSink& sk, i
       if (tup < cur) atomicMin(k, dkey(tup));
     }
   }
+  if (alo || aup) d.touch[j] = 1;
   wave_append(alo, Cand{2 * j, pos, tlo}, sk.list, sk.counter);
   wave_append(aup, Cand{2 * j + 1, pos, tup}, sk.list, sk.counter);
 }
@@ -408,7 +409,7 @@ template <int G, int C>
 __device__ __forceinline__ void row_entry(const Dev& d, int bin, int vblock, RowIn<C>& in) {
   const int per_block = PSL_BLOCK / G;
   int gid = vblock * per_block + (int)(threadIdx.x / G);
-  int count = d.bin_off[bin + 1] - d.bin_off[bin];
+  int count = d.sel[bin].v;
   in.vr = gid < count;
   BinEnt be = d.bins[d.bin_off[bin] + (in.vr ? gid : 0)];
   in.row = be.row;
@@ -504,7 +505,8 @@ __device__ __forceinline__ void row_block(const Dev& d, const CandSink& sk, RowI
 // processed, so a lane has REP rows' gathers in flight together.
 template <int G, int C, int MODE, int REP>
 __device__ __forceinline__ void sweep_rows(const Dev& d, const CandSink& sk, int bin, int lblock) {
-  int count = d.bin_off[bin + 1] - d.bin_off[bin];
+  int count = d.sel[bin].v;
+  if (lblock * REP * (PSL_BLOCK / G) >= count) return;  // uniform over the workgroup
   int gl = threadIdx.x & (G - 1);
   if (C == 1) {
     RowIn<C> in[REP];
@@ -584,7 +586,12 @@ __device__ __forceinline__ void pass_stats(const Dev& d, int64_t s0, int len, in
 
 // partial statistics of one chunk (its passes combined in tree order)
 template <int MODE>
-__global__ void __launch_bounds__(PSL_BLOCK) k_long_stats(Dev d) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_long_stats(Dev d, int seq) {
+  if (MODE == MODE_ROUND) {
+    if (round_over(d, seq)) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) d.flags->stamp[0] = wall_clock64();
+  }
+  if ((int)blockIdx.x >= d.sel[SEL_CHUNKS].v) return;
   __shared__ double ps[2 * LONG_MAX_PASSES];
   __shared__ double wl[8];
   __shared__ int il[4];
@@ -726,18 +733,25 @@ __device__ __forceinline__ int long_first_block(const SweepGrid& g) {
 enum { KIND_SHORT = 0, KIND_WIDE = 1, KIND_LONG = 2, KIND_ALL = 3 };
 
 template <int MODE, int KIND>
-__global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int base) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int base, int seq) {
   __shared__ double lds[8];
   __shared__ int32_t lcount;
+  if (MODE == MODE_ROUND && round_over(d, seq)) return;
   if (threadIdx.x == 0) lcount = 0;
   __syncthreads();
   int gb = blockIdx.x + base;  // global workgroup number
+  if (MODE == MODE_ROUND && gb == 0 && threadIdx.x == 0) {
+    unsigned long long t = wall_clock64();
+    d.flags->stamp[1] = t;
+    if (g.nb[BIN_LONG] == 0) d.flags->stamp[0] = t;
+  }
   int b = gb;
   int bin;
   int64_t start = cand_region_start(g, b, bin);
   int lfb = long_first_block(g);
-  if (MODE == MODE_ROUND && (KIND == KIND_LONG || (KIND == KIND_ALL && b >= lfb)))
-    start = g.long_base + (int64_t)d.lchunk[b - lfb].cand_off;
+  if (MODE == MODE_ROUND && (KIND == KIND_LONG || (KIND == KIND_ALL && gb >= lfb)) &&
+      gb - lfb < d.sel[SEL_CHUNKS].v)
+    start = g.long_base + (int64_t)d.lchunk[gb - lfb].cand_off;
   CandSink sk{d.cand + (start < 0 ? 0 : start), &lcount};
   if (KIND == KIND_ALL) {
     if (b < g.nb[BIN_G4]) {
@@ -753,7 +767,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int bas
     } else if ((b -= g.nb[BIN_W4]) < g.nb[BIN_W8]) {
       sweep_rows<64, 8, MODE, 1>(d, sk, BIN_W8, b);
     } else if (MODE == MODE_ROUND) {
-      sweep_long_chunk(d, sk, gb - lfb, lds);
+      if (gb - lfb < d.sel[SEL_CHUNKS].v) sweep_long_chunk(d, sk, gb - lfb, lds);
     }
   } else if (KIND == KIND_SHORT) {
     if (b < g.nb[BIN_G4]) {
@@ -771,7 +785,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int bas
     if (b < g.nb[BIN_W4]) sweep_rows<64, 4, MODE, 1>(d, sk, BIN_W4, b);
     else sweep_rows<64, 8, MODE, 1>(d, sk, BIN_W8, b - g.nb[BIN_W4]);
   } else if (MODE == MODE_ROUND) {
-    sweep_long_chunk(d, sk, b - lfb, lds);
+    if (b - lfb < d.sel[SEL_CHUNKS].v) sweep_long_chunk(d, sk, b - lfb, lds);
   }
   if (MODE == MODE_ROUND) {
     __syncthreads();
@@ -799,9 +813,8 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_long_finish_compact(Dev d) {
 // ---------------------------------------------------------------------------
 // source rows of the final bounds
 // ---------------------------------------------------------------------------
-// one workgroup per sweep workgroup: its candidate region
-__global__ void __launch_bounds__(PSL_BLOCK) k_src(Dev d, SweepGrid g) {
-  int b = blockIdx.x;
+// the candidate region of sweep workgroup b
+__device__ __forceinline__ void sources(const Dev& d, const SweepGrid& g, int b) {
   int n = d.cand_cnt[b];
   if (n == 0) return;
   int bin;
@@ -810,7 +823,6 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_src(Dev d, SweepGrid g) {
   const Cand* list = d.cand + start;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     Cand c = list[i];
-    d.touch[c.js >> 1] = 1;
     if (c.t == dunkey(d.bkey[c.js])) atomicMin(&d.src[c.js], c.pos);
   }
 }
@@ -864,6 +876,7 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
     ++k;
   }
   bool fin = !is_inf(lo) && !is_inf(up);
+  bool lfin = !is_inf(lo), ufin = !is_inf(up);  // the new bounds
   if (fin && lo > up + tol_of(d.cfg, up)) code |= CC_INFEAS;
   if (fin && up - lo <= d.cfg.fix_tol * mx1(lo)) {
     code |= CC_FIX;
@@ -874,6 +887,7 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
       code |= CC_UNBOUNDED;
     } else {
       code |= CC_EMPTY;
+      lfin = ufin = true;
       ++k;
     }
   } else if (d.cfg.dual_fix) {
@@ -884,10 +898,15 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
         code |= CC_UNBOUNDED;
       } else {
         code |= CC_DUALFIX;
+        lfin = ufin = true;
         ++k;
       }
     }
   }
+  // bounds that become finite lower the infinite-contribution counts of the
+  // column's rows (applied by the marks)
+  if (is_inf(b.x) && lfin) code |= CC_LBFIN;
+  if (is_inf(b.y) && ufin) code |= CC_UBFIN;
   if (code & CC_INFEAS) flag_infeasible(d, col_lp_of(d, j));
   if (code & CC_UNBOUNDED) flag_unbounded(d, col_lp_of(d, j));
   return code;
@@ -909,6 +928,7 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
 // an index has at most 3 records (a row 1; a column: each bound side and one
 // of fixed, empty or dual-fixed), so a lane's count fits in 4 bits
 static_assert(3 * DEC_ITEMS < 16, "record counts per lane must fit in 4 bits");
+static_assert(DEC_BLOCK == PSL_BLOCK, "block scans");
 static_assert(DEC_ITEMS == 4, "a lane's codes are one 32-bit word");
 
 // prefix (lanes below) and total of per-lane counts 0..15 across the
@@ -935,25 +955,109 @@ __device__ __forceinline__ int col_recs(uint32_t code) {
   return (code & CC_LB ? 1 : 0) + (code & CC_UB ? 1 : 0) + (code & (CC_FIX | CC_EMPTY) ? 1 : 0);
 }
 
-// Column decisions of the touched columns (untouched ones cannot change: an
-// active column with unchanged bounds and rows is neither fixed nor empty),
-// and the record count of each tile.
-__global__ void __launch_bounds__(DEC_BLOCK) k_decide_count(Dev d, int32_t* tile_sum, int64_t row_tiles) {
+// The tiles' record counts are summed per 64 tiles with atomic adds whose
+// results are awaited, so that the workgroup that finishes the last tile sees
+// every sum without a fence: it scans the few sums of 64 (a tile's offset is
+// then one of them plus at most 63 tile counts) and sets the next round's mode.
+// Column tiles start at a multiple of 64, so the rows removed are the records
+// before the first of them.
+#define SUPER 64
+
+static int64_t row_supers(int64_t m) { return ((m + DEC_TILE - 1) / DEC_TILE + SUPER - 1) / SUPER; }
+
+// tiles, with the row tiles filled up to a multiple of SUPER; at least one
+// column tile (the last workgroup's work is done in any case)
+int64_t decide_tiles(int64_t m, int64_t n) {
+  int64_t ct = (n + DEC_TILE - 1) / DEC_TILE;
+  return SUPER * row_supers(m) + (ct > 0 ? ct : 1);
+}
+
+size_t decide_supers(int64_t m, int64_t n) { return (size_t)((decide_tiles(m, n) + SUPER - 1) / SUPER + 1); }
+
+struct TileGrid {
+  int nsrc;       // workgroups of the sweep (their candidate regions come first)
+  int row_tiles;  // tiles of rows
+  int col0;       // first column tile (a multiple of SUPER)
+  int tiles;      // col0 + the column tiles
+};
+
+// the next round's selection mode from this round's totals
+__device__ __forceinline__ int round_mode(const Dev& d, const RoundMode& rm, int changed, int fin_cols) {
+  bool incr = rm.allow && (int64_t)changed * rm.incr_factor < (int64_t)d.n;
+  bool counts = (int64_t)fin_cols * rm.count_factor < (int64_t)d.n;
+  return (incr ? 1 : 0) | (counts ? 2 : 0);
+}
+
+// the sums of 64 tiles scanned, the round's totals, the next mode (one
+// workgroup)
+__device__ __forceinline__ void decide_totals(const Dev& d, const TileGrid& tg, const RoundMode& rm) {
+  int ns = (tg.tiles + SUPER - 1) / SUPER, rs = tg.col0 / SUPER;
+  int run = 0, fin = 0, removed = 0;
+  for (int k0 = 0; k0 < ns; k0 += DEC_BLOCK) {
+    int k = k0 + (int)threadIdx.x;
+    unsigned long long v = 0;
+    if (k < ns) {
+      v = __hip_atomic_load(&d.super[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      atomicExch(&d.super[k], 0ull);
+    }
+    int c = (int)(v & 0xFFFFFFFFull), f = (int)(v >> 32), tot, ftot, rtot;
+    int pre = block_excl_scan(c, &tot);
+    if (k < ns) d.super_off[k] = run + pre;
+    block_excl_scan(f, &ftot);
+    block_excl_scan(k < rs ? c : 0, &rtot);
+    run += tot;
+    fin += ftot;
+    removed += rtot;
+  }
+  if (threadIdx.x == 0) {
+    d.super_done[ns] = 0;
+    d.flags->round_total = run;
+    d.flags->rows_removed = removed;
+    d.flags->fin_cols = fin;
+    d.flags->mode = round_mode(d, rm, run - removed, fin);
+    int64_t rows = 0, nnz = d.sel[SEL_NNZ].v;
+#pragma unroll
+    for (int b = 0; b < NBINS; ++b) rows += d.sel[b].v;
+    d.flags->sum_rows += rows;
+    d.flags->sum_nnz += nnz;
+    d.flags->sum_cols += nnz < d.n ? nnz : d.n;
+  }
+}
+
+// Sources of the final bounds, and beside them the column decisions of the
+// touched columns (untouched ones cannot change: an active column with
+// unchanged bounds and rows is neither fixed nor empty), and the record count
+// of each tile.
+__global__ void __launch_bounds__(DEC_BLOCK) k_decide(Dev d, SweepGrid g, TileGrid tg, RoundMode rm, int seq,
+                                                      int32_t* tile_sum) {
+  if (round_over(d, seq)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    unsigned long long t = wall_clock64();
+    d.flags->stamp[2] = t;
+    if (tg.nsrc == 0) d.flags->stamp[0] = d.flags->stamp[1] = t;  // no row to sweep
+  }
+  if ((int)blockIdx.x < tg.nsrc) {
+    sources(d, g, blockIdx.x);
+    return;
+  }
   __shared__ int list[DEC_TILE];
-  __shared__ int wtot[DEC_WAVES];
+  __shared__ int wtot[DEC_WAVES], wfin[DEC_WAVES];
+  __shared__ int last;
   int w = threadIdx.x >> 6, lane = lane_id();
   int* wl = list + w * DEC_WAVE_ITEMS;
-  int64_t tile = blockIdx.x;
-  int c = 0, nt = 0, ntot = 0;
-  if (tile < row_tiles) {
-    int64_t i0 = tile * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
+  int t = (int)blockIdx.x - tg.nsrc;
+  const bool rows = t < tg.row_tiles;
+  const int tile = rows ? t : tg.col0 + (t - tg.row_tiles);
+  int c = 0, nt = 0, ntot = 0, fin = 0;
+  if (rows) {
+    int64_t i0 = (int64_t)tile * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
     if (i0 < d.m) {
       uint32_t cw = code_word(d.row_code, i0) & valid_bytes(d.m - i0);
 #pragma unroll
       for (int b = 0; b < 4; ++b) c += ((cw >> (8 * b)) & 0xFFu) != RC_KEEP;
     }
   } else {
-    int64_t j0 = (tile - row_tiles) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
+    int64_t j0 = (int64_t)(tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
     uint32_t tw = 0;
     if (j0 < d.n) {
       uint32_t vm = valid_bytes(d.n - j0);
@@ -980,24 +1084,41 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide_count(Dev d, int32_t* tile
   for (int e = lane; e < ntot; e += PSL_WAVE) {
     int j = wl[e];
     int kk;
-    d.col_code[j] = col_decide(d, j, kk);
+    uint8_t code = col_decide(d, j, kk);
+    d.col_code[j] = code;
     c += kk;
+    fin += (code & (CC_LBFIN | CC_UBFIN)) != 0;
   }
-  // the tile's record count: wavefront totals by ballots, summed by thread 0
-  int pre_w, tot_w;
+  // the tile's counts: wavefront totals by ballots, summed by thread 0
+  int pre_w, tot_w, fin_w;
   wave_small_scan(c, pre_w, tot_w);
-  if (lane == 0) wtot[w] = tot_w;
+  wave_small_scan(fin, pre_w, fin_w);
+  if (lane == 0) {
+    wtot[w] = tot_w;
+    wfin[w] = fin_w;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int tot = 0;
+    int tot = 0, ftot = 0;
 #pragma unroll
-    for (int k = 0; k < DEC_WAVES; ++k) tot += wtot[k];
+    for (int k = 0; k < DEC_WAVES; ++k) {
+      tot += wtot[k];
+      ftot += wfin[k];
+    }
     tile_sum[tile] = tot;
+    int sp = tile / SUPER;
+    int end = rows ? tg.row_tiles : tg.tiles;  // tiles of this 64 that exist
+    int members = (end < (sp + 1) * SUPER ? end : (sp + 1) * SUPER) - sp * SUPER;
+    last = 0;
+    // each add is issued once the one before it has returned
+    unsigned long long o = atomicAdd(&d.super[sp], (unsigned long long)tot | ((unsigned long long)ftot << 32));
+    if (o != ~0ull && atomicAdd(&d.super_done[sp], 1) == members - 1) {
+      int ns = (tg.tiles + SUPER - 1) / SUPER;
+      if (atomicExch(&d.super_done[sp], 0) == members) last = atomicAdd(&d.super_done[ns], 1) == ns - 1;
+    }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    d.flags->rows_removed = 0;
-    d.flags->fin_cols = 0;
-  }
+  __syncthreads();
+  if (last) decide_totals(d, tg, rm);
 }
 
 __device__ __forceinline__ Record mkrec(uint8_t type, uint8_t side, int round, int i, int j, int k, double v0,
@@ -1028,9 +1149,8 @@ __device__ __forceinline__ void emit_row(const Dev& d, int i, int round, Record*
   d.row_code[i] = RC_KEEP;
 }
 
-// returns 1 when a bound of the column became finite
-__device__ __forceinline__ int emit_col(const Dev& d, int j, int round, Record* r) {
-  uint8_t code = d.col_code[j];
+// the records and new state of a column with decision code `code`
+__device__ __forceinline__ void emit_col(const Dev& d, int j, uint8_t code, int round, Record* r) {
   double2 b = d.bnd[j];
   double lo = dunkey(d.bkey[2 * (int64_t)j]);
   double up = dunkey(d.bkey[2 * (int64_t)j + 1]);
@@ -1042,16 +1162,20 @@ __device__ __forceinline__ int emit_col(const Dev& d, int j, int round, Record* 
     bool ok = q >= 0 && q < d.nnz;
     int k = ok ? d.rowid1[q + 1] : -1;
     *r++ = mkrec(REC_BOUND_CHANGE, 0, round, -1, j, k, b.x, lo, ok ? d.va[q] : __builtin_nan(""), 0.0);
-    int ls = d.lsrc[j];
-    d.lsrc[j] = ls == -1 || ls == k ? k : -2;  // a bound from one row only keeps it implied by that row
+    if (d.cfg.free_sing) {
+      int ls = d.lsrc[j];
+      d.lsrc[j] = ls == -1 || ls == k ? k : -2;  // a bound from one row only keeps it implied by that row
+    }
   }
   if (code & CC_UB) {
     int q = d.src[2 * (int64_t)j + 1];
     bool ok = q >= 0 && q < d.nnz;
     int k = ok ? d.rowid1[q + 1] : -1;
     *r++ = mkrec(REC_BOUND_CHANGE, 1, round, -1, j, k, b.y, up, ok ? d.va[q] : __builtin_nan(""), 0.0);
-    int us = d.usrc[j];
-    d.usrc[j] = us == -1 || us == k ? k : -2;
+    if (d.cfg.free_sing) {
+      int us = d.usrc[j];
+      d.usrc[j] = us == -1 || us == k ? k : -2;
+    }
   }
   double nlo = lo, nup = up;
   if ((code & CC_DUALFIX) == CC_DUALFIX) {
@@ -1069,40 +1193,160 @@ __device__ __forceinline__ int emit_col(const Dev& d, int j, int round, Record* 
     *r++ = mkrec(REC_EMPTY_COL, 0, round, -1, j, -1, v, d.c[j], 0.0, 0.0);
     nlo = nup = v;
   }
-  // bounds that became finite lower the infinite-contribution counts of
-  // the column's rows (applied by the marking pass)
-  uint8_t fin = (is_inf(b.x) && !is_inf(nlo) ? CC_LBFIN : 0) | (is_inf(b.y) && !is_inf(nup) ? CC_UBFIN : 0);
-  if (fin) d.col_code[j] = code | fin;
   d.bnd[j] = make_double2(nlo, nup);
   d.bkey[2 * (int64_t)j] = dkey(nlo);
   d.bkey[2 * (int64_t)j + 1] = dkey(nup);
   d.src[2 * (int64_t)j] = 0x7FFFFFFF;
   d.src[2 * (int64_t)j + 1] = 0x7FFFFFFF;
-  return fin ? 1 : 0;
 }
 
-// Records of the round in index order: each tile's offset comes from the
-// scanned tile sums, the position of an index's records inside the tile from
-// the counts of the indices before it (ballots inside the wavefront, the
-// wavefronts' totals through LDS). The indices with records are compacted per
-// wavefront and dealt out to its lanes, each writing its index's records at
-// that position. Also sets the rows removed and (batches) marks the LPs that
-// changed.
-__global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t* tile_sum, const int32_t* tile_off,
-                                                            int64_t row_tiles, int64_t base, int round) {
-  int64_t tile = blockIdx.x;
-  // a row tile's records are its removed rows, so the rows removed are the
-  // records before the first column tile (the scanned tile sums)
-  if (tile == 0 && threadIdx.x == 0)
-    d.flags->rows_removed = row_tiles < (int64_t)gridDim.x ? tile_off[row_tiles] : d.flags->round_total;
+// ---------------------------------------------------------------------------
+// marks for the next round
+// ---------------------------------------------------------------------------
+// Rows of the columns whose bounds changed (or that were fixed) this round,
+// from the transposed copy; their infinite-contribution counts follow the
+// bounds that became finite. The wavefront that emitted its columns' records
+// walks their entries; columns of more than MARK_DENSE entries (listed once at
+// ingest) are walked by every workgroup of a second launch.
+#define MARK_SHORT 16
+#define MARK_MASK (CC_LB | CC_UB | CC_FIX)
+
+// One entry (q, row i) of a changed column: mark the row (when the next
+// round sweeps dirty rows only), and (with count) lower its infinite-
+// contribution counts when the column's lb / ub became finite.
+__device__ __forceinline__ void mark_entry(const Dev& d, int64_t q, int code, bool mark, bool count) {
+  int i = d.ri[q];
+  if (mark) {
+    d.dirty[i] = 1;
+    d.dirty_tile[i >> 10] = 1;
+  }
+  if (count && (code & (CC_LBFIN | CC_UBFIN))) {
+    bool pos = d.cva[q] > 0;
+    bool lbf = (code & CC_LBFIN) != 0, ubf = (code & CC_UBFIN) != 0;
+    if ((lbf && pos) || (ubf && !pos)) atomicSub(&d.rinf[i].x, 1);  // min contribution now finite
+    if ((lbf && !pos) || (ubf && pos)) atomicSub(&d.rinf[i].y, 1);  // max contribution now finite
+  }
+}
+
+// columns the marking pass walks: changed ones when rows are marked, those
+// with a bound that became finite when counts are kept
+__device__ __forceinline__ bool mark_col(int code, int mode) {
+  return ((mode & 1) && (code & MARK_MASK)) || ((mode & 2) && (code & (CC_LBFIN | CC_UBFIN)));
+}
+
+// exclusive prefix (lanes below) and total of per-lane values 0..31 across
+// the wavefront, from one ballot per bit
+__device__ __forceinline__ void wave_scan5(int v, int& pre, int& tot) {
+  unsigned long long below = lanemask_lt();
+  pre = tot = 0;
+#pragma unroll
+  for (int b = 0; b < 5; ++b) {
+    unsigned long long m = __ballot((v >> b) & 1);
+    pre += __popcll(m & below) << b;
+    tot += __popcll(m) << b;
+  }
+}
+
+// marks of the wavefront's columns wl[0 .. n) (any of them with records)
+__device__ __forceinline__ void mark_cols(const Dev& d, const int* wl, int n, int mode) {
+  int lane = lane_id();
+  for (int c0 = 0; c0 < n; c0 += PSL_WAVE) {
+    int q0 = 0, q1 = 0, code = 0;
+    if (c0 + lane < n) {
+      int j = wl[c0 + lane];
+      code = d.col_code[j];
+      if (mark_col(code, mode)) {
+        q0 = d.cp[j];
+        q1 = d.cp[j + 1];
+      }
+    }
+    int len = q1 - q0;
+    // short columns: the entries of the lanes' columns, concatenated in
+    // column order, one per lane (a column's entries are contiguous, so the
+    // row-index loads of a step touch a few lines, and no lane walks a
+    // column alone)
+    int sl = len <= MARK_SHORT ? len : 0;
+    int pre, tot;
+    wave_scan5(sl, pre, tot);
+    for (int e0 = 0; e0 < tot; e0 += PSL_WAVE) {
+      int e = e0 + lane;
+      // the entry's column: the last lane whose prefix is <= e
+      int lo = 0, hi = PSL_WAVE - 1;
+#pragma unroll
+      for (int it = 0; it < 6; ++it) {
+        int mid = (lo + hi + 1) >> 1;
+        bool le = __shfl(pre, mid, PSL_WAVE) <= e;
+        lo = le ? mid : lo;
+        hi = le ? hi : mid - 1;
+      }
+      int q = __shfl(q0, lo, PSL_WAVE) + (e - __shfl(pre, lo, PSL_WAVE));
+      int cl = __shfl(code, lo, PSL_WAVE);
+      if (e < tot) mark_entry(d, q, cl, mode & 1, mode & 2);
+    }
+    // longer ones: the wavefront walks them one after another
+    unsigned long long mask = __ballot(len > MARK_SHORT && len <= MARK_DENSE);
+    while (mask) {
+      int l = __ffsll((long long)mask) - 1;
+      mask &= mask - 1;
+      int a = __shfl(q0, l, PSL_WAVE), b = __shfl(q1, l, PSL_WAVE), cl = __shfl(code, l, PSL_WAVE);
+      for (int q = a + lane; q < b; q += PSL_WAVE) mark_entry(d, q, cl, mode & 1, mode & 2);
+    }
+  }
+}
+
+// every workgroup lists the changed dense columns (in slices of 1024, checked
+// in parallel) and walks a grid-strided share of their entries
+__global__ void __launch_bounds__(PSL_BLOCK) k_mark_dense(Dev d, int seq) {
+  __shared__ int32_t list[1024];
+  __shared__ int32_t cnt;
+  if (round_over(d, seq)) return;
+  int mode = d.flags->mode;
+  if (mode == 0) return;
+  int nd = *d.n_dense;
+  for (int k0 = 0; k0 < nd; k0 += 1024) {
+    if (threadIdx.x == 0) cnt = 0;
+    __syncthreads();
+    for (int k = k0 + threadIdx.x; k < nd && k < k0 + 1024; k += PSL_BLOCK) {
+      int j = d.dense_cols[k];
+      if (mark_col(d.col_code[j], mode)) list[atomicAdd(&cnt, 1)] = j;
+    }
+    __syncthreads();
+    int nc = cnt;
+    for (int c = 0; c < nc; ++c) {
+      int j = list[c];
+      int code = d.col_code[j];
+      int64_t q1 = d.cp[j + 1];
+      for (int64_t q = d.cp[j] + (int64_t)blockIdx.x * PSL_BLOCK + threadIdx.x; q < q1;
+           q += (int64_t)gridDim.x * PSL_BLOCK)
+        mark_entry(d, q, code, mode & 1, mode & 2);
+    }
+    __syncthreads();
+  }
+}
+
+// Records of the round in index order: a tile's offset is the sum of the tiles
+// before its 64 (scanned) and of the tiles before it among them; the position
+// of an index's records inside the tile comes from the counts of the indices
+// before it (ballots inside the wavefront, the wavefronts' totals through LDS).
+// The indices with records are compacted per wavefront and dealt out to its
+// lanes, each writing its index's records at that position; a wavefront of
+// columns then marks their rows for the next round. Also marks the LPs that
+// changed (batches) and clears the next selection's counts.
+__global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t* tile_sum, TileGrid tg, int round,
+                                                           int seq) {
+  if (round_over(d, seq)) return;
+  if (blockIdx.x == 0 && threadIdx.x < SEL_N) d.flags->sel[1][threadIdx.x].v = 0;
+  const bool rows = (int)blockIdx.x < tg.row_tiles;
+  const int tile = rows ? (int)blockIdx.x : tg.col0 + ((int)blockIdx.x - tg.row_tiles);
   int tsum = tile_sum[tile];
   if (tsum == 0) return;  // a tile without records
   __shared__ int list[DEC_TILE], lpos[DEC_TILE];
-  __shared__ int wtot[DEC_WAVES], wfin[DEC_WAVES];
+  __shared__ int wtot[DEC_WAVES];
   int w = threadIdx.x >> 6, lane = lane_id();
-  bool rows = tile < row_tiles;
-  int64_t t0 = (rows ? tile : tile - row_tiles) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
+  int64_t t0 = (int64_t)(rows ? tile : tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
   int64_t lim = rows ? d.m : d.n;
+  const int mode = d.flags->mode;
+  int before = lane < (tile & (SUPER - 1)) ? tile_sum[(tile & ~(SUPER - 1)) + lane] : 0;
   uint32_t cnt4 = 0;  // the records of the lane's 4 indices, a byte each
   if (t0 < lim) {
     uint32_t vm = valid_bytes(lim - t0);
@@ -1124,6 +1368,7 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t*
   wave_small_scan(c, pre, tot_w);
   wave_small_scan(ni, ipre, itot);
   if (lane == 0) wtot[w] = tot_w;
+  before = group_sum_int<PSL_WAVE>(before);
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < DEC_WAVES; ++k) pre += k < w ? wtot[k] : 0;
@@ -1140,8 +1385,7 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t*
     }
   }
   __syncthreads();
-  Record* r0 = d.rec + base + tile_off[tile];
-  int fin = 0;
+  Record* r0 = d.rec + d.flags->rec_at + d.super_off[tile / SUPER] + before;
   for (int e = lane; e < itot; e += PSL_WAVE) {
     int x = wl[e];
     Record* r = r0 + wp[e];
@@ -1151,54 +1395,40 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t*
       emit_row(d, x, round_of(d, lp, round), r);
     } else {
       lp = col_lp_of(d, x);
-      fin += emit_col(d, x, round_of(d, lp, round), r);
+      emit_col(d, x, d.col_code[x], round_of(d, lp, round), r);
     }
     if (d.K > 1) d.lpo[lp].total = 1;  // the LP changed this round
   }
-  if (rows) return;
-  // columns whose bound became finite: one atomic per workgroup
-  int fpre, ftot_w;
-  wave_small_scan(fin, fpre, ftot_w);
-  if (lane == 0) wfin[w] = ftot_w;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int ftot = 0;
-#pragma unroll
-    for (int k = 0; k < DEC_WAVES; ++k) ftot += wfin[k];
-    if (ftot) atomicAdd(&d.flags->fin_cols, ftot);
-  }
+  if (!rows && mode != 0) mark_cols(d, wl, itot, mode);
 }
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-void launch_long_stats(const Dev& d, int mode, hipStream_t s) {
-  if (d.nchunks == 0) return;
-  if (mode == MODE_ROUND) hipLaunchKernelGGL(k_long_stats<MODE_ROUND>, dim3(d.nchunks), dim3(PSL_BLOCK), 0, s, d);
-  else hipLaunchKernelGGL(k_long_stats<MODE_COMPACT>, dim3(d.nchunks), dim3(PSL_BLOCK), 0, s, d);
+void launch_long_stats(const Dev& d, int mode, int chunks, int seq, hipStream_t s) {
+  if (chunks == 0) return;
+  if (mode == MODE_ROUND) hipLaunchKernelGGL(k_long_stats<MODE_ROUND>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, seq);
+  else hipLaunchKernelGGL(k_long_stats<MODE_COMPACT>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, 0);
 }
 
-void launch_sweep(const Dev& d, const SweepGrid& g, int mode, hipStream_t s) {
+void launch_sweep(const Dev& d, const SweepGrid& g, int mode, int seq, hipStream_t s) {
   int n_short = g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1];
   int n_wide = g.nb[BIN_W4] + g.nb[BIN_W8];
   int n_long = g.nb[BIN_LONG];
+  dim3 blk(PSL_BLOCK);
   if (mode == MODE_ROUND) {
     int total = n_short + n_wide + n_long;
-    if (total) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_ALL>), dim3(total), dim3(PSL_BLOCK), 0, s, d, g, 0);
+    if (total) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_ALL>), dim3(total), blk, 0, s, d, g, 0, seq);
   } else if (mode == 2) {
-    if (n_short) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_SHORT>), dim3(n_short), dim3(PSL_BLOCK), 0, s, d, g, 0);
-    if (n_wide)
-      hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_WIDE>), dim3(n_wide), dim3(PSL_BLOCK), 0, s, d, g, n_short);
+    if (n_short) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_SHORT>), dim3(n_short), blk, 0, s, d, g, 0, seq);
+    if (n_wide) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_WIDE>), dim3(n_wide), blk, 0, s, d, g, n_short, seq);
     if (n_long)
-      hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_LONG>), dim3(n_long), dim3(PSL_BLOCK), 0, s, d, g,
-                         n_short + n_wide);
+      hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_LONG>), dim3(n_long), blk, 0, s, d, g, n_short + n_wide, seq);
   } else {
-    if (n_short)
-      hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_SHORT>), dim3(n_short), dim3(PSL_BLOCK), 0, s, d, g, 0);
-    if (n_wide)
-      hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_WIDE>), dim3(n_wide), dim3(PSL_BLOCK), 0, s, d, g, n_short);
+    if (n_short) hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_SHORT>), dim3(n_short), blk, 0, s, d, g, 0, 0);
+    if (n_wide) hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_WIDE>), dim3(n_wide), blk, 0, s, d, g, n_short, 0);
     if (d.nlong > 0)
-      hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), dim3(PSL_BLOCK), 0, s, d);
+      hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), blk, 0, s, d);
   }
 }
 
@@ -1206,31 +1436,25 @@ void launch_sweep(const Dev& d, const SweepGrid& g, int mode, hipStream_t s) {
 // the compaction-mode chunk partials
 void launch_long_consts(const Dev& d, hipStream_t s) {
   if (d.nlong == 0) return;
-  launch_long_stats(d, MODE_COMPACT, s);
+  launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, s);
   hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), dim3(PSL_BLOCK), 0, s, d);
 }
 
-void launch_src(const Dev& d, const SweepGrid& g, hipStream_t s) {
-  int total = 0;
-  for (int b = 0; b < NBINS; ++b) total += g.nb[b];
-  if (total > 0) hipLaunchKernelGGL(k_src, dim3(total), dim3(PSL_BLOCK), 0, s, d, g);
-}
-
-// the round's decisions and records: counts per tile, scan, emission; the
-// record total goes to d.flags->round_total
-void launch_decide(const Dev& d, int64_t base, int round, int32_t* tile_sum, int32_t* tile_off, int32_t* ws,
-                   hipStream_t s) {
-  int64_t row_tiles = ((int64_t)d.m + DEC_TILE - 1) / DEC_TILE;
-  int64_t tiles = row_tiles + ((int64_t)d.n + DEC_TILE - 1) / DEC_TILE;
-  if (tiles == 0) {
-    fill_i32(&d.flags->round_total, 0, 1, s);
-    fill_i32(&d.flags->rows_removed, 0, 1, s);
-    return;
-  }
-  hipLaunchKernelGGL(k_decide_count, dim3((unsigned)tiles), dim3(DEC_BLOCK), 0, s, d, tile_sum, row_tiles);
-  scan_excl(tile_sum, tile_off, tiles, &d.flags->round_total, ws, s);
-  hipLaunchKernelGGL(k_decide_emit, dim3((unsigned)tiles), dim3(DEC_BLOCK), 0, s, d, (const int32_t*)tile_sum,
-                     (const int32_t*)tile_off, row_tiles, base, round);
+// the round's sources, decisions, records and marks; the record total goes to
+// d.flags->round_total
+void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, bool dense, int round, int seq,
+                   int32_t* tile_sum, hipStream_t s) {
+  TileGrid tg;
+  tg.nsrc = 0;
+  for (int b = 0; b < NBINS; ++b) tg.nsrc += g.nb[b];
+  tg.row_tiles = (int)(((int64_t)d.m + DEC_TILE - 1) / DEC_TILE);
+  tg.col0 = (int)(SUPER * row_supers(d.m));
+  tg.tiles = (int)decide_tiles(d.m, d.n);
+  int nt = tg.row_tiles + tg.tiles - tg.col0;
+  hipLaunchKernelGGL(k_decide, dim3((unsigned)(tg.nsrc + nt)), dim3(DEC_BLOCK), 0, s, d, g, tg, rm, seq, tile_sum);
+  hipLaunchKernelGGL(k_decide_emit, dim3((unsigned)nt), dim3(DEC_BLOCK), 0, s, d, (const int32_t*)tile_sum, tg, round,
+                     seq);
+  if (dense) hipLaunchKernelGGL(k_mark_dense, dim3(1024), dim3(PSL_BLOCK), 0, s, d, seq);
 }
 
 int long_max_passes() { return LONG_MAX_PASSES; }
