@@ -383,6 +383,7 @@ static psl_status setup_arena(psl_presolver* p) {
     ALLOC(p->lp_row0, K + 1);
     ALLOC(p->lp_col0, K + 1);
     ALLOC(p->lp_round, K);
+    ALLOC(p->lp_round_b, K);
     ALLOC(p->lp_ok, K);
     ALLOC(p->lpf, K);
     ALLOC(p->lpo, K);
@@ -450,7 +451,8 @@ static psl_status setup_arena(psl_presolver* p) {
   d.lp_row0 = p->lp_row0;
   d.lp_col0 = p->lp_col0;
   d.lp_ok = p->lp_ok;
-  d.lp_round = d.lp_round_mut = p->lp_round;
+  d.lp_round = p->lp_round;
+  d.lp_round_next = p->lp_round_b;
   d.lpf = p->lpf;
   d.lpo = p->lpo;
   const psl_settings& s = p->s;
@@ -498,6 +500,10 @@ static SweepGrid grid_of(const int32_t* rows, int32_t chunks) {
 // selection is queued; p->grid covers every row of the bins)
 static void use_full_view(psl_presolver* p) {
   Dev& d = p->d;
+  if (d.direct) {  // the ingest's lists, always
+    p->grid = grid_of(p->bin_counts, d.nchunks);
+    return;
+  }
   select_all(d, p->thresholds[0], p->thresholds[2], p->bins_a, p->chunks_a, d.flags->sel[0], p->stream);
   d.bins = p->bins_a;
   d.lchunk = p->chunks_a;
@@ -508,10 +514,11 @@ static void use_full_view(psl_presolver* p) {
 // the rows the last round's selection chose
 static void use_round_view(psl_presolver* p) {
   Dev& d = p->d;
+  p->grid = grid_of(p->bin_counts, d.nchunks);
+  if (d.direct) return;
   d.bins = p->bins_s;
   d.lchunk = p->chunks_s;
   d.sel = d.flags->sel[1];
-  p->grid = grid_of(p->bin_counts, d.nchunks);
 }
 
 static std::string error_what(int32_t bits) {
@@ -550,6 +557,16 @@ static std::string error_message(psl_presolver* p, int32_t bits, int64_t pos) {
          std::to_string(local) + ")";
 }
 
+// Up to DIRECT_NNZ nonzeros the launches take the ingest's lists of all rows and
+// test each row themselves: a launch is a chain of dependent loads there, the
+// row tests ride along with the row's entries, and the selection (a launch of
+// 8 us beside a sweep of 17 on an LP of 2000 rows) goes. Larger LPs have the
+// rows to sweep selected, so that a late round's sweep is as small as they
+// are. A pass, direct and selected: 2000 rows 1.64 and 1.81 ms, 31337 rows
+// (3.6e5 nonzeros) 1.31 and 1.44, 48 LPs of 1.1e6 nonzeros 3.77 and 3.40, the
+// power-law LP (1e7) 6.11 and 5.12.
+static const int64_t DIRECT_NNZ = 500000;
+
 // the LP (or union of LPs) of the handle is in d.rp .. p->c_mut; validate,
 // transpose, bin
 static psl_status ingest_rest(psl_presolver* p) {
@@ -578,6 +595,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   LongChunk* chunks0 = p->chunks_0;  // kept intact: the row selections copy from it
   d.bins = bins0;
   d.lchunk = chunks0;
+  d.direct = p->nnz <= DIRECT_NNZ;
   build_bins(d, p->thresholds, bins0, p->bin_counts_dev, p->isc, st);
   HIPCHK(p, hipMemcpyAsync(p->htot, p->bin_counts_dev, NBINS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIPCHK(p, hipStreamSynchronize(st));
@@ -894,7 +912,7 @@ static float elapsed(psl_presolver* p, int a, int b) {
 // K > 1: upload the LPs' round numbers and clear their flags before a round
 static psl_status begin_lp_round(psl_presolver* p) {
   if (p->K == 1) return PSL_OK;
-  HIPCHK(p, hipMemcpyAsync(p->lp_round, p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
+  HIPCHK(p, hipMemcpyAsync(const_cast<int32_t*>(p->d.lp_round), p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
   HIPCHK(p, hipMemsetAsync(p->lpf, 0, p->K * sizeof(LpFlags), p->stream));
   HIPCHK(p, hipMemsetAsync(p->lpo, 0, p->K * sizeof(LpOut), p->stream));
   return PSL_OK;
@@ -905,7 +923,7 @@ static psl_status begin_lp_round(psl_presolver* p) {
 static psl_status queue_lp_read(psl_presolver* p, bool rounds) {
   if (p->K == 1) return PSL_OK;
   if (rounds)
-    HIPCHK(p, hipMemcpyAsync(p->h_round, p->lp_round, p->K * sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
+    HIPCHK(p, hipMemcpyAsync(p->h_round, p->d.lp_round, p->K * sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipMemcpyAsync(p->h_lpf, p->lpf, p->K * sizeof(LpFlags), hipMemcpyDeviceToHost, p->stream));
   return PSL_OK;
 }
@@ -1098,16 +1116,17 @@ static psl_status launch_round(psl_presolver* p) {
   if (p->K > 1) {
     for (int k = 0; k < p->K; ++k)
       p->h_round[k] = p->lst[k].phase == LP_PROP ? p->lst[k].rounds + 1 : -p->lst[k].rounds;
-    HIPCHK(p, hipMemcpyAsync(p->lp_round, p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    HIPCHK(p, hipMemcpyAsync(const_cast<int32_t*>(p->d.lp_round), p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, st));
   }
   launch_rounds_begin(d, p->rec_count - p->rec_flushed, p->rec_cap, st);
   const bool ahead = p->nnz <= RUN_AHEAD_NNZ && !p->step_rounds;
   R.queued = std::min(ahead ? RUN_AHEAD : 1, s.max_rounds - R.r);
   for (int q = 0; q < R.queued; ++q) {
     const int seq = ++R.seq, round = R.round + 1 + q;
+    const RoundSeq rs{seq, R.own ? 0 : 1};
     if (R.own) {
       use_round_view(p);
-      if (R.queued == 1) {  // the counts were read with the round before
+      if (R.queued == 1 && !d.direct) {  // the counts were read with the round before
         int32_t rows[NBINS];
         for (int b = 0; b < NBINS; ++b) rows[b] = p->hflags->sel[1][b].v;
         p->grid = grid_of(rows, p->hflags->sel[1][SEL_CHUNKS].v);
@@ -1116,8 +1135,8 @@ static psl_status launch_round(psl_presolver* p) {
       use_full_view(p);
     }
     R.own = true;
-    launch_long_stats(d, MODE_ROUND, p->grid.nb[BIN_LONG], seq, st);
-    launch_sweep(d, p->grid, p->sweep_mode, seq, st);
+    launch_long_stats(d, MODE_ROUND, p->grid.nb[BIN_LONG], rs, st);
+    launch_sweep(d, p->grid, p->sweep_mode, rs, st);
     // The next round's selection is made by the device. Rows none of whose
     // columns changed since they were last swept give the same statistics
     // and no qualifying candidate, so after a round with few column changes
@@ -1132,12 +1151,20 @@ static psl_status launch_round(psl_presolver* p) {
     // round's totals (d.flags->mode); an LP that stopped has left lp_ok already.
     // When the rounds end here the selection is not used.
     RoundMode rm{R.r + q + 1 < s.max_rounds ? 1 : 0, p->incr_factor, p->count_factor};
-    launch_decide(d, p->grid, rm, p->dense, round, seq, d.cnt, st);
+    const RoundCtl ctl{need, q + 1 == R.queued ? 1 : 0, s.enable_free_singletons ? 0 : 1};
+    launch_decide(d, p->grid, rm, ctl, p->dense, round, seq, d.cnt, st);
     // (the candidate regions are free until the next sweep)
-    if (s.enable_free_singletons)
+    if (s.enable_free_singletons) {
       launch_free_singletons(d, reinterpret_cast<int32_t*>(d.cand), round, seq, p->ws, st);
-    select_next(d, p->thresholds[0], p->thresholds[2], p->bins_s, p->chunks_s, d.flags->sel[1], need,
-                q + 1 == R.queued, seq, st);
+      launch_control(d, ctl, seq, st);
+    }
+    if (!d.direct)
+      select_next(d, p->thresholds[0], p->thresholds[2], p->bins_s, p->chunks_s, d.flags->sel[1], seq, st);
+    if (p->K > 1) {
+      int32_t* now = const_cast<int32_t*>(d.lp_round);
+      d.lp_round = d.lp_round_next;
+      d.lp_round_next = now;
+    }
   }
   e = queue_lp_read(p, true);
   if (e != PSL_OK) return e;
@@ -1171,6 +1198,7 @@ static psl_status complete_round(psl_presolver* p) {
   p->rec_count += recs;
   R.round += done;
   R.r += done;
+  R.seq -= R.queued - done;  // the marks left are those of the round after the last one run
   int nprop = 0;
   for (int k = 0; k < p->K; ++k) {
     LpState& L = p->lst[k];
@@ -1237,8 +1265,8 @@ static psl_status launch_pass(psl_presolver* p) {
   if (s.enable_doubletons) {
     // active lengths and removed-column constants after the parallel
     // passes (row_out), then the substitutions
-    launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, st);
-    launch_sweep(d, p->grid, MODE_COMPACT, 0, st);
+    launch_long_stats(d, MODE_COMPACT, d.nchunks, RoundSeq{0, 1}, st);
+    launch_sweep(d, p->grid, MODE_COMPACT, RoundSeq{0, 1}, st);
     launch_doubletons(d, p->dbl, p->rec_count - p->rec_flushed, R.round, p->ws, st);
   }
   HIPCHK(p, hipEventRecord(p->ev[5], st));
@@ -1312,8 +1340,8 @@ static psl_status launch_compact(psl_presolver* p) {
   HIPCHK(p, hipEventRecord(p->ev[4], st));
   if (!R.consts_current) {
     use_full_view(p);
-    launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, st);
-    launch_sweep(d, p->grid, MODE_COMPACT, 0, st);
+    launch_long_stats(d, MODE_COMPACT, d.nchunks, RoundSeq{0, 1}, st);
+    launch_sweep(d, p->grid, MODE_COMPACT, RoundSeq{0, 1}, st);
   }
   compact_flags(d, p->cmp, st);
   compact_write(d, p->cmp, p->red, p->obj_offset, st);

@@ -12,7 +12,9 @@
 #include "sweep.h"
 
 using psl::BinEnt;
+using psl::RoundCtl;
 using psl::RoundMode;
+using psl::RoundSeq;
 using psl::SEL_CHUNKS;
 using psl::SelCnt;
 using psl::CompactScratch;
@@ -73,7 +75,7 @@ struct psl_presolver {
 
   // batch (K > 1): device maps and per-LP arrays, pinned host mirrors
   int32_t K = 1;
-  int32_t *row_lp = nullptr, *col_lp = nullptr, *lp_row0 = nullptr, *lp_col0 = nullptr, *lp_round = nullptr;
+  int32_t *row_lp = nullptr, *col_lp = nullptr, *lp_row0 = nullptr, *lp_col0 = nullptr, *lp_round = nullptr, *lp_round_b = nullptr;
   uint8_t* lp_ok = nullptr;
   LpFlags* lpf = nullptr;
   LpOut* lpo = nullptr;

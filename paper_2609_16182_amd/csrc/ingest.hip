@@ -311,9 +311,7 @@ void build_long_chunks(const Dev& d, int npass0, LongChunk* chunks, int32_t* cnt
 struct SelArgs {
   int mode;             // -1: the device's (bit 0: marked rows only; bit 1: inert rows skipped)
   int t_long, t_g8;     // bin thresholds of the ingest
-  int64_t need;         // control: records a round may add
-  int last;             // control: no round is queued after this one
-  int seq;              // launch number of the round (control)
+  int seq;              // launch number of the round before
 };
 
 // bin of a row of len entries (the bins of the ingest)
@@ -333,71 +331,27 @@ __device__ __forceinline__ int long_row_index(const Dev& d, int row) {
   return lo;
 }
 
-// The round's control, one workgroup beside the selection's: its records and
-// clock ticks added up, each LP's state after it (d.lp_round: the number of
-// the LP's next round while it propagates, minus its last one once it does
-// not), and the end of the rounds: no LP goes on, or the record buffer might
-// not hold another round.
-__device__ __forceinline__ void round_control(const Dev& d, const SelArgs& a) {
-  __shared__ int go_on;
-  if (threadIdx.x == 0) go_on = 0;
-  __syncthreads();
-  Flags& f = *d.flags;
-  if (d.K == 1) {
-    if (threadIdx.x == 0) go_on = !f.infeasible && !f.unbounded && f.round_total != 0;
-  } else {
-    bool any = false;
-    for (int k = threadIdx.x; k < d.K; k += blockDim.x) {
-      int r = d.lp_round_mut[k];
-      if (r <= 0) continue;
-      bool more = !d.lpf[k].infeasible && !d.lpf[k].unbounded && d.lpo[k].total != 0;
-      d.lpo[k].total = 0;
-      d.lp_round_mut[k] = more ? r + 1 : -r;
-      any = any || more;
-    }
-    if (any) go_on = 1;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  f.rounds_done += 1;
-  f.rec_at += f.round_total;
-  unsigned long long now = wall_clock64();
-  f.ticks[0] += f.stamp[1] - f.stamp[0];
-  f.ticks[1] += f.stamp[2] - f.stamp[1];
-  f.ticks[2] += now - f.stamp[2];
-  if (!go_on || (!a.last && f.rec_at + a.need > f.rec_cap)) f.stop_at = a.seq;
-}
-
 template <int BS>
-__global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, int T, BinEnt* out, LongChunk* cout, SelCnt* cnt) {
+__global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, BinEnt* out, LongChunk* cout, SelCnt* cnt) {
   constexpr int W = BS / PSL_WAVE;
   constexpr int MARKS = BS * SEL_ITEMS / 1024;  // tiles of the marks in one of ours
   __shared__ int wc[SEL_ITEMS][NBINS][W];       // per item row and bin: each wavefront's rows
   __shared__ int at[NBINS];
   __shared__ int wz[W];
-  __shared__ int marked;
   const int tile = blockIdx.x;
   const bool next = a.mode < 0;
-  if (next && round_over(d, a.seq)) return;
-  if (tile == T) {
-    round_control(d, a);
-    return;
-  }
-  const int mode = next ? d.flags->mode : a.mode;
-  if (threadIdx.x == 0) marked = 0;
-  __syncthreads();
-  if (threadIdx.x < MARKS) {
-    int64_t x = (int64_t)tile * MARKS + threadIdx.x;
-    if (x <= d.m / 1024 && d.dirty_tile[x]) {
-      marked = 1;
-      d.dirty_tile[x] = 0;  // the tile's marks are taken now (rows not kept keep
-                            // theirs, harmlessly: a change marks them again)
-    }
-  }
-  __syncthreads();
-  if ((mode & 1) && !marked) return;
   const int w = threadIdx.x >> 6;
   const int64_t t0 = (int64_t)tile * BS * SEL_ITEMS + threadIdx.x;
+  const uint8_t mark = round_mark(a.seq + 1);
+  // the tile's marks
+  bool marked = false;
+#pragma unroll
+  for (int k = 0; k < MARKS; ++k) {
+    int64_t x = (int64_t)tile * MARKS + k;
+    if (x <= d.m / 1024) marked = marked || d.dirty_tile[x] == mark;
+  }
+  const int mode = next ? d.flags->mode : a.mode;
+  if ((next && round_over(d, a.seq)) || ((mode & 1) && !marked)) return;
   // level by level for all items, without branches around the loads (a row
   // that fails the cheap tests reads row 0's data, which is cached)
   bool keep[SEL_ITEMS];
@@ -405,7 +359,7 @@ __global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, int T, BinEnt* 
   for (int k = 0; k < SEL_ITEMS; ++k) {
     int64_t i = t0 + k * BS, ii = i < d.m ? i : 0;
     uint8_t on = d.row_on[ii], dt = d.dirty[ii];
-    keep[k] = i < d.m && on != 0 && (!(mode & 1) || dt != 0);
+    keep[k] = i < d.m && on != 0 && (!(mode & 1) || dt == mark);
   }
   int r0[SEL_ITEMS], len[SEL_ITEMS], lpi[SEL_ITEMS];
   int2 rf[SEL_ITEMS];
@@ -465,7 +419,6 @@ __global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, int T, BinEnt* 
     if (!keep[k]) continue;
     const int i = (int)(t0 + k * BS), b = bin[k];
     out[d.bin_off[b] + at[b] + wc[k][b][w] + pre[k]] = BinEnt{i, r0[k], len[k], 0};
-    d.dirty[i] = 0;
     if (b == BIN_LONG) {
       LongRow lr = d.lrow[long_row_index(d, i)];
       int c0 = atomicAdd(&cnt[SEL_CHUNKS].v, lr.nchunk);
@@ -475,24 +428,24 @@ __global__ void __launch_bounds__(BS) k_select(Dev d, SelArgs a, int T, BinEnt* 
 }
 
 static void launch_select(const Dev& d, const SelArgs& a, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s) {
-  const int extra = a.mode < 0 ? 1 : 0;  // the control's workgroup
+  if (d.m == 0) return;
   if (d.m >= SEL_BIG) {
     int T = (d.m + 1024 * SEL_ITEMS - 1) / (1024 * SEL_ITEMS);
-    hipLaunchKernelGGL(k_select<1024>, dim3(T + extra), dim3(1024), 0, s, d, a, T, out, cout, cnt);
+    hipLaunchKernelGGL(k_select<1024>, dim3(T), dim3(1024), 0, s, d, a, out, cout, cnt);
   } else {
     int T = (d.m + PSL_BLOCK * SEL_ITEMS - 1) / (PSL_BLOCK * SEL_ITEMS);
-    if (T + extra > 0) hipLaunchKernelGGL(k_select<PSL_BLOCK>, dim3(T + extra), dim3(PSL_BLOCK), 0, s, d, a, T, out, cout, cnt);
+    hipLaunchKernelGGL(k_select<PSL_BLOCK>, dim3(T), dim3(PSL_BLOCK), 0, s, d, a, out, cout, cnt);
   }
 }
 
 void select_all(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s) {
   fill_i32(&cnt[0].v, 0, (int64_t)SEL_N * (sizeof(SelCnt) / sizeof(int32_t)), s);
-  launch_select(d, SelArgs{0, t_long, t_g8, 0, 1, 0}, out, cout, cnt, s);
+  launch_select(d, SelArgs{0, t_long, t_g8, 0}, out, cout, cnt, s);
 }
 
-void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int64_t need,
-                 bool last, int seq, hipStream_t s) {
-  launch_select(d, SelArgs{-1, t_long, t_g8, need, last ? 1 : 0, seq}, out, cout, cnt, s);
+void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int seq,
+                 hipStream_t s) {
+  launch_select(d, SelArgs{-1, t_long, t_g8, seq}, out, cout, cnt, s);
 }
 
 __global__ void k_rounds_begin(Dev d, int64_t rec_at, int64_t rec_cap) {
@@ -560,7 +513,8 @@ __global__ void k_init_state(Dev d, int64_t supers) {
     f.dbl_count = f.dbl_applied = 0;
     f.stop_at = 0x7FFFFFFF;
     f.rounds_done = 0;
-    f.rec_at = f.rec_cap = 0;
+    f.rec_base = f.rec_at = f.rec_cap = 0;
+    for (int k = 0; k < SWEPT_SLOTS; ++k) f.swept[k].rows = f.swept[k].nnz = 0;
     f.sum_rows = f.sum_nnz = f.sum_cols = 0;
     for (int k = 0; k < 3; ++k) f.stamp[k] = f.ticks[k] = 0;
     for (int k = 0; k < 2; ++k)

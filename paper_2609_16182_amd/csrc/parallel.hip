@@ -186,7 +186,7 @@ __global__ void k_par_reset(Dev d, ParScratch P) {
 template <int G, int REP>
 __device__ __forceinline__ void hash_groups(const Dev& d, const ParScratch& P, int bin, int lblock0) {
   const int per_block = PSL_BLOCK / G;
-  int count = d.sel[bin].v;
+  int count = bin_rows_listed(d, bin);
   if (lblock0 * per_block >= count) return;  // uniform over the workgroup
   int gl = threadIdx.x & (G - 1);
   int row[REP], len[REP];
@@ -207,7 +207,7 @@ __device__ __forceinline__ void hash_groups(const Dev& d, const ParScratch& P, i
   double a[REP];
 #pragma unroll
   for (int k = 0; k < REP; ++k) {
-    on[k] = vr[k] && d.row_on[row[k]] != 0;
+    on[k] = vr[k] && d.row_on[row[k]] != 0 && row_lp_on(d, row[k]);
     j[k] = d.ci[p[k]];
     a[k] = d.va[p[k]];
   }
@@ -270,7 +270,7 @@ __device__ __forceinline__ void hash_wave_row(const Dev& d, const ParScratch& P,
   int lane = lane_id();
   int64_t s0 = d.rp[row];
   int len = d.rp[row + 1] - (int)s0;
-  if (!d.row_on[row]) return;
+  if (!d.row_on[row] || !row_lp_on(d, row)) return;
   int j[C];
   double a[C];
   bool v[C];
@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_long_first(Dev d, ParScratch 
 __device__ __forceinline__ void hash_long_chunk(const Dev& d, const ParScratch& P, int chunk) {
   LongChunk ch = d.lchunk[chunk];
   int row = ch.row;
-  if (!d.row_on[row]) return;
+  if (!d.row_on[row] || !row_lp_on(d, row)) return;
   unsigned long long a0b = P.hacc[4 * (int64_t)ch.lrow + 3];
   if (a0b == 0ull) return;  // no active column
   double a0 = __longlong_as_double((long long)a0b);
@@ -368,7 +368,7 @@ __device__ __forceinline__ void hash_long_chunk(const Dev& d, const ParScratch& 
 // the wavefront rows of a row block (four per workgroup)
 __device__ __forceinline__ void hash_wave_block(const Dev& d, const ParScratch& P, int bin, int vb) {
   int wid = vb * (PSL_BLOCK / PSL_WAVE) + (threadIdx.x >> 6);
-  if (wid >= d.sel[bin].v) return;
+  if (wid >= bin_rows_listed(d, bin)) return;
   int row = d.bins[d.bin_off[bin] + wid].row;
   if (bin == BIN_W1) hash_wave_row<1>(d, P, row);
   else if (bin == BIN_W4) hash_wave_row<4>(d, P, row);
@@ -384,7 +384,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, Swe
       continue;
     }
     int rep = bin_rep(bin);
-    int count = d.sel[bin].v;
+    int count = bin_rows_listed(d, bin);
     if (bin == BIN_G4) hash_groups<4, 4>(d, P, bin, b * rep);
     else if (bin == BIN_G8) hash_groups<8, 4>(d, P, bin, b * rep);
     else if (bin == BIN_G16) hash_groups<16, 4>(d, P, bin, b * rep);
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, Swe
       }
     return;
   }
-  if (b < d.sel[SEL_CHUNKS].v) hash_long_chunk(d, P, b);
+  if (b < chunks_listed(d)) hash_long_chunk(d, P, b);
 }
 
 __global__ void k_par_long_insert(Dev d, ParScratch P) {

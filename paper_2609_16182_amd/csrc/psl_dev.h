@@ -111,6 +111,13 @@ struct SelCnt {
 // counts of a selection: rows per bin, long-row chunks, nonzeros
 enum { SEL_CHUNKS = NBINS, SEL_NNZ = NBINS + 1, SEL_N = NBINS + 2 };
 
+// Rows and nonzeros swept so far in the run, spread over cache lines.
+#define SWEPT_SLOTS 16
+struct Swept {
+  unsigned long long rows, nnz;
+  int64_t pad[6];
+};
+
 struct Flags {
   int32_t infeasible, unbounded, error, merged;
   int32_t cand_count, round_total, vlist_count, rows_removed;
@@ -127,11 +134,13 @@ struct Flags {
   // rounds queued ahead of the host: a round's kernels do nothing when its
   // number is above stop_at, which the last round's control sets
   int32_t stop_at, rounds_done;
+  int64_t rec_base;                  // first record of the running round
   int64_t rec_at, rec_cap;           // next free record; records the buffer holds
   int64_t sum_rows, sum_nnz, sum_cols;  // swept so far in the run: rows, nonzeros, columns at most
   uint64_t stamp[3];       // clock at the round's long-row statistics, sweep, decisions
   uint64_t ticks[3];       // clock ticks of those phases so far in the run
   SelCnt sel[2][SEL_N];    // counts of the full view / of the rounds' selections
+  Swept swept[SWEPT_SLOTS];  // (direct sweeps)
 };
 
 struct Cfg {
@@ -164,8 +173,9 @@ struct Dev {
   uint8_t *fs_bad;             // per row: a long substituting row lost a column
   int32_t *col_len;
   uint8_t *row_on, *row_code, *col_code;
-  uint8_t *dirty;          // rows touched by a column change since last swept
-  uint8_t *dirty_tile;     // per 1024 rows: some row of it was marked (the row
+  uint8_t *dirty;          // rows touched by a column change: the mark (round_mark) of
+                           // the round after it, so that no mark needs clearing
+  uint8_t *dirty_tile;     // per 1024 rows, the same for some row of it (the row
                            // selection skips the other tiles when it takes
                            // marked rows only)
   const int32_t *rowid1;   // row of CSR position p at index p + 1 (built at ingest)
@@ -193,13 +203,16 @@ struct Dev {
   const BinEnt *bins;
   int32_t bin_off[NBINS + 1];
   const SelCnt *sel;
+  int32_t direct;              // the lists hold every row (those of the ingest): a
+                               // kernel tests each row itself, sel is not used
   const LongChunk *lchunk;
   const LongChunk *chunks0;    // chunk table of all long rows (built at ingest)
   LongPart *lpart;
   LongRow *lrow;
   int32_t nlong, nchunks;      // long rows and their chunks (of all rows)
-  // the decision tiles' sums: per 64 tiles the records and the columns with a
-  // bound made finite (low / high word), tiles done, and the records before
+  // the decision tiles' sums: per 64 tiles the records, the columns with a bound
+  // made finite and the tiles done (fields of a word), groups of 64 tiles
+  // done, and the records before each
   unsigned long long *super;
   int32_t *super_done, *super_off;
   // batched presolve (K LPs); with K == 1 every row and column is in LP 0
@@ -210,7 +223,7 @@ struct Dev {
   uint8_t *lp_ok;                     // [K] LP still presolving (its rows stay in the bins;
                                       // cleared here when the LP stops)
   const int32_t *lp_round;            // [K] the LP's own number of the current round
-  int32_t *lp_round_mut;              // the same, moved on by a round's control
+  int32_t *lp_round_next;             // the same after the round, written by its control
   LpFlags *lpf;                       // [K]
   LpOut *lpo;                         // [K]
   Cfg cfg;
@@ -222,6 +235,27 @@ __device__ __forceinline__ int col_lp_of(const Dev& d, int j) { return d.K > 1 ?
 __device__ __forceinline__ int round_of(const Dev& d, int lp, int round) { return d.K > 1 ? d.lp_round[lp] : round; }
 // the round with launch number seq is not run: an earlier one ended the rounds
 __device__ __forceinline__ bool round_over(const Dev& d, int seq) { return seq > d.flags->stop_at; }
+
+// the mark of rows to sweep in the round with launch number seq, 1 .. 255 (a
+// mark left from 255 rounds before only sweeps its row once more)
+__device__ __forceinline__ uint8_t round_mark(int seq) { return (uint8_t)(1 + (unsigned)seq % 255u); }
+
+// rows of bin b in the lists (at most)
+__device__ __forceinline__ int bin_rows_listed(const Dev& d, int b) {
+  return d.direct ? d.bin_off[b + 1] - d.bin_off[b] : d.sel[b].v;
+}
+__device__ __forceinline__ int chunks_listed(const Dev& d) { return d.direct ? d.nchunks : d.sel[SEL_CHUNKS].v; }
+// (direct lists hold rows of every LP) the row's LP is still presolving
+__device__ __forceinline__ bool row_lp_on(const Dev& d, int i) {
+  return !d.direct || d.K == 1 || d.lp_ok[d.row_lp[i]] != 0;
+}
+
+// A value the compiler has to have loaded here: loads written before it are
+// in flight together instead of each behind the branch that first needs it.
+template <class T>
+__device__ __forceinline__ void hold(T x) {
+  asm volatile("" : : "v"(x));
+}
 // an LP that stops leaves the next selection at once
 __device__ __forceinline__ void flag_infeasible(const Dev& d, int lp) {
   atomicOr(&d.flags->infeasible, 1);

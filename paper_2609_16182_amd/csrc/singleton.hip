@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
   rec.v[1] = lhs;
   rec.v[2] = rhs;
   rec.v[3] = cj;
-  d.rec[d.flags->rec_at + d.flags->round_total + d.off[blockIdx.x] + pre] = rec;
+  d.rec[d.flags->rec_base + d.flags->round_total + d.off[blockIdx.x] + pre] = rec;
   d.row_on[i] = 0;
   d.bnd[j] = make_double2(v, v);
   d.bkey[2 * (int64_t)j] = dkey(v);

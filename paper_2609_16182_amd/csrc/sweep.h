@@ -25,9 +25,13 @@ __host__ __device__ __forceinline__ int64_t cand_region_start(const SweepGrid& g
 }
 
 // sweep.hip
-// (rounds: seq is the round's launch number, see Flags::stop_at)
-void launch_long_stats(const Dev& d, int mode, int chunks, int seq, hipStream_t s);
-void launch_sweep(const Dev& d, const SweepGrid& g, int mode, int seq, hipStream_t s);
+// a round's place in the run: its launch number (see Flags::stop_at), and
+// whether it sweeps every active row
+struct RoundSeq {
+  int seq, full;
+};
+void launch_long_stats(const Dev& d, int mode, int chunks, RoundSeq rs, hipStream_t s);
+void launch_sweep(const Dev& d, const SweepGrid& g, int mode, RoundSeq rs, hipStream_t s);
 void launch_long_consts(const Dev& d, hipStream_t s);
 // after the sweep: the sources of the final bounds, the decisions and record
 // counts, the records and the marks for the next round (whose mode the
@@ -39,12 +43,21 @@ void launch_long_consts(const Dev& d, hipStream_t s);
 struct RoundMode {
   int allow, incr_factor, count_factor;
 };
-// tile_sum: an int per decision tile (decide_tiles(d)); dense: the LP has
-// columns of more than MARK_DENSE entries
+// A round's control, by the records' launch or (with launches of the round
+// after them) one of its own: the records and swept rows added up, each LP's
+// state, and whether the rounds queued after it run: some LP goes on, and the
+// record buffer has room for need more records (last: none is queued).
+struct RoundCtl {
+  int64_t need;
+  int last, by_emit;
+};
+// tile_sum: an int per decision tile (decide_tiles); dense: the LP has columns
+// of more than MARK_DENSE entries
 int64_t decide_tiles(int64_t m, int64_t n);
 size_t decide_supers(int64_t m, int64_t n);
-void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, bool dense, int round, int seq,
-                   int32_t* tile_sum, hipStream_t s);
+void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, const RoundCtl& ctl, bool dense, int round,
+                   int seq, int32_t* tile_sum, hipStream_t s);
+void launch_control(const Dev& d, const RoundCtl& ctl, int seq, hipStream_t s);
 int long_max_passes();
 
 // ingest.hip
@@ -72,13 +85,10 @@ void build_bins(const Dev& d, const int32_t* thresholds, BinEnt* bins, int32_t* 
 // d.chunks0) in cout and the counts in cnt (cleared before). A bin's rows
 // come in row order within each tile of rows, the tiles in any order.
 void select_all(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, hipStream_t s);
-// The same for the next round, at the end of a round's launches: by
-// d.flags->mode only the marked rows / none that is inert (marks of kept rows
-// are cleared), and the round's control: its records and swept rows added up,
-// each LP's state, and whether the rounds queued after it run. need: records a
-// round may add (room for them is checked; last: no round is queued after)
-void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int64_t need,
-                 bool last, int seq, hipStream_t s);
+// The same for the next round (after round seq), by d.flags->mode only the
+// marked rows / none that is inert
+void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int seq,
+                 hipStream_t s);
 // before rounds are queued: the record buffer's state, no stop, and (K > 1)
 // the LPs' flags cleared
 void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStream_t s);

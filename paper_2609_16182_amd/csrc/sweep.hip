@@ -392,10 +392,18 @@ __device__ __forceinline__ void lane_drop(const Dev& d, const El (&e)[C], double
 // rows of at most G*C entries: one G-lane group per row, C positions per lane
 // ---------------------------------------------------------------------------
 
+// a round's sweep: what its workgroups know of the round, and what they count
+struct RoundArgs {
+  int mode;       // bit 0: marked rows only; bit 1: inert rows skipped (direct lists)
+  uint8_t mark;   // the round's mark
+  int32_t* rows;  // LDS: rows and nonzeros swept (direct lists)
+  int32_t* nnz;
+};
+
 // what a lane reads of its row in a row block
 template <int C>
 struct RowIn {
-  bool vr, on;   // the lane's group has a row; the row is active
+  bool vr, on;   // the lane's group has a row; the row is swept
   int row, len;
   int64_t s0;
   double lhs, rhs;
@@ -403,28 +411,40 @@ struct RowIn {
 };
 
 // First level of a row block's loads: the bin entry of the lane's row. A
-// lane without a row reads the bin's first entry (the workgroup exists
-// because the bin has one), so no load of the row block is conditional.
+// lane beyond the bin's last row (cap rows at most) reads that one's entry, so
+// the load does not wait for the list's length.
 template <int G, int C>
-__device__ __forceinline__ void row_entry(const Dev& d, int bin, int vblock, RowIn<C>& in) {
-  const int per_block = PSL_BLOCK / G;
-  int gid = vblock * per_block + (int)(threadIdx.x / G);
-  int count = d.sel[bin].v;
-  in.vr = gid < count;
-  BinEnt be = d.bins[d.bin_off[bin] + (in.vr ? gid : 0)];
-  in.row = be.row;
-  in.s0 = be.start;
+__device__ __forceinline__ BinEnt row_entry(const Dev& d, int bin, int cap, int vblock) {
+  int gid = vblock * (PSL_BLOCK / G) + (int)(threadIdx.x / G);
+  return d.bins[d.bin_off[bin] + (gid < cap ? gid : cap - 1)];
+}
+
+template <int G, int C>
+__device__ __forceinline__ void row_take(const BinEnt& be, int count, int vblock, RowIn<C>& in) {
+  in.vr = vblock * (PSL_BLOCK / G) + (int)(threadIdx.x / G) < count;
+  in.row = in.vr ? be.row : 0;
+  in.s0 = in.vr ? be.start : 0;
   in.len = in.vr ? be.len : 0;
 }
 
-// Second level: the row's flag and sides and the lane's positions (columns
-// and coefficients); the third level, the bounds, is issued by load_els or
-// by the caller.
-template <int G, int C>
-__device__ __forceinline__ void row_data(const Dev& d, RowIn<C>& in) {
-  in.on = in.vr && d.row_on[in.row] != 0;
+// Second level: the row's flags and sides, beside the lane's positions
+// (columns and coefficients); the third level, the bounds, is issued by
+// load_els or by the caller. A row of the direct lists is swept when it is
+// active, of an LP still presolving and, by the mode, marked / not inert.
+template <int MODE, bool DIR, int C>
+__device__ __forceinline__ void row_data(const Dev& d, const RoundArgs& ra, RowIn<C>& in) {
   in.lhs = d.lhs[in.row];
   in.rhs = d.rhs[in.row];
+  if (MODE == MODE_COMPACT) {
+    in.on = in.vr && d.row_on[in.row] != 0;
+  } else if (DIR) {
+    uint8_t on = d.row_on[in.row], dt = d.dirty[in.row];
+    int2 rf = d.rinf[in.row];
+    in.on = in.vr && on != 0 && (!(ra.mode & 1) || dt == ra.mark) && row_lp_on(d, in.row) &&
+            (!(ra.mode & 2) || !row_inert(rf, in.lhs, in.rhs));
+  } else {
+    in.on = in.vr;  // selected
+  }
 }
 
 // statistics, decisions, candidates and removals of the row block's rows
@@ -487,7 +507,7 @@ __device__ __forceinline__ void row_block(const Dev& d, const CandSink& sk, RowI
     if (prop && dec.single && !dec.infeasible && captured) code = RC_SINGLETON;
     if (dec.infeasible && gl == 0) flag_infeasible(d, row_lp_of(d, row));
   }
-  if (vr && gl == 0) d.row_code[row] = code;
+  if (live && gl == 0) d.row_code[row] = code;
   if (live && gl == 0 && (code == RC_EMPTY || code == RC_REDUNDANT || is_forcing(code)))
     d.row_out[row] = row_out_of(code, st);
   if (code == RC_SINGLETON && mine) {
@@ -500,33 +520,54 @@ __device__ __forceinline__ void row_block(const Dev& d, const CandSink& sk, RowI
   }
 }
 
+// rows and nonzeros of a row block that are swept (direct lists)
+template <int G, int C, int MODE, bool DIR>
+__device__ __forceinline__ void count_swept(const Dev& d, const RoundArgs& ra, const RowIn<C>& in) {
+  if (MODE != MODE_ROUND || !DIR) return;
+  int gl = threadIdx.x & (G - 1);
+  unsigned long long m = __ballot(in.on && gl == 0);
+  int z = in.on && gl == 0 ? in.len : 0;
+  z = group_sum_int<PSL_WAVE>(z);
+  if (lane_id() == 0 && m) {
+    atomicAdd(ra.rows, (int)__popcll(m));
+    atomicAdd(ra.nnz, z);
+  }
+}
+
 // The workgroup's REP row blocks of the bin. With one position per lane the
 // loads of all REP blocks are issued level by level before any block is
 // processed, so a lane has REP rows' gathers in flight together.
-template <int G, int C, int MODE, int REP>
-__device__ __forceinline__ void sweep_rows(const Dev& d, const CandSink& sk, int bin, int lblock) {
-  int count = d.sel[bin].v;
-  if (lblock * REP * (PSL_BLOCK / G) >= count) return;  // uniform over the workgroup
+template <int G, int C, int MODE, int REP, bool DIR>
+__device__ __forceinline__ void sweep_rows(const Dev& d, const CandSink& sk, RoundArgs ra, bool over, int bin,
+                                           int lblock) {
+  const int cap = d.bin_off[bin + 1] - d.bin_off[bin];
   int gl = threadIdx.x & (G - 1);
   if (C == 1) {
+    BinEnt be[REP];
+#pragma unroll
+    for (int k = 0; k < REP; ++k) be[k] = row_entry<G, C>(d, bin, cap, lblock * REP + k);
+    int count = (DIR ? cap : d.sel[bin].v);
+#pragma unroll
+    for (int k = 0; k < REP; ++k) hold(be[k].row);
+    if (over || lblock * REP * (PSL_BLOCK / G) >= count) return;  // uniform over the workgroup
     RowIn<C> in[REP];
     int j[REP];
     double a[REP];
 #pragma unroll
-    for (int k = 0; k < REP; ++k) row_entry<G, C>(d, bin, lblock * REP + k, in[k]);
-#pragma unroll
     for (int k = 0; k < REP; ++k) {
-      row_data<G, C>(d, in[k]);
+      row_take<G, C>(be[k], count, lblock * REP + k, in[k]);
       bool v = gl < in[k].len;
       int64_t p = v ? in[k].s0 + gl : 0;
       j[k] = d.ci[p];
       a[k] = d.va[p];
       in[k].e[0].v = v;
+      row_data<MODE, DIR, C>(d, ra, in[k]);
     }
 #pragma unroll
     for (int k = 0; k < REP; ++k) {
-      double2 bb = d.bnd[j[k]];
       bool v = in[k].e[0].v;
+      double2 bb = make_double2(0.0, 0.0);
+      if (!DIR || in[k].on) bb = d.bnd[j[k]];
       in[k].e[0].j = v ? j[k] : 0;
       in[k].e[0].a = v ? a[k] : 0.0;
       in[k].e[0].lb = v ? bb.x : 0.0;
@@ -535,16 +576,22 @@ __device__ __forceinline__ void sweep_rows(const Dev& d, const CandSink& sk, int
 #pragma unroll
     for (int k = 0; k < REP; ++k) {
       if ((lblock * REP + k) * (PSL_BLOCK / G) >= count) break;  // uniform over the workgroup
+      if (DIR && MODE == MODE_ROUND && __ballot(in[k].on) == 0) continue;
+      count_swept<G, C, MODE, DIR>(d, ra, in[k]);
       row_block<G, C, MODE>(d, sk, in[k]);
     }
   } else {
+    int count = (DIR ? cap : d.sel[bin].v);
+    if (over) return;
 #pragma unroll 1
     for (int k = 0; k < REP; ++k) {
       int vb = lblock * REP + k;
       if (vb * (PSL_BLOCK / G) >= count) break;  // uniform over the workgroup
       RowIn<C> in;
-      row_entry<G, C>(d, bin, vb, in);
-      row_data<G, C>(d, in);
+      row_take<G, C>(row_entry<G, C>(d, bin, cap, vb), count, vb, in);
+      row_data<MODE, DIR, C>(d, ra, in);
+      if (DIR && MODE == MODE_ROUND && __ballot(in.on) == 0) continue;
+      count_swept<G, C, MODE, DIR>(d, ra, in);
       load_els<C>(d, in.s0, in.len, gl * C, true, in.e);
       row_block<G, C, MODE>(d, sk, in);
     }
@@ -584,20 +631,30 @@ __device__ __forceinline__ void pass_stats(const Dev& d, int64_t s0, int len, in
   __syncthreads();
 }
 
+// Is long row `row` (active) swept this round, from the direct lists? Every
+// workgroup of the row's chunks takes the same answer: the counts its inert
+// test reads are rewritten by the sweep with the values they have.
+__device__ __forceinline__ bool long_swept(const Dev& d, int row, RoundSeq rs) {
+  int mode = rs.full ? 0 : d.flags->mode;
+  return (!(mode & 1) || d.dirty[row] == round_mark(rs.seq)) && row_lp_on(d, row) &&
+         (!(mode & 2) || !row_inert(d.rinf[row], d.lhs[row], d.rhs[row]));
+}
+
 // partial statistics of one chunk (its passes combined in tree order)
 template <int MODE>
-__global__ void __launch_bounds__(PSL_BLOCK) k_long_stats(Dev d, int seq) {
+__global__ void __launch_bounds__(PSL_BLOCK) k_long_stats(Dev d, RoundSeq rs) {
   if (MODE == MODE_ROUND) {
-    if (round_over(d, seq)) return;
+    if (round_over(d, rs.seq)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) d.flags->stamp[0] = wall_clock64();
   }
-  if ((int)blockIdx.x >= d.sel[SEL_CHUNKS].v) return;
+  if ((int)blockIdx.x >= chunks_listed(d)) return;
   __shared__ double ps[2 * LONG_MAX_PASSES];
   __shared__ double wl[8];
   __shared__ int il[4];
   LongChunk ch = d.lchunk[blockIdx.x];
   int row = ch.row;
   if (!d.row_on[row]) return;
+  if (MODE == MODE_ROUND && d.direct && !long_swept(d, row, rs)) return;
   int64_t s0 = d.rp[row];
   int len = d.rp[row + 1] - (int)s0;
   int tmin = 0, tmax = 0, tl = 0;
@@ -658,7 +715,8 @@ __device__ __forceinline__ void long_totals(const Dev& d, const LongRow& lr, Row
 }
 
 // decisions and propagation over one chunk of a long row
-__device__ __forceinline__ void sweep_long_chunk(const Dev& d, const CandSink& sk, int chunk, double* lds) {
+__device__ __forceinline__ void sweep_long_chunk(const Dev& d, const CandSink& sk, const RoundArgs& ra, RoundSeq rs,
+                                                 int chunk, double* lds) {
   LongChunk ch = d.lchunk[chunk];
   int row = ch.row;
   if (!d.row_on[row]) {
@@ -666,6 +724,13 @@ __device__ __forceinline__ void sweep_long_chunk(const Dev& d, const CandSink& s
     return;
   }
   LongRow lr = d.lrow[ch.lrow];
+  if (d.direct) {
+    if (!long_swept(d, row, rs)) return;
+    if (ch.first == 0 && threadIdx.x == 0) {
+      atomicAdd(ra.rows, 1);
+      atomicAdd(ra.nnz, d.rp[row + 1] - d.rp[row]);
+    }
+  }
   int* li = (int*)(lds + 2);
   if (threadIdx.x < PSL_WAVE) {
     RowStat st;
@@ -732,15 +797,20 @@ __device__ __forceinline__ int long_first_block(const SweepGrid& g) {
 // launches (candidate regions and counts are indexed by it).
 enum { KIND_SHORT = 0, KIND_WIDE = 1, KIND_LONG = 2, KIND_ALL = 3 };
 
-template <int MODE, int KIND>
-__global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int base, int seq) {
+template <int MODE, int KIND, bool DIR>
+__global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int base, RoundSeq rs) {
   __shared__ double lds[8];
-  __shared__ int32_t lcount;
-  if (MODE == MODE_ROUND && round_over(d, seq)) return;
-  if (threadIdx.x == 0) lcount = 0;
+  __shared__ int32_t lcount, lrows, lnnz;
+  if (threadIdx.x == 0) lcount = lrows = lnnz = 0;
   __syncthreads();
+  const bool over = MODE == MODE_ROUND && round_over(d, rs.seq);
+  RoundArgs ra{0, 0, &lrows, &lnnz};
+  if (MODE == MODE_ROUND) {
+    ra.mode = rs.full ? 0 : d.flags->mode;
+    ra.mark = round_mark(rs.seq);
+  }
   int gb = blockIdx.x + base;  // global workgroup number
-  if (MODE == MODE_ROUND && gb == 0 && threadIdx.x == 0) {
+  if (MODE == MODE_ROUND && gb == 0 && threadIdx.x == 0 && !over) {
     unsigned long long t = wall_clock64();
     d.flags->stamp[1] = t;
     if (g.nb[BIN_LONG] == 0) d.flags->stamp[0] = t;
@@ -749,47 +819,38 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int bas
   int bin;
   int64_t start = cand_region_start(g, b, bin);
   int lfb = long_first_block(g);
-  if (MODE == MODE_ROUND && (KIND == KIND_LONG || (KIND == KIND_ALL && gb >= lfb)) &&
-      gb - lfb < d.sel[SEL_CHUNKS].v)
-    start = g.long_base + (int64_t)d.lchunk[gb - lfb].cand_off;
-  CandSink sk{d.cand + (start < 0 ? 0 : start), &lcount};
-  if (KIND == KIND_ALL) {
-    if (b < g.nb[BIN_G4]) {
-      sweep_rows<4, 1, MODE, 4>(d, sk, BIN_G4, b);
-    } else if ((b -= g.nb[BIN_G4]) < g.nb[BIN_G8]) {
-      sweep_rows<8, 1, MODE, 4>(d, sk, BIN_G8, b);
-    } else if ((b -= g.nb[BIN_G8]) < g.nb[BIN_G16]) {
-      sweep_rows<16, 1, MODE, 4>(d, sk, BIN_G16, b);
-    } else if ((b -= g.nb[BIN_G16]) < g.nb[BIN_W1]) {
-      sweep_rows<64, 1, MODE, 2>(d, sk, BIN_W1, b);
-    } else if ((b -= g.nb[BIN_W1]) < g.nb[BIN_W4]) {
-      sweep_rows<64, 4, MODE, 1>(d, sk, BIN_W4, b);
-    } else if ((b -= g.nb[BIN_W4]) < g.nb[BIN_W8]) {
-      sweep_rows<64, 8, MODE, 1>(d, sk, BIN_W8, b);
-    } else if (MODE == MODE_ROUND) {
-      if (gb - lfb < d.sel[SEL_CHUNKS].v) sweep_long_chunk(d, sk, gb - lfb, lds);
+  if (MODE == MODE_ROUND && (KIND == KIND_LONG || KIND == KIND_ALL) && gb >= lfb) {
+    // a chunk of a long row
+    int chunk = gb - lfb;
+    if (!over && chunk < chunks_listed(d)) {
+      CandSink sk{d.cand + g.long_base + (int64_t)d.lchunk[chunk].cand_off, &lcount};
+      sweep_long_chunk(d, sk, ra, rs, chunk, lds);
     }
-  } else if (KIND == KIND_SHORT) {
-    if (b < g.nb[BIN_G4]) {
-      sweep_rows<4, 1, MODE, 4>(d, sk, BIN_G4, b);
-    } else if ((b -= g.nb[BIN_G4]) < g.nb[BIN_G8]) {
-      sweep_rows<8, 1, MODE, 4>(d, sk, BIN_G8, b);
-    } else if ((b -= g.nb[BIN_G8]) < g.nb[BIN_G16]) {
-      sweep_rows<16, 1, MODE, 4>(d, sk, BIN_G16, b);
-    } else {
-      b -= g.nb[BIN_G16];
-      sweep_rows<64, 1, MODE, 2>(d, sk, BIN_W1, b);
+  } else {
+    CandSink sk{d.cand + start, &lcount};
+    if (KIND != KIND_WIDE && b < g.nb[BIN_G4]) {
+      sweep_rows<4, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G4, b);
+    } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G4]) < g.nb[BIN_G8]) {
+      sweep_rows<8, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G8, b);
+    } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G8]) < g.nb[BIN_G16]) {
+      sweep_rows<16, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G16, b);
+    } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G16]) < g.nb[BIN_W1]) {
+      sweep_rows<64, 1, MODE, 2, DIR>(d, sk, ra, over, BIN_W1, b);
+    } else if (KIND != KIND_SHORT) {
+      b -= KIND == KIND_WIDE ? g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1] : g.nb[BIN_W1];
+      if (b < g.nb[BIN_W4]) sweep_rows<64, 4, MODE, 1, DIR>(d, sk, ra, over, BIN_W4, b);
+      else sweep_rows<64, 8, MODE, 1, DIR>(d, sk, ra, over, BIN_W8, b - g.nb[BIN_W4]);
     }
-  } else if (KIND == KIND_WIDE) {
-    b -= g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1];
-    if (b < g.nb[BIN_W4]) sweep_rows<64, 4, MODE, 1>(d, sk, BIN_W4, b);
-    else sweep_rows<64, 8, MODE, 1>(d, sk, BIN_W8, b - g.nb[BIN_W4]);
-  } else if (MODE == MODE_ROUND) {
-    if (b - lfb < d.sel[SEL_CHUNKS].v) sweep_long_chunk(d, sk, b - lfb, lds);
   }
-  if (MODE == MODE_ROUND) {
+  if (MODE == MODE_ROUND && !over) {
     __syncthreads();
-    if (threadIdx.x == 0) d.cand_cnt[gb] = lcount;
+    if (threadIdx.x == 0) {
+      d.cand_cnt[gb] = lcount;
+      if (DIR && lrows) {
+        atomicAdd(&d.flags->swept[gb % SWEPT_SLOTS].rows, (unsigned long long)lrows);
+        atomicAdd(&d.flags->swept[gb % SWEPT_SLOTS].nnz, (unsigned long long)lnnz);
+      }
+    }
   }
 }
 
@@ -863,9 +924,12 @@ __device__ __forceinline__ bool dual_fix_of(double c, double lo, double up, unsi
 __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
   k = 0;
   double2 b = d.bnd[j];
+  longlong2 key = *reinterpret_cast<const longlong2*>(&d.bkey[2 * (int64_t)j]);
+  int left = d.col_len[j];
+  hold(left);
   if (b.x == b.y) return 0;
-  double lo = dunkey(d.bkey[2 * (int64_t)j]);
-  double up = dunkey(d.bkey[2 * (int64_t)j + 1]);
+  double lo = dunkey(key.x);
+  double up = dunkey(key.y);
   uint8_t code = 0;
   if (lo != b.x) {
     code |= CC_LB;
@@ -881,7 +945,7 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
   if (fin && up - lo <= d.cfg.fix_tol * mx1(lo)) {
     code |= CC_FIX;
     ++k;
-  } else if (d.col_len[j] == 0) {
+  } else if (left == 0) {
     double v = empty_value(d.c[j], lo, up);
     if (is_inf(v)) {
       code |= CC_UNBOUNDED;
@@ -988,6 +1052,12 @@ __device__ __forceinline__ int round_mode(const Dev& d, const RoundMode& rm, int
   return (incr ? 1 : 0) | (counts ? 2 : 0);
 }
 
+// fields of a word of the sums
+#define SUP_REC(v) ((int)((v) & 0xFFFFFFull))
+#define SUP_FIN(v) ((int)((v) >> 24 & 0xFFFFFull))
+#define SUP_TILES(v) ((int)((v) >> 44))
+static_assert(3ull * DEC_TILE * SUPER < (1ull << 24), "records of 64 tiles");
+
 // the sums of 64 tiles scanned, the round's totals, the next mode (one
 // workgroup)
 __device__ __forceinline__ void decide_totals(const Dev& d, const TileGrid& tg, const RoundMode& rm) {
@@ -1000,7 +1070,7 @@ __device__ __forceinline__ void decide_totals(const Dev& d, const TileGrid& tg, 
       v = __hip_atomic_load(&d.super[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       atomicExch(&d.super[k], 0ull);
     }
-    int c = (int)(v & 0xFFFFFFFFull), f = (int)(v >> 32), tot, ftot, rtot;
+    int c = SUP_REC(v), f = SUP_FIN(v), tot, ftot, rtot;
     int pre = block_excl_scan(c, &tot);
     if (k < ns) d.super_off[k] = run + pre;
     block_excl_scan(f, &ftot);
@@ -1010,17 +1080,21 @@ __device__ __forceinline__ void decide_totals(const Dev& d, const TileGrid& tg, 
     removed += rtot;
   }
   if (threadIdx.x == 0) {
-    d.super_done[ns] = 0;
-    d.flags->round_total = run;
-    d.flags->rows_removed = removed;
-    d.flags->fin_cols = fin;
-    d.flags->mode = round_mode(d, rm, run - removed, fin);
-    int64_t rows = 0, nnz = d.sel[SEL_NNZ].v;
+    *d.super_done = 0;
+    Flags& F = *d.flags;
+    F.round_total = run;
+    F.rows_removed = removed;
+    F.fin_cols = fin;
+    F.mode = round_mode(d, rm, run - removed, fin);
+    F.rec_base = F.rec_at;
+    if (!d.direct) {
+      int64_t rows = 0, nnz = d.sel[SEL_NNZ].v;
 #pragma unroll
-    for (int b = 0; b < NBINS; ++b) rows += d.sel[b].v;
-    d.flags->sum_rows += rows;
-    d.flags->sum_nnz += nnz;
-    d.flags->sum_cols += nnz < d.n ? nnz : d.n;
+      for (int b = 0; b < NBINS; ++b) rows += d.sel[b].v;
+      F.sum_rows += rows;
+      F.sum_nnz += nnz;
+      F.sum_cols += nnz < d.n ? nnz : d.n;
+    }
   }
 }
 
@@ -1030,14 +1104,14 @@ __device__ __forceinline__ void decide_totals(const Dev& d, const TileGrid& tg, 
 // of each tile.
 __global__ void __launch_bounds__(DEC_BLOCK) k_decide(Dev d, SweepGrid g, TileGrid tg, RoundMode rm, int seq,
                                                       int32_t* tile_sum) {
-  if (round_over(d, seq)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  const bool over = round_over(d, seq);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !over) {
     unsigned long long t = wall_clock64();
     d.flags->stamp[2] = t;
     if (tg.nsrc == 0) d.flags->stamp[0] = d.flags->stamp[1] = t;  // no row to sweep
   }
   if ((int)blockIdx.x < tg.nsrc) {
-    sources(d, g, blockIdx.x);
+    if (!over) sources(d, g, blockIdx.x);
     return;
   }
   __shared__ int list[DEC_TILE];
@@ -1048,37 +1122,41 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide(Dev d, SweepGrid g, TileGr
   int t = (int)blockIdx.x - tg.nsrc;
   const bool rows = t < tg.row_tiles;
   const int tile = rows ? t : tg.col0 + (t - tg.row_tiles);
+  const int64_t i0 = (int64_t)(rows ? tile : tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
+  const int64_t lim = rows ? d.m : d.n;
+  uint32_t traw = 0, cw = 0, vm = 0;  // touched, codes
+  if (i0 < lim) {
+    vm = valid_bytes(lim - i0);
+    cw = code_word(rows ? d.row_code : d.col_code, i0) & vm;
+    if (!rows) traw = code_word(d.touch, i0);
+  }
+  hold(cw);
+  hold(traw);
+  if (over) return;
   int c = 0, nt = 0, ntot = 0, fin = 0;
   if (rows) {
-    int64_t i0 = (int64_t)tile * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
-    if (i0 < d.m) {
-      uint32_t cw = code_word(d.row_code, i0) & valid_bytes(d.m - i0);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) c += ((cw >> (8 * b)) & 0xFFu) != RC_KEEP;
-    }
-  } else {
-    int64_t j0 = (int64_t)(tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
-    uint32_t tw = 0;
-    if (j0 < d.n) {
-      uint32_t vm = valid_bytes(d.n - j0);
-      uint32_t traw = code_word(d.touch, j0);
-      tw = traw & vm;
-      uint32_t cw = code_word(d.col_code, j0) & vm;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        bool touched = ((tw >> (8 * b)) & 0xFFu) != 0;
-        nt += touched;
-        // a code left from an earlier round of an untouched column
-        if (!touched && ((cw >> (8 * b)) & 0xFFu)) d.col_code[j0 + b] = 0;
+    for (int b = 0; b < 4; ++b)
+      if (((cw >> (8 * b)) & 0xFFu) != RC_KEEP) {
+        ++c;
+        if (d.K > 1) d.lpo[d.row_lp[i0 + b]].total = 1;  // the LP changes this round
       }
-      if (tw) reinterpret_cast<uint32_t*>(d.touch)[j0 >> 2] = traw & ~vm;
+  } else {
+    uint32_t tw = traw & vm;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      bool touched = ((tw >> (8 * b)) & 0xFFu) != 0;
+      nt += touched;
+      // a code left from an earlier round of an untouched column
+      if (!touched && ((cw >> (8 * b)) & 0xFFu)) d.col_code[i0 + b] = 0;
     }
+    if (tw) reinterpret_cast<uint32_t*>(d.touch)[i0 >> 2] = traw & ~vm;
     // the touched columns of the wavefront, in LDS, dealt out to its lanes
     int pre;
     wave_small_scan(nt, pre, ntot);
 #pragma unroll
     for (int b = 0; b < 4; ++b)
-      if ((tw >> (8 * b)) & 0xFFu) wl[pre++] = (int)(j0 + b);
+      if ((tw >> (8 * b)) & 0xFFu) wl[pre++] = (int)(i0 + b);
   }
   __syncthreads();
   for (int e = lane; e < ntot; e += PSL_WAVE) {
@@ -1088,6 +1166,7 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide(Dev d, SweepGrid g, TileGr
     d.col_code[j] = code;
     c += kk;
     fin += (code & (CC_LBFIN | CC_UBFIN)) != 0;
+    if (kk && d.K > 1) d.lpo[d.col_lp[j]].total = 1;
   }
   // the tile's counts: wavefront totals by ballots, summed by thread 0
   int pre_w, tot_w, fin_w;
@@ -1110,12 +1189,10 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide(Dev d, SweepGrid g, TileGr
     int end = rows ? tg.row_tiles : tg.tiles;  // tiles of this 64 that exist
     int members = (end < (sp + 1) * SUPER ? end : (sp + 1) * SUPER) - sp * SUPER;
     last = 0;
-    // each add is issued once the one before it has returned
-    unsigned long long o = atomicAdd(&d.super[sp], (unsigned long long)tot | ((unsigned long long)ftot << 32));
-    if (o != ~0ull && atomicAdd(&d.super_done[sp], 1) == members - 1) {
-      int ns = (tg.tiles + SUPER - 1) / SUPER;
-      if (atomicExch(&d.super_done[sp], 0) == members) last = atomicAdd(&d.super_done[ns], 1) == ns - 1;
-    }
+    // the second add is issued once the first has returned
+    unsigned long long o =
+        atomicAdd(&d.super[sp], (unsigned long long)tot | ((unsigned long long)ftot << 24) | (1ull << 44));
+    if (SUP_TILES(o) == members - 1) last = atomicAdd(d.super_done, 1) == (tg.tiles + SUPER - 1) / SUPER - 1;
   }
   __syncthreads();
   if (last) decide_totals(d, tg, rm);
@@ -1214,11 +1291,11 @@ __device__ __forceinline__ void emit_col(const Dev& d, int j, uint8_t code, int 
 // One entry (q, row i) of a changed column: mark the row (when the next
 // round sweeps dirty rows only), and (with count) lower its infinite-
 // contribution counts when the column's lb / ub became finite.
-__device__ __forceinline__ void mark_entry(const Dev& d, int64_t q, int code, bool mark, bool count) {
+__device__ __forceinline__ void mark_entry(const Dev& d, int64_t q, int code, bool mark, bool count, uint8_t with) {
   int i = d.ri[q];
   if (mark) {
-    d.dirty[i] = 1;
-    d.dirty_tile[i >> 10] = 1;
+    d.dirty[i] = with;
+    if (!d.direct) d.dirty_tile[i >> 10] = with;
   }
   if (count && (code & (CC_LBFIN | CC_UBFIN))) {
     bool pos = d.cva[q] > 0;
@@ -1248,7 +1325,7 @@ __device__ __forceinline__ void wave_scan5(int v, int& pre, int& tot) {
 }
 
 // marks of the wavefront's columns wl[0 .. n) (any of them with records)
-__device__ __forceinline__ void mark_cols(const Dev& d, const int* wl, int n, int mode) {
+__device__ __forceinline__ void mark_cols(const Dev& d, const int* wl, int n, int mode, uint8_t with) {
   int lane = lane_id();
   for (int c0 = 0; c0 < n; c0 += PSL_WAVE) {
     int q0 = 0, q1 = 0, code = 0;
@@ -1281,7 +1358,7 @@ __device__ __forceinline__ void mark_cols(const Dev& d, const int* wl, int n, in
       }
       int q = __shfl(q0, lo, PSL_WAVE) + (e - __shfl(pre, lo, PSL_WAVE));
       int cl = __shfl(code, lo, PSL_WAVE);
-      if (e < tot) mark_entry(d, q, cl, mode & 1, mode & 2);
+      if (e < tot) mark_entry(d, q, cl, mode & 1, mode & 2, with);
     }
     // longer ones: the wavefront walks them one after another
     unsigned long long mask = __ballot(len > MARK_SHORT && len <= MARK_DENSE);
@@ -1289,7 +1366,7 @@ __device__ __forceinline__ void mark_cols(const Dev& d, const int* wl, int n, in
       int l = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
       int a = __shfl(q0, l, PSL_WAVE), b = __shfl(q1, l, PSL_WAVE), cl = __shfl(code, l, PSL_WAVE);
-      for (int q = a + lane; q < b; q += PSL_WAVE) mark_entry(d, q, cl, mode & 1, mode & 2);
+      for (int q = a + lane; q < b; q += PSL_WAVE) mark_entry(d, q, cl, mode & 1, mode & 2, with);
     }
   }
 }
@@ -1301,6 +1378,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_mark_dense(Dev d, int seq) {
   __shared__ int32_t cnt;
   if (round_over(d, seq)) return;
   int mode = d.flags->mode;
+  const uint8_t with = round_mark(seq + 1);
   if (mode == 0) return;
   int nd = *d.n_dense;
   for (int k0 = 0; k0 < nd; k0 += 1024) {
@@ -1318,10 +1396,64 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_mark_dense(Dev d, int seq) {
       int64_t q1 = d.cp[j + 1];
       for (int64_t q = d.cp[j] + (int64_t)blockIdx.x * PSL_BLOCK + threadIdx.x; q < q1;
            q += (int64_t)gridDim.x * PSL_BLOCK)
-        mark_entry(d, q, code, mode & 1, mode & 2);
+        mark_entry(d, q, code, mode & 1, mode & 2, with);
     }
     __syncthreads();
   }
+}
+
+// The round's control (one workgroup; sweep.h, RoundCtl). d.lp_round: the
+// number of the LP's running round while it propagates, minus its last one once
+// it does not.
+// A round that is not run only hands the numbers on.
+__device__ __forceinline__ void round_control(const Dev& d, const RoundCtl& ctl, bool over, int seq) {
+  __shared__ int go_on;
+  Flags& f = *d.flags;
+  if (over) {
+    if (d.K > 1)
+      for (int k = threadIdx.x; k < d.K; k += blockDim.x) d.lp_round_next[k] = d.lp_round[k];
+    return;
+  }
+  if (threadIdx.x == 0) go_on = d.K == 1 && !f.infeasible && !f.unbounded && f.round_total != 0;
+  __syncthreads();
+  if (d.K > 1) {
+    bool any = false;
+    for (int k = threadIdx.x; k < d.K; k += blockDim.x) {
+      int r = d.lp_round[k];
+      if (r > 0) {
+        bool more = !d.lpf[k].infeasible && !d.lpf[k].unbounded && d.lpo[k].total != 0;
+        d.lpo[k].total = 0;
+        r = more ? r + 1 : -r;
+        any = any || more;
+      }
+      d.lp_round_next[k] = r;
+    }
+    if (any) go_on = 1;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  if (d.direct) {
+    int64_t rows = 0, nnz = 0;
+    for (int k = 0; k < SWEPT_SLOTS; ++k) {
+      rows += f.swept[k].rows;
+      nnz += f.swept[k].nnz;
+    }
+    int64_t z = nnz - f.sum_nnz;
+    f.sum_cols += z < d.n ? z : d.n;
+    f.sum_rows = rows;
+    f.sum_nnz = nnz;
+  }
+  f.rounds_done += 1;
+  f.rec_at = f.rec_base + f.round_total;
+  unsigned long long now = wall_clock64();
+  f.ticks[0] += f.stamp[1] - f.stamp[0];
+  f.ticks[1] += f.stamp[2] - f.stamp[1];
+  f.ticks[2] += now - f.stamp[2];
+  if (!go_on || (!ctl.last && f.rec_at + ctl.need > f.rec_cap)) f.stop_at = seq;
+}
+
+__global__ void __launch_bounds__(PSL_BLOCK) k_round_control(Dev d, RoundCtl ctl, int seq) {
+  round_control(d, ctl, round_over(d, seq), seq);
 }
 
 // Records of the round in index order: a tile's offset is the sum of the tiles
@@ -1330,32 +1462,39 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_mark_dense(Dev d, int seq) {
 // before it (ballots inside the wavefront, the wavefronts' totals through LDS).
 // The indices with records are compacted per wavefront and dealt out to its
 // lanes, each writing its index's records at that position; a wavefront of
-// columns then marks their rows for the next round. Also marks the LPs that
-// changed (batches) and clears the next selection's counts.
-__global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t* tile_sum, TileGrid tg, int round,
-                                                           int seq) {
-  if (round_over(d, seq)) return;
-  if (blockIdx.x == 0 && threadIdx.x < SEL_N) d.flags->sel[1][threadIdx.x].v = 0;
+// columns then marks their rows for the next round. The last workgroup is the
+// round's control. Also clears the next selection's counts.
+__global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t* tile_sum, TileGrid tg, RoundCtl ctl,
+                                                           int round, int seq) {
+  const bool over = round_over(d, seq);
   const bool rows = (int)blockIdx.x < tg.row_tiles;
   const int tile = rows ? (int)blockIdx.x : tg.col0 + ((int)blockIdx.x - tg.row_tiles);
-  int tsum = tile_sum[tile];
-  if (tsum == 0) return;  // a tile without records
+  if (tile == tg.tiles) {
+    if (ctl.by_emit) round_control(d, ctl, over, seq);
+    return;
+  }
+  if (!over && !d.direct && blockIdx.x == 0 && threadIdx.x < SEL_N) d.flags->sel[1][threadIdx.x].v = 0;
   __shared__ int list[DEC_TILE], lpos[DEC_TILE];
   __shared__ int wtot[DEC_WAVES];
   int w = threadIdx.x >> 6, lane = lane_id();
-  int64_t t0 = (int64_t)(rows ? tile : tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
-  int64_t lim = rows ? d.m : d.n;
+  // one level of loads: the tile's count, the codes, the tile's offset
+  const int tsum = tile_sum[tile];
   const int mode = d.flags->mode;
+  const int64_t t0 = (int64_t)(rows ? tile : tile - tg.col0) * DEC_TILE + (int64_t)threadIdx.x * DEC_ITEMS;
+  const int64_t lim = rows ? d.m : d.n;
+  uint32_t cw = 0;
+  if (t0 < lim) cw = code_word(rows ? d.row_code : d.col_code, t0) & valid_bytes(lim - t0);
   int before = lane < (tile & (SUPER - 1)) ? tile_sum[(tile & ~(SUPER - 1)) + lane] : 0;
+  const int64_t base = d.flags->rec_base + d.super_off[tile / SUPER];
+  hold(cw);
+  hold(before);
+  hold(base);
+  if (over || tsum == 0) return;  // a tile without records
   uint32_t cnt4 = 0;  // the records of the lane's 4 indices, a byte each
-  if (t0 < lim) {
-    uint32_t vm = valid_bytes(lim - t0);
-    uint32_t cw = code_word(rows ? d.row_code : d.col_code, t0) & vm;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      uint32_t code = (cw >> (8 * b)) & 0xFFu;
-      cnt4 |= (uint32_t)(rows ? code != RC_KEEP : col_recs(code)) << (8 * b);
-    }
+  for (int b = 0; b < 4; ++b) {
+    uint32_t code = (cw >> (8 * b)) & 0xFFu;
+    cnt4 |= (uint32_t)(rows ? code != RC_KEEP : col_recs(code)) << (8 * b);
   }
   int c = 0, ni = 0;
 #pragma unroll
@@ -1385,50 +1524,51 @@ __global__ void __launch_bounds__(DEC_BLOCK) k_decide_emit(Dev d, const int32_t*
     }
   }
   __syncthreads();
-  Record* r0 = d.rec + d.flags->rec_at + d.super_off[tile / SUPER] + before;
+  Record* r0 = d.rec + base + before;
   for (int e = lane; e < itot; e += PSL_WAVE) {
     int x = wl[e];
     Record* r = r0 + wp[e];
-    int lp;
-    if (rows) {
-      lp = row_lp_of(d, x);
-      emit_row(d, x, round_of(d, lp, round), r);
-    } else {
-      lp = col_lp_of(d, x);
-      emit_col(d, x, d.col_code[x], round_of(d, lp, round), r);
-    }
-    if (d.K > 1) d.lpo[lp].total = 1;  // the LP changed this round
+    if (rows) emit_row(d, x, round_of(d, row_lp_of(d, x), round), r);
+    else emit_col(d, x, d.col_code[x], round_of(d, col_lp_of(d, x), round), r);
   }
-  if (!rows && mode != 0) mark_cols(d, wl, itot, mode);
+  if (!rows && mode != 0) mark_cols(d, wl, itot, mode, round_mark(seq + 1));
 }
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-void launch_long_stats(const Dev& d, int mode, int chunks, int seq, hipStream_t s) {
+void launch_long_stats(const Dev& d, int mode, int chunks, RoundSeq rs, hipStream_t s) {
   if (chunks == 0) return;
-  if (mode == MODE_ROUND) hipLaunchKernelGGL(k_long_stats<MODE_ROUND>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, seq);
-  else hipLaunchKernelGGL(k_long_stats<MODE_COMPACT>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, 0);
+  if (mode == MODE_ROUND) hipLaunchKernelGGL(k_long_stats<MODE_ROUND>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, rs);
+  else hipLaunchKernelGGL(k_long_stats<MODE_COMPACT>, dim3(chunks), dim3(PSL_BLOCK), 0, s, d, rs);
 }
 
-void launch_sweep(const Dev& d, const SweepGrid& g, int mode, int seq, hipStream_t s) {
+template <int MODE, bool DIR>
+static void sweep_launches(const Dev& d, const SweepGrid& g, bool split, RoundSeq rs, hipStream_t s) {
   int n_short = g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1];
   int n_wide = g.nb[BIN_W4] + g.nb[BIN_W8];
-  int n_long = g.nb[BIN_LONG];
+  int n_long = MODE == MODE_ROUND ? g.nb[BIN_LONG] : 0;
   dim3 blk(PSL_BLOCK);
-  if (mode == MODE_ROUND) {
+  if (!split) {
     int total = n_short + n_wide + n_long;
-    if (total) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_ALL>), dim3(total), blk, 0, s, d, g, 0, seq);
-  } else if (mode == 2) {
-    if (n_short) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_SHORT>), dim3(n_short), blk, 0, s, d, g, 0, seq);
-    if (n_wide) hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_WIDE>), dim3(n_wide), blk, 0, s, d, g, n_short, seq);
-    if (n_long)
-      hipLaunchKernelGGL((k_sweep<MODE_ROUND, KIND_LONG>), dim3(n_long), blk, 0, s, d, g, n_short + n_wide, seq);
-  } else {
-    if (n_short) hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_SHORT>), dim3(n_short), blk, 0, s, d, g, 0, 0);
-    if (n_wide) hipLaunchKernelGGL((k_sweep<MODE_COMPACT, KIND_WIDE>), dim3(n_wide), blk, 0, s, d, g, n_short, 0);
+    if (total) hipLaunchKernelGGL((k_sweep<MODE, KIND_ALL, DIR>), dim3(total), blk, 0, s, d, g, 0, rs);
+    return;
+  }
+  if (n_short) hipLaunchKernelGGL((k_sweep<MODE, KIND_SHORT, DIR>), dim3(n_short), blk, 0, s, d, g, 0, rs);
+  if (n_wide) hipLaunchKernelGGL((k_sweep<MODE, KIND_WIDE, DIR>), dim3(n_wide), blk, 0, s, d, g, n_short, rs);
+  if (n_long)
+    hipLaunchKernelGGL((k_sweep<MODE, KIND_LONG, DIR>), dim3(n_long), blk, 0, s, d, g, n_short + n_wide, rs);
+}
+
+void launch_sweep(const Dev& d, const SweepGrid& g, int mode, RoundSeq rs, hipStream_t s) {
+  if (mode == MODE_COMPACT) {
+    if (d.direct) sweep_launches<MODE_COMPACT, true>(d, g, true, rs, s);
+    else sweep_launches<MODE_COMPACT, false>(d, g, true, rs, s);
     if (d.nlong > 0)
-      hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), blk, 0, s, d);
+      hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), dim3(PSL_BLOCK), 0, s, d);
+  } else {
+    if (d.direct) sweep_launches<MODE_ROUND, true>(d, g, mode == 2, rs, s);
+    else sweep_launches<MODE_ROUND, false>(d, g, mode == 2, rs, s);
   }
 }
 
@@ -1436,14 +1576,14 @@ void launch_sweep(const Dev& d, const SweepGrid& g, int mode, int seq, hipStream
 // the compaction-mode chunk partials
 void launch_long_consts(const Dev& d, hipStream_t s) {
   if (d.nlong == 0) return;
-  launch_long_stats(d, MODE_COMPACT, d.nchunks, 0, s);
+  launch_long_stats(d, MODE_COMPACT, d.nchunks, RoundSeq{0, 1}, s);
   hipLaunchKernelGGL(k_long_finish_compact, dim3((d.nlong + 3) / 4), dim3(PSL_BLOCK), 0, s, d);
 }
 
 // the round's sources, decisions, records and marks; the record total goes to
 // d.flags->round_total
-void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, bool dense, int round, int seq,
-                   int32_t* tile_sum, hipStream_t s) {
+void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, const RoundCtl& ctl, bool dense, int round,
+                   int seq, int32_t* tile_sum, hipStream_t s) {
   TileGrid tg;
   tg.nsrc = 0;
   for (int b = 0; b < NBINS; ++b) tg.nsrc += g.nb[b];
@@ -1452,9 +1592,13 @@ void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, bool d
   tg.tiles = (int)decide_tiles(d.m, d.n);
   int nt = tg.row_tiles + tg.tiles - tg.col0;
   hipLaunchKernelGGL(k_decide, dim3((unsigned)(tg.nsrc + nt)), dim3(DEC_BLOCK), 0, s, d, g, tg, rm, seq, tile_sum);
-  hipLaunchKernelGGL(k_decide_emit, dim3((unsigned)nt), dim3(DEC_BLOCK), 0, s, d, (const int32_t*)tile_sum, tg, round,
-                     seq);
+  hipLaunchKernelGGL(k_decide_emit, dim3((unsigned)(nt + 1)), dim3(DEC_BLOCK), 0, s, d, (const int32_t*)tile_sum, tg,
+                     ctl, round, seq);
   if (dense) hipLaunchKernelGGL(k_mark_dense, dim3(1024), dim3(PSL_BLOCK), 0, s, d, seq);
+}
+
+void launch_control(const Dev& d, const RoundCtl& ctl, int seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_round_control, dim3(1), dim3(PSL_BLOCK), 0, s, d, ctl, seq);
 }
 
 int long_max_passes() { return LONG_MAX_PASSES; }
