@@ -484,13 +484,14 @@ static psl_status read_flags(psl_presolver* p) {
 
 
 // workgroups per bin for a launch over `rows` rows of each bin (and chunks)
-static SweepGrid grid_of(const int32_t* rows, int32_t chunks) {
+static SweepGrid grid_of(const int32_t* rows, int32_t chunks, int one) {
   SweepGrid g;
+  g.one = one;
   g.long_base = 0;
   for (int b = 0; b < BIN_LONG; ++b) {
-    int per_wg = bin_rows(b) * bin_rep(b);  // rows one workgroup sweeps
+    int per_wg = bin_rows(b) * bin_rep(b, one);  // rows one workgroup sweeps
     g.nb[b] = (rows[b] + per_wg - 1) / per_wg;
-    g.long_base += (int64_t)g.nb[b] * cand_region(b);
+    g.long_base += (int64_t)g.nb[b] * cand_region(b, one);
   }
   g.nb[BIN_LONG] = chunks;
   return g;
@@ -501,20 +502,20 @@ static SweepGrid grid_of(const int32_t* rows, int32_t chunks) {
 static void use_full_view(psl_presolver* p) {
   Dev& d = p->d;
   if (d.direct) {  // the ingest's lists, always
-    p->grid = grid_of(p->bin_counts, d.nchunks);
+    p->grid = grid_of(p->bin_counts, d.nchunks, d.direct);
     return;
   }
   select_all(d, p->thresholds[0], p->thresholds[2], p->bins_a, p->chunks_a, d.flags->sel[0], p->stream);
   d.bins = p->bins_a;
   d.lchunk = p->chunks_a;
   d.sel = d.flags->sel[0];
-  p->grid = grid_of(p->bin_counts, d.nchunks);
+  p->grid = grid_of(p->bin_counts, d.nchunks, d.direct);
 }
 
 // the rows the last round's selection chose
 static void use_round_view(psl_presolver* p) {
   Dev& d = p->d;
-  p->grid = grid_of(p->bin_counts, d.nchunks);
+  p->grid = grid_of(p->bin_counts, d.nchunks, d.direct);
   if (d.direct) return;
   d.bins = p->bins_s;
   d.lchunk = p->chunks_s;
@@ -619,7 +620,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   if (p->htot[0] > p->chunk_cap) return fail(p, PSL_ERR_CAPACITY, "too many long-row chunks");
   d.nchunks = p->htot[0];
   d.colid = nullptr;
-  p->grid = grid_of(p->bin_counts, d.nchunks);
+  p->grid = grid_of(p->bin_counts, d.nchunks, d.direct);
   if (p->grid.long_base + (int64_t)p->htot[1] > p->cand_cap)
     return fail(p, PSL_ERR_CAPACITY, "candidate buffer too small for the row bins");
 
@@ -1129,7 +1130,7 @@ static psl_status launch_round(psl_presolver* p) {
       if (R.queued == 1 && !d.direct) {  // the counts were read with the round before
         int32_t rows[NBINS];
         for (int b = 0; b < NBINS; ++b) rows[b] = p->hflags->sel[1][b].v;
-        p->grid = grid_of(rows, p->hflags->sel[1][SEL_CHUNKS].v);
+        p->grid = grid_of(rows, p->hflags->sel[1][SEL_CHUNKS].v, 0);
       }
     } else {
       use_full_view(p);

@@ -376,6 +376,7 @@ __device__ __forceinline__ void hash_wave_block(const Dev& d, const ParScratch& 
 }
 
 // one workgroup per workgroup of the sweep's grid (the same row blocks)
+template <int REP>
 __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, SweepGrid g) {
   int b = blockIdx.x;
   for (int bin = 0; bin < BIN_LONG; ++bin) {
@@ -383,11 +384,11 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_hash(Dev d, ParScratch P, Swe
       b -= g.nb[bin];
       continue;
     }
-    int rep = bin_rep(bin);
+    int rep = bin_rep(bin, g.one);
     int count = bin_rows_listed(d, bin);
-    if (bin == BIN_G4) hash_groups<4, 4>(d, P, bin, b * rep);
-    else if (bin == BIN_G8) hash_groups<8, 4>(d, P, bin, b * rep);
-    else if (bin == BIN_G16) hash_groups<16, 4>(d, P, bin, b * rep);
+    if (bin == BIN_G4) hash_groups<4, REP>(d, P, bin, b * rep);
+    else if (bin == BIN_G8) hash_groups<8, REP>(d, P, bin, b * rep);
+    else if (bin == BIN_G16) hash_groups<16, REP>(d, P, bin, b * rep);
     else
       for (int k = 0; k < rep; ++k) {
         int vb = b * rep + k;
@@ -684,7 +685,8 @@ void launch_par_hash(const Dev& d, const ParScratch& p, const SweepGrid& g, hipS
   for (int b = 0; b < NBINS; ++b) total += g.nb[b];
   if (d.nlong > 0)
     hipLaunchKernelGGL(k_par_long_first, dim3((d.nlong + 3) / 4), dim3(PSL_BLOCK), 0, s, d, p);
-  if (total > 0) hipLaunchKernelGGL(k_par_hash, dim3(total), dim3(PSL_BLOCK), 0, s, d, p, g);
+  if (total > 0 && g.one) hipLaunchKernelGGL(k_par_hash<1>, dim3(total), dim3(PSL_BLOCK), 0, s, d, p, g);
+  else if (total > 0) hipLaunchKernelGGL(k_par_hash<4>, dim3(total), dim3(PSL_BLOCK), 0, s, d, p, g);
   if (d.nlong > 0)
     hipLaunchKernelGGL(k_par_long_insert, dim3((d.nlong + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d, p);
   if (d.m > 0) hipLaunchKernelGGL(k_par_vlist, dim3((d.m + VLIST_BLOCK - 1) / VLIST_BLOCK), dim3(VLIST_BLOCK), 0, s, d, p);

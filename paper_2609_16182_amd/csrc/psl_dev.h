@@ -407,8 +407,14 @@ __device__ __forceinline__ void wave_append(bool pred, const Cand& e, Cand* list
 // candidate-region sizes (entries) of the sweep bins, per workgroup
 // Row blocks (of 256 threads' rows) one workgroup of a bin sweeps in turn:
 // short rows give a wavefront little work, so their workgroups take several.
-__host__ __device__ __forceinline__ int bin_rep(int bin) {
-  return bin <= BIN_G16 ? 4 : bin == BIN_W1 ? 2 : 1;
+// With the direct lists (one: an LP of at most 5e5 nonzeros) the chip has more
+// room than there are row blocks and a workgroup takes one: the chains of four
+// blocks one after another were the launch's time (2000 rows: 16.5 us a sweep,
+// 8.0 with one block; a presolve 1.64 and 1.28 ms). Selected lists keep four:
+// with one block a wavefront has fewer gathers in flight (1e7 rows: 77 ms with
+// four, 90 with one; a 4096-LP batch 77 and 88 ms).
+__host__ __device__ __forceinline__ int bin_rep(int bin, int one) {
+  return one ? 1 : bin <= BIN_G16 ? 4 : bin == BIN_W1 ? 2 : 1;
 }
 
 // rows of a row block of the bin
@@ -416,10 +422,10 @@ __host__ __device__ __forceinline__ int bin_rows(int bin) {
   return bin == BIN_G4 ? 64 : bin == BIN_G8 ? 32 : bin == BIN_G16 ? 16 : 4;
 }
 
-__host__ __device__ __forceinline__ int64_t cand_region(int bin) {
+__host__ __device__ __forceinline__ int64_t cand_region(int bin, int one) {
   // 2 candidates x (rows per workgroup x longest row of the bin)
   int len = bin == BIN_G4 ? 4 : bin == BIN_G8 ? 8 : bin == BIN_G16 ? 16 : bin == BIN_W1 ? 64 : bin == BIN_W4 ? 256 : 512;
-  return 2 * (int64_t)bin_rep(bin) * bin_rows(bin) * len;
+  return 2 * (int64_t)bin_rep(bin, one) * bin_rows(bin) * len;
 }
 
 // SplitMix64 output function for state x (Steele, Lea & Flood 2014).

@@ -11,15 +11,16 @@ enum { MODE_ROUND = 0, MODE_COMPACT = 1 };
 struct SweepGrid {
   int nb[NBINS];        // workgroups per bin in the fused sweep launch
   int64_t long_base;    // candidate entries before the long-row regions
+  int one;              // a workgroup takes one row block (bin_rep)
 };
 
 // candidate region start of sweep workgroup b (non-long bins)
 __host__ __device__ __forceinline__ int64_t cand_region_start(const SweepGrid& g, int b, int& bin) {
   int64_t off = 0;
   for (bin = 0; bin < BIN_LONG; ++bin) {
-    if (b < g.nb[bin]) return off + (int64_t)b * cand_region(bin);
+    if (b < g.nb[bin]) return off + (int64_t)b * cand_region(bin, g.one);
     b -= g.nb[bin];
-    off += (int64_t)g.nb[bin] * cand_region(bin);
+    off += (int64_t)g.nb[bin] * cand_region(bin, g.one);
   }
   return -1;  // a long-row chunk: region from its chunk record
 }

@@ -829,13 +829,13 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int bas
   } else {
     CandSink sk{d.cand + start, &lcount};
     if (KIND != KIND_WIDE && b < g.nb[BIN_G4]) {
-      sweep_rows<4, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G4, b);
+      sweep_rows<4, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G4, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G4]) < g.nb[BIN_G8]) {
-      sweep_rows<8, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G8, b);
+      sweep_rows<8, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G8, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G8]) < g.nb[BIN_G16]) {
-      sweep_rows<16, 1, MODE, 4, DIR>(d, sk, ra, over, BIN_G16, b);
+      sweep_rows<16, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G16, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G16]) < g.nb[BIN_W1]) {
-      sweep_rows<64, 1, MODE, 2, DIR>(d, sk, ra, over, BIN_W1, b);
+      sweep_rows<64, 1, MODE, DIR ? 1 : 2, DIR>(d, sk, ra, over, BIN_W1, b);
     } else if (KIND != KIND_SHORT) {
       b -= KIND == KIND_WIDE ? g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1] : g.nb[BIN_W1];
       if (b < g.nb[BIN_W4]) sweep_rows<64, 4, MODE, 1, DIR>(d, sk, ra, over, BIN_W4, b);

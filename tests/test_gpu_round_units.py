@@ -69,3 +69,19 @@ def test_batch_lps_end_in_different_rounds(rounds):
         assert b.lp_stats(k)["rounds"] == ref.rounds
     b.close()
     assert np.isfinite(b.stats["ms_sweep"]) and b.stats["ms_sweep"] >= 0
+
+
+@pytest.mark.parametrize("length,block", [(4, 64), (8, 32), (16, 16), (60, 4), (250, 1)])
+@pytest.mark.parametrize("off", [-1, 0, 1])
+def test_row_block_edges(length, block, off):
+    """One row block to a workgroup: rows of one bin, one less and one more
+    than whole blocks of it."""
+    lp = lpgen.make_lp(max(1, 3 * block + off), 400, seed=length, row_len=(max(1, length - 1), length))
+    assert_same(gpu(lp, max_rounds=4), O.presolve(lp, max_rounds=4), f"{lp['m']} rows of {length}")
+
+
+@pytest.mark.parametrize("rows", [96000, 98000])
+def test_direct_and_selected_lists(rows):
+    """On both sides of the 500000 nonzeros up to which a sweep tests each row."""
+    lp = lp_of(rows, 100000, seed=1)
+    assert_same(gpu(lp), O.presolve(lp), f"{rows} rows, {len(lp['val'])} nonzeros")
