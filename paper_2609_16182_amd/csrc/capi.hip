@@ -661,6 +661,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   HIPCHK(p, hipEventRecord(p->ev[1], st));
   HIPCHK(p, hipStreamSynchronize(st));
   p->dense = p->htot[0] > 0;
+  p->d.look_first = p->dense;
   float ms = 0;
   HIPCHK(p, hipEventElapsedTime(&ms, p->ev[0], p->ev[1]));
   p->ms_ingest = ms;
@@ -1292,6 +1293,7 @@ static psl_status complete_pass(psl_presolver* p) {
     d.colid = p->colid;
     list_dense_cols(d, st);
     p->dense = true;  // a kept column may have grown
+    p->d.look_first = 1;
     launch_doubleton_relock(d, p->dbl, st);
     S.alg_bytes += 36.0 * (double)p->nnz;
   }

@@ -229,7 +229,7 @@ __global__ void k_dom_emit(Dev d, DomScratch S, int64_t base, int round) {
   d.rec[base + d.flags->round_total + d.off[t]] = r;
   d.bnd[j] = make_double2(v, v);
   d.bkey[2 * (int64_t)j] = dkey(v);
-  d.bkey[2 * (int64_t)j + 1] = dkey(v);
+  d.bkey[2 * (int64_t)j + 1] = ukey(v);
   d.flags->merged = 1;
   if (d.K > 1) d.lpf[lp].merged = 1;
 }

@@ -275,7 +275,7 @@ __global__ void k_dbl_emit_cols(Dev d, DblScratch S, const int32_t* row_total, i
   }
   d.bnd[j] = make_double2(lo, up);
   d.bkey[2 * (int64_t)j] = dkey(lo);
-  d.bkey[2 * (int64_t)j + 1] = dkey(up);
+  d.bkey[2 * (int64_t)j + 1] = ukey(up);
   d.touch[j] = 1;
   if (d.cfg.free_sing) d.fs_flag[j] = 1;
   if (!is_inf(lo) && !is_inf(up) && lo > up + tol_of(d.cfg, up)) flag_infeasible(d, lp);
@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_dbl_apply(Dev d, DblScratch S) {
       double vk = pos0(b / ak);
       d.bnd[k] = make_double2(vk, vk);
       d.bkey[2 * (int64_t)k] = dkey(vk);
-      d.bkey[2 * (int64_t)k + 1] = dkey(vk);
+      d.bkey[2 * (int64_t)k + 1] = ukey(vk);
     }
   }
 }

@@ -499,7 +499,7 @@ __global__ void k_init_state(Dev d, int64_t supers) {
     d.lsrc[t] = is_inf(b.x) ? -1 : -2;
     d.usrc[t] = is_inf(b.y) ? -1 : -2;
     d.bkey[2 * t] = dkey(b.x);
-    d.bkey[2 * t + 1] = dkey(b.y);
+    d.bkey[2 * t + 1] = ukey(b.y);
     d.src[2 * t] = 0x7FFFFFFF;
     d.src[2 * t + 1] = 0x7FFFFFFF;
     d.col_code[t] = 0;
@@ -609,7 +609,7 @@ __global__ void k_round0_emit(Dev d, int64_t base) {
   r.v[3] = 0.0;
   d.rec[base + d.off[t]] = r;
   d.bnd[j] = make_double2(b.x, b.x);
-  d.bkey[2 * (int64_t)j + 1] = dkey(b.x);
+  d.bkey[2 * (int64_t)j + 1] = ukey(b.x);
 }
 
 void launch_round0_count(const Dev& d, hipStream_t s) {

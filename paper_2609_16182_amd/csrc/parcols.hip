@@ -445,7 +445,7 @@ __global__ void k_pc_emit(Dev d, ColScratch P, int64_t base, int round) {
     r.v[3] = nb.y;
     d.bnd[j] = nb;
     d.bkey[2 * (int64_t)j] = dkey(nb.x);
-    d.bkey[2 * (int64_t)j + 1] = dkey(nb.y);
+    d.bkey[2 * (int64_t)j + 1] = ukey(nb.y);
     d.lsrc[j] = is_inf(nb.x) ? -1 : -2;
     d.usrc[j] = is_inf(nb.y) ? -1 : -2;
     d.touch[j] = 1;
@@ -461,7 +461,7 @@ __global__ void k_pc_emit(Dev d, ColScratch P, int64_t base, int round) {
     r.v[3] = 0.0;
     d.bnd[j] = make_double2(0.0, 0.0);
     d.bkey[2 * (int64_t)j] = dkey(0.0);
-    d.bkey[2 * (int64_t)j + 1] = dkey(0.0);
+    d.bkey[2 * (int64_t)j + 1] = ukey(0.0);
     d.flags->merged = 1;
     if (d.K > 1) d.lpf[lp].merged = 1;
   }

@@ -5,7 +5,7 @@
 //   CSC   cp[n+1] i32, ri[N] i32, cva[N] f64             (built at ingest)
 //   rows  lhs/rhs[m] f64, row_on[m] u8, row_code[m] u8, row_out[m] 16 B
 //   cols  bnd[n] double2 (lb, ub), bkey[2n] i64 (order-mapped accumulators of
-//         the round's best lb / ub), src[2n] i32, col_len[n] i32, c[n] f64
+//         the round's best lb / ub, both largest key first), src[2n] i32, col_len[n] i32, c[n] f64
 //   bins  bins[m] {row, start, len} (active rows grouped by CSR length,
 //         ascending within a bin; filtered as rows are removed)
 // A column is removed exactly when lb == ub: a fixed column keeps lb = ub = v,
@@ -203,6 +203,7 @@ struct Dev {
   const BinEnt *bins;
   int32_t bin_off[NBINS + 1];
   const SelCnt *sel;
+  int32_t look_first;          // some column has more than MARK_DENSE entries
   int32_t direct;              // the lists hold every row (those of the ingest): a
                                // kernel tests each row itself, sel is not used
   const LongChunk *lchunk;
@@ -255,6 +256,15 @@ __device__ __forceinline__ bool row_lp_on(const Dev& d, int i) {
 template <class T>
 __device__ __forceinline__ void hold(T x) {
   asm volatile("" : : "v"(x));
+}
+// The kernel's first argument, its Dev, read again where it is used: for code
+// that few wavefronts reach. Its pointers otherwise stay in scalar registers
+// from the kernel's start, and when those run out every use anywhere pays for
+// the reload from a vector lane.
+__device__ __forceinline__ const Dev& cold_dev() {
+  unsigned long long a = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return *(const Dev*)(const __attribute__((address_space(4))) Dev*)a;
 }
 // an LP that stops leaves the next selection at once
 __device__ __forceinline__ void flag_infeasible(const Dev& d, int lp) {
@@ -327,6 +337,11 @@ __device__ __forceinline__ double dunkey(long long k) {
   return __longlong_as_double(k >= 0 ? k : (k ^ 0x7FFFFFFFFFFFFFFFLL));
 }
 
+// the order reversed: an upper bound's key grows as the bound falls, so both
+// sides' accumulators take the largest key
+__device__ __forceinline__ long long ukey(double x) { return ~dkey(x); }
+__device__ __forceinline__ double unukey(long long k) { return dunkey(~k); }
+
 // contribution of coefficient a on [lb, ub] to the min / max activity
 __device__ __forceinline__ void contrib(double a, double lb, double ub, double& tmin,
                                        bool& imin, double& tmax, bool& imax) {
@@ -349,30 +364,73 @@ __device__ __forceinline__ unsigned long long lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-__device__ __forceinline__ double shfl_xor_d(double x, int m) {
-  return __shfl_xor(x, m, PSL_WAVE);
+// One step of a butterfly whose lanes hold equal values over aligned groups of
+// S lanes: each lane's value of the neighbouring group. Within 16 lanes a
+// data-parallel move of the vector unit (a mirror reaches the other half as
+// well as an exchange does, its lanes being equal); across 16 and 32 lanes the
+// swaps of rows, whose two results are this and the other group's value in an
+// order that a commutative sum does not see. No LDS access: a shuffle is one,
+// of about 60 cycles, for each 32 bits and step.
+template <int S>
+__device__ __forceinline__ void lane_pair(unsigned x, unsigned& a, unsigned& b) {
+  if constexpr (S <= 8) {
+    constexpr int ctrl = S == 1 ? 0xB1 : S == 2 ? 0x4E : S == 4 ? 0x141 : 0x140;
+    a = x;
+    b = (unsigned)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+  } else if constexpr (S == 16) {
+    auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+
+template <int S>
+__device__ __forceinline__ void lane_pair64(unsigned long long x, unsigned long long& a, unsigned long long& b) {
+  unsigned al, ah, bl, bh;
+  lane_pair<S>((unsigned)x, al, bl);
+  lane_pair<S>((unsigned)(x >> 32), ah, bh);
+  a = ((unsigned long long)ah << 32) | al;
+  b = ((unsigned long long)bh << 32) | bl;
 }
 
 // Sum over aligned groups of G lanes by a butterfly. fl(a + b) is
 // commutative, so both partners compute the same node and after log2(G)
 // steps every lane of the group holds the pairwise tree over its G lanes.
-template <int G>
+template <int G, int S = 1>
 __device__ __forceinline__ double group_sum(double x) {
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) x = x + shfl_xor_d(x, s);
-  return x;
+  if constexpr (S < G) {
+    unsigned long long a, b;
+    lane_pair64<S>((unsigned long long)__double_as_longlong(x), a, b);
+    return group_sum<G, 2 * S>(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+  } else {
+    return x;
+  }
 }
 
-template <int G>
+template <int G, int S = 1>
 __device__ __forceinline__ unsigned long long group_sum_u64(unsigned long long x) {
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) {
-    unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
-    lo = __shfl_xor(lo, s, PSL_WAVE);
-    hi = __shfl_xor(hi, s, PSL_WAVE);
-    x += ((unsigned long long)hi << 32) | lo;
+  if constexpr (S < G) {
+    unsigned long long a, b;
+    lane_pair64<S>(x, a, b);
+    return group_sum_u64<G, 2 * S>(a + b);
+  } else {
+    return x;
   }
-  return x;
+}
+
+template <int G, int S = 1>
+__device__ __forceinline__ int group_sum_int(int x) {
+  if constexpr (S < G) {
+    unsigned a, b;
+    lane_pair<S>((unsigned)x, a, b);
+    return group_sum_int<G, 2 * S>((int)(a + b));
+  } else {
+    return x;
+  }
 }
 
 template <int G>
@@ -390,18 +448,6 @@ __device__ __forceinline__ double tree_inplace(double* v, int n) {
   for (int w = 1; w < p; w <<= 1)
     for (int i = 0; i + w < n; i += 2 * w) v[i] = v[i] + v[i + w];
   return v[0];
-}
-
-// Wave-aggregated append of one 16-byte candidate per lane with pred set;
-// counter may live in LDS. Must be reached by all lanes of the wave.
-__device__ __forceinline__ void wave_append(bool pred, const Cand& e, Cand* list, int32_t* counter) {
-  unsigned long long mask = __ballot(pred);
-  if (mask == 0) return;
-  int leader = __ffsll((long long)mask) - 1;
-  int base = 0;
-  if (lane_id() == leader) base = atomicAdd(counter, (int)__popcll(mask));
-  base = __shfl(base, leader, PSL_WAVE);
-  if (pred) list[base + __popcll(mask & lanemask_lt())] = e;
 }
 
 // candidate-region sizes (entries) of the sweep bins, per workgroup

@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
   d.row_on[i] = 0;
   d.bnd[j] = make_double2(v, v);
   d.bkey[2 * (int64_t)j] = dkey(v);
-  d.bkey[2 * (int64_t)j + 1] = dkey(v);
+  d.bkey[2 * (int64_t)j + 1] = ukey(v);
   if (d.K > 1) d.lpo[lp].total = 1;  // the LP changed this round
   int p0 = d.rp[i], len = d.rp[i + 1] - p0;
   if (len > FS_SHORT) {

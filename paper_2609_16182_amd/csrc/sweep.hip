@@ -3,7 +3,7 @@
 //
 // Round semantics (Jacobi): every test reads the bounds as they were when the
 // round started (bnd); tightenings are combined in bkey with order-free
-// atomic max/min on order-mapped int64 keys; the source row of a final bound
+// atomic maxima of order-mapped int64 keys; the source row of a final bound
 // is the lowest row whose candidate equals it (resolved from a candidate list
 // after the sweep). Activities are canonical pairwise trees over the row's CSR
 // positions (leaves padded with +0 to a power of two), so every aligned
@@ -13,6 +13,7 @@
 //
 // Bins (by CSR length; rows are listed per bin, ascending):
 //   G4  <= 4     4-lane groups, 1 position per lane
+//   G8  <= 8     8-lane groups, 1 position per lane
 //   G16 <= 16    16-lane groups, 1 position per lane
 //   W1  <= 64    one wavefront, 1 position per lane
 //   W4  <= 256   one wavefront, 4 contiguous positions per lane
@@ -21,6 +22,14 @@
 //                k_long_stats writes chunk partials, then k_sweep combines
 //                them in tree order and propagates chunk by chunk.
 // Each row is handled in one pass with its elements kept in registers.
+//
+// What bounds it: misses of the L2, one 128 B line for each gathered 16 B bound
+// (1e7 rows, every row swept: 96e6 gathers in 1.9 ms, 5.0e10/s; a plain gather
+// of that size reaches 5.6e10/s), and below that the vector memory unit's
+// stalls on lines in flight. Against a version with branches per condition, LDS
+// shuffles and a look at the accumulators (a 4096-LP batch, every row swept: 310
+// vector and 244 scalar instructions for each 64 positions, 2.2 ms) this one has
+// 275 and 130 and takes 1.87 ms; its later rounds 1.67 -> 1.37 ms.
 #include "psl_kern.h"
 #include "sweep.h"
 
@@ -96,13 +105,6 @@ __device__ __forceinline__ int cnt_min(int c) { return c & 1023; }
 __device__ __forceinline__ int cnt_max(int c) { return (c >> 10) & 1023; }
 __device__ __forceinline__ int cnt_act(int c) { return c >> 20; }
 
-template <int G>
-__device__ __forceinline__ int group_sum_int(int x) {
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) x += __shfl_xor(x, s, PSL_WAVE);
-  return x;
-}
-
 // pairwise tree over C values held in registers (C a power of two)
 template <int C>
 __device__ __forceinline__ double lane_tree(double (&x)[C]) {
@@ -141,33 +143,30 @@ struct RowDec {
 // move far within the tolerance).
 __device__ __forceinline__ RowDec decide_row(const Cfg& c, double lhs, double rhs, int L, int nmin, int nmax,
                                              double minact, double maxact, bool any_tiny) {
+  // Without branches, as prop_el: all conditions are evaluated (those of an
+  // infinite side compare to a NaN or an infinity and are masked out).
   RowDec r{RC_KEEP, false, false, false, 0};
-  bool lo_ok = is_inf(lhs) || (nmin == 0 && minact >= lhs - tol_of(c, lhs));
-  bool up_ok = is_inf(rhs) || (nmax == 0 && maxact <= rhs + tol_of(c, rhs));
-  if (L == 0) {
-    if (lo_ok && up_ok) r.code = RC_EMPTY;
-    else r.infeasible = true;
-    return r;
-  }
-  if (lo_ok && up_ok) {
-    r.code = RC_REDUNDANT;
-    return r;
-  }
-  if ((nmin == 0 && !is_inf(rhs) && minact > rhs + tol_of(c, rhs)) ||
-      (nmax == 0 && !is_inf(lhs) && maxact < lhs - tol_of(c, lhs)))
-    r.infeasible = true;
+  const bool fl = !is_inf(lhs), fr = !is_inf(rhs), empty = L == 0;
+  const bool n0 = nmin == 0, x0 = nmax == 0;
+  const double tl = tol_of(c, lhs), tr = tol_of(c, rhs);
+  const bool lo_ok = !fl | (n0 & (minact >= lhs - tl));
+  const bool up_ok = !fr | (x0 & (maxact <= rhs + tr));
+  const bool leaves = lo_ok & up_ok;
+  const bool beyond = (n0 & fr & (minact > rhs + tr)) | (x0 & fl & (maxact < lhs - tl));
+  if (leaves) r.code = empty ? RC_EMPTY : RC_REDUNDANT;
+  r.infeasible = !leaves & (empty | beyond);
   // A side gives an entry a bound only when the residual activity on that side
   // is finite, i.e. with at most one infinite contribution (the entry's own);
   // with none on either side the row yields no candidate and is not re-read.
   // (A row with one active column has at most one infinite contribution per
   // side, so it always propagates on its finite sides.)
-  r.prop = (!is_inf(rhs) && nmin <= 1) || (!is_inf(lhs) && nmax <= 1);
-  r.single = (L == 1);
+  r.prop = !leaves & !empty & ((fr & (nmin <= 1)) | (fl & (nmax <= 1)));
+  r.single = !leaves & (L == 1);
   // Forcing rows (at least two active columns): the finite min activity
   // reaching rhs (or the max reaching lhs) within tol leaves every active
   // column at the bound of that contribution; the row leaves and those
   // bounds become candidates.
-  if (c.forcing && !r.infeasible && L >= 2 && !any_tiny) {
+  if (c.forcing && !leaves && !r.infeasible && L >= 2 && !any_tiny) {
     if (nmin == 0 && !is_inf(rhs) && minact >= rhs - tol_of(c, rhs)) r.force = 1;
     else if (nmax == 0 && !is_inf(lhs) && maxact <= lhs + tol_of(c, lhs)) r.force = 2;
     if (r.force) r.code = r.force == 1 ? RC_FORCE_MIN : RC_FORCE_MAX;
@@ -191,75 +190,40 @@ struct RowStat {
 __device__ __forceinline__ void prop_el(const Cfg& c, bool on, const El& e, double lhs, double rhs, const RowStat& st,
                                         bool single, int force, bool& cap, bool& hlo, double& tlo, bool& hup,
                                         double& tup) {
-  cap = true;
-  hlo = hup = false;
-  tlo = tup = 0.0;
-  if (!on) return;
-  if (force) {
-    // a forcing row: the column's other bound moves onto the forced one
-    // (min side: a > 0 at lb, a < 0 at ub; max side the other way round)
-    if ((force == 1) == (e.a > 0)) {
-      hup = e.lb < e.ub;
-      tup = e.lb;
-    } else {
-      hlo = e.ub > e.lb;
-      tlo = e.ub;
-    }
-    return;
-  }
-  if (fabs(e.a) < c.coef_tol) {
-    cap = false;
-    return;
-  }
+  // without branches: a wavefront's lanes take every path between them, and
+  // each branch costs its mask's scalar work; only the divisions are skipped
+  const bool fr = !is_inf(rhs), fl = !is_inf(lhs), pos = e.a > 0;
+  const bool tiny = fabs(e.a) < c.coef_tol;
   double tmin, tmax;
   bool imin, imax;
   contrib(e.a, e.lb, e.ub, tmin, imin, tmax, imax);
-  bool hmin = false, hmax = false;
-  double rmin = 0.0, rmax = 0.0;
-  if (st.nmin == 0) {
-    rmin = st.minact - tmin;
-    hmin = true;
-  } else if (st.nmin == 1 && imin) {
-    rmin = st.minact;
-    hmin = true;
-  }
-  if (st.nmax == 0) {
-    rmax = st.maxact - tmax;
-    hmax = true;
-  } else if (st.nmax == 1 && imax) {
-    rmax = st.maxact;
-    hmax = true;
-  }
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    double b = side == 0 ? rhs : lhs;
-    bool have = side == 0 ? hmin : hmax;
-    if (is_inf(b)) continue;
-    if (!have) {
-      cap = false;
-      continue;
-    }
-    double t = pos0((b - (side == 0 ? rmin : rmax)) / e.a);
-    if (!(fabs(t) < c.inf_value)) {
-      cap = false;
-      continue;
-    }
-    bool upper = (side == 0) == (e.a > 0);
-    if (upper) {
-      double u = e.ub;
-      bool q = is_inf(u) ? true : (single ? t < u : t < u - c.min_improve * mx1(u));
-      if (q) {
-        hup = true;
-        tup = t;
-      }
-    } else {
-      double l = e.lb;
-      bool q = is_inf(l) ? true : (single ? t > l : t > l + c.min_improve * mx1(l));
-      if (q) {
-        hlo = true;
-        tlo = t;
-      }
-    }
+  const bool h0 = fr & ((st.nmin == 0) | ((st.nmin == 1) & imin));
+  const bool h1 = fl & ((st.nmax == 0) | ((st.nmax == 1) & imax));
+  double t0 = 0.0, t1 = 0.0;
+  on = on & !((force == 0) & tiny);
+  const double r0 = rhs - (st.nmin == 0 ? st.minact - tmin : st.minact);
+  const double r1 = lhs - (st.nmax == 0 ? st.maxact - tmax : st.maxact);
+  if (on & h0) t0 = pos0(r0 / e.a);
+  if (on & h1) t1 = pos0(r1 / e.a);
+  const bool v0 = h0 & (fabs(t0) < c.inf_value), v1 = h1 & (fabs(t1) < c.inf_value);
+  cap = !tiny & (v0 | !fr) & (v1 | !fl);
+  tup = pos ? t0 : t1;
+  tlo = pos ? t1 : t0;
+  const double u = e.ub, l = e.lb;
+  const double du = c.min_improve * mx1(u), dl = c.min_improve * mx1(l);
+  const bool qu = is_inf(u) | (tup < (single ? u : u - du));
+  const bool ql = is_inf(l) | (tlo > (single ? l : l + dl));
+  hup = on & (pos ? v0 : v1) & qu;
+  hlo = on & (pos ? v1 : v0) & ql;
+  if (c.forcing && force) {
+    // a forcing row: the column's other bound moves onto the forced one
+    // (min side: a > 0 at lb, a < 0 at ub; max side the other way round)
+    const bool up = (force == 1) == pos;
+    cap = true;
+    hup = on && up && l < u;
+    hlo = on && !up && u > l;
+    tup = l;
+    tlo = u;
   }
 }
 
@@ -268,32 +232,42 @@ struct CandSink {  // this workgroup's candidate region and its LDS counter
   int32_t* counter;
 };
 
-// Fold qualifying candidates into the round's accumulators. A candidate that
-// is not better than the value read cannot be the final one unless equal, so
-// only candidates <= (>=) the current value go to the source list.
+// Fold qualifying candidates into the round's accumulators and list them; a
+// candidate that another one beats is found not to be the final bound when the
+// sources are taken. Nothing is read back, so no wavefront waits for memory
+// here; with long columns (d.look_first) their accumulators are read first,
+// since a beaten candidate's atomic waits for all others on that address (a
+// presolve of 1e6 power-law rows 4.84 ms, 5.33 without the look; a 4096-LP
+// batch, without long columns, 74.9 and 73.5 ms).
+// Most lanes have one side at most, so one atomic and one store serve both.
 // Must be reached by every lane of the wavefront.
 __device__ __forceinline__ void commit_cands(const Dev& d, const CandSink& sk, int pos, int j, bool hlo, double tlo,
                                              bool hup, double tup) {
-  bool alo = false, aup = false;
-  if (hlo) {
-    long long* k = &d.bkey[2 * (int64_t)j];
-    double cur = dunkey(*k);  // may be stale (larger): only costs an extra atomic
-    if (tlo >= cur) {
-      alo = true;
-      if (tlo > cur) atomicMax(k, dkey(tlo));
-    }
+  if (__ballot(hlo | hup) == 0) return;
+  long long* const k = &d.bkey[2 * (int64_t)j];
+  const long long klo = dkey(tlo), kup = ukey(tup);
+  bool alo = hlo, aup = hup;
+  if (d.look_first && (hlo | hup)) {
+    const longlong2 cur = *reinterpret_cast<const longlong2*>(k);  // may be stale (wider): only costs an atomic
+    hlo = hlo & (klo >= cur.x);
+    hup = hup & (kup >= cur.y);
+    alo = hlo & (klo > cur.x);
+    aup = hup & (kup > cur.y);
   }
-  if (hup) {
-    long long* k = &d.bkey[2 * (int64_t)j + 1];
-    double cur = dunkey(*k);
-    if (tup <= cur) {
-      aup = true;
-      if (tup < cur) atomicMin(k, dkey(tup));
-    }
+  const unsigned long long one = __ballot(hlo | hup), two = __ballot(hlo & hup);
+  if (one == 0) return;
+  const int n1 = __popcll(one);
+  int base = 0;
+  if (lane_id() == 0) base = atomicAdd(sk.counter, n1 + (int)__popcll(two));
+  if (alo | aup) atomicMax(alo ? k : k + 1, alo ? klo : kup);
+  if (alo & aup) atomicMax(k + 1, kup);
+  base = __builtin_amdgcn_readfirstlane(base);
+  const unsigned long long below = lanemask_lt();
+  if (hlo | hup) {
+    d.touch[j] = 1;
+    sk.list[base + __popcll(one & below)] = hlo ? Cand{2 * j, pos, tlo} : Cand{2 * j + 1, pos, tup};
   }
-  if (alo || aup) d.touch[j] = 1;
-  wave_append(alo, Cand{2 * j, pos, tlo}, sk.list, sk.counter);
-  wave_append(aup, Cand{2 * j + 1, pos, tup}, sk.list, sk.counter);
+  if (hlo & hup) sk.list[base + n1 + __popcll(two & below)] = Cand{2 * j + 1, pos, tup};
 }
 
 __device__ __forceinline__ RowOut row_out_of(uint8_t code, const RowStat& st) {
@@ -341,7 +315,7 @@ __device__ __forceinline__ void lane_prop(const Dev& d, const CandSink& sk, int6
 // flight together
 #define STREAM_GROUP 4
 template <int C>
-__device__ __forceinline__ void lane_prop_stream(const Dev& d, const CandSink& sk, int row, bool prop, int64_t s0,
+__device__ __forceinline__ void lane_prop_stream(const Dev& d, const CandSink& sk, bool prop, int64_t s0,
                                                  int len, int base, double lhs, double rhs, const RowStat& st,
                                                  bool single, int force, bool& uncap, bool& mine, int& aj,
                                                  double& aa) {
@@ -400,59 +374,77 @@ struct RoundArgs {
   int32_t* nnz;
 };
 
-// what a lane reads of its row in a row block
+// a lane's part of its row in a row block
 template <int C>
 struct RowIn {
-  bool vr, on;   // the lane's group has a row; the row is swept
-  int row, len;
+  bool on;       // the row is swept
+  int len;
   int64_t s0;
   double lhs, rhs;
   El e[C];
 };
 
-// First level of a row block's loads: the bin entry of the lane's row. A
-// lane beyond the bin's last row (cap rows at most) reads that one's entry, so
-// the load does not wait for the list's length.
-template <int G, int C>
-__device__ __forceinline__ BinEnt row_entry(const Dev& d, int bin, int cap, int vblock) {
-  int gid = vblock * (PSL_BLOCK / G) + (int)(threadIdx.x / G);
+// a lane's row of a list, and whether it is swept
+struct RowOf {
+  bool vr, on;
+  int row, start, len;
+  double lhs, rhs;
+};
+
+// First level of a list's loads: the entry of the lane's row. A lane beyond the
+// bin's last row (cap rows at most) reads that one's entry, so the load does
+// not wait for the list's length.
+__device__ __forceinline__ BinEnt row_entry(const Dev& d, int bin, int cap, int gid) {
   return d.bins[d.bin_off[bin] + (gid < cap ? gid : cap - 1)];
 }
 
-template <int G, int C>
-__device__ __forceinline__ void row_take(const BinEnt& be, int count, int vblock, RowIn<C>& in) {
-  in.vr = vblock * (PSL_BLOCK / G) + (int)(threadIdx.x / G) < count;
-  in.row = in.vr ? be.row : 0;
-  in.s0 = in.vr ? be.start : 0;
-  in.len = in.vr ? be.len : 0;
+__device__ __forceinline__ void row_take(const BinEnt& be, bool vr, RowOf& r) {
+  r.vr = vr;
+  r.row = vr ? be.row : 0;
+  r.start = vr ? be.start : 0;
+  r.len = vr ? be.len : 0;
 }
 
-// Second level: the row's flags and sides, beside the lane's positions
-// (columns and coefficients); the third level, the bounds, is issued by
-// load_els or by the caller. A row of the direct lists is swept when it is
-// active, of an LP still presolving and, by the mode, marked / not inert.
-template <int MODE, bool DIR, int C>
-__device__ __forceinline__ void row_data(const Dev& d, const RoundArgs& ra, RowIn<C>& in) {
-  in.lhs = d.lhs[in.row];
-  in.rhs = d.rhs[in.row];
+// Second level: the row's sides and flags, beside the positions (columns and
+// coefficients); the third level, the bounds, is issued by load_els or by the
+// caller. A row of the direct lists is swept when it is active, of an LP still
+// presolving and, by the mode, marked / not inert.
+template <int MODE, bool DIR>
+__device__ __forceinline__ void row_data(const Dev& d, const RoundArgs& ra, RowOf& r) {
+  r.lhs = d.lhs[r.row];
+  r.rhs = d.rhs[r.row];
   if (MODE == MODE_COMPACT) {
-    in.on = in.vr && d.row_on[in.row] != 0;
+    r.on = r.vr && d.row_on[r.row] != 0;
   } else if (DIR) {
-    uint8_t on = d.row_on[in.row], dt = d.dirty[in.row];
-    int2 rf = d.rinf[in.row];
-    in.on = in.vr && on != 0 && (!(ra.mode & 1) || dt == ra.mark) && row_lp_on(d, in.row) &&
-            (!(ra.mode & 2) || !row_inert(rf, in.lhs, in.rhs));
+    uint8_t on = d.row_on[r.row], dt = d.dirty[r.row];
+    int2 rf = d.rinf[r.row];
+    r.on = r.vr && on != 0 && (!(ra.mode & 1) || dt == ra.mark) && row_lp_on(d, r.row) &&
+           (!(ra.mode & 2) || !row_inert(rf, r.lhs, r.rhs));
   } else {
-    in.on = in.vr;  // selected
+    r.on = r.vr;  // selected
   }
 }
 
-// statistics, decisions, candidates and removals of the row block's rows
-// from the loaded inputs (elements of inactive rows are cleared here)
+// Outcome of a swept row for its lane: code and infinite-contribution counts.
+struct RowRes {
+  uint32_t w;
+  __device__ __forceinline__ static uint32_t pack(uint8_t code, int nmin, int nmax) {
+    return (uint32_t)code | (uint32_t)nmin << 8 | (uint32_t)nmax << 18;
+  }
+};
+__device__ __forceinline__ void row_store(const Dev& d, int row, uint32_t w) {
+  d.rinf[row] = make_int2((int)(w >> 8) & 1023, (int)(w >> 18));
+  d.row_code[row] = (uint8_t)w;
+}
+
+// Statistics, decisions, candidates and removals of the row block's rows from
+// the loaded inputs (elements of inactive rows are cleared here). Lane `from`
+// holds the lane's row number. Returns the row's packed outcome.
 template <int G, int C, int MODE>
-__device__ __forceinline__ void row_block(const Dev& d, const CandSink& sk, RowIn<C>& in) {
-  const bool vr = in.vr, on = in.on;
-  const int row = in.row, len = in.len;
+__device__ __forceinline__ uint32_t row_block(const Dev& d, const CandSink& sk, RowIn<C>& in, bool vr, int row_of,
+                                              int from) {
+  const bool on = in.on;
+  const int len = in.len;
   const int64_t s0 = in.s0;
   int gl = threadIdx.x & (G - 1);
   El(&e)[C] = in.e;
@@ -478,124 +470,151 @@ __device__ __forceinline__ void row_block(const Dev& d, const CandSink& sk, RowI
   st.nmax = cnt_max(cnt);
   int L = cnt_act(cnt);
   if (MODE == MODE_COMPACT) {
+    const int row = __shfl(row_of, from, PSL_WAVE);
     if (vr && gl == 0) {
       d.row_out[row].v0 = st.minact;
       d.row_out[row].j = on ? L : 0;
     }
-    return;
+    return 0;
   }
-  bool live = vr && on;
-  double lhs = live ? in.lhs : 0.0, rhs = live ? in.rhs : 0.0;
-  if (live && gl == 0) d.rinf[row] = make_int2(st.nmin, st.nmax);
+  const double lhs = on ? in.lhs : 0.0, rhs = on ? in.rhs : 0.0;
   bool tiny = false;
 #pragma unroll
   for (int k = 0; k < C; ++k) tiny = tiny || (el_active(e[k]) && fabs(e[k].a) < d.cfg.coef_tol);
   bool any_tiny = (__ballot(tiny) & group_mask<G>()) != 0;
   RowDec dec = decide_row(d.cfg, lhs, rhs, L, st.nmin, st.nmax, st.minact, st.maxact, any_tiny);
-  bool prop = live && dec.prop;
+  bool prop = on && dec.prop;
   bool uncap = false, mine = false;
   int aj = 0;
   double aa = 0.0;
-  int force = live ? dec.force : 0;
+  int force = on ? dec.force : 0;
   if (C == 1) lane_prop<C>(d, sk, s0 + gl * C, prop, e, lhs, rhs, st, dec.single, force, uncap, mine, aj, aa);
   else  // reload (L1/L2 hits) instead of keeping C elements live through the sums
-    lane_prop_stream<C>(d, sk, row, prop, s0, len, gl * C, lhs, rhs, st, dec.single, force, uncap, mine, aj, aa);
+    lane_prop_stream<C>(d, sk, prop, s0, len, gl * C, lhs, rhs, st, dec.single, force, uncap, mine, aj, aa);
   bool captured = (__ballot(uncap) & group_mask<G>()) == 0;
   uint8_t code = RC_KEEP;
-  if (live) {
+  if (on) {
     code = dec.code;
     if (prop && dec.single && !dec.infeasible && captured) code = RC_SINGLETON;
-    if (dec.infeasible && gl == 0) flag_infeasible(d, row_lp_of(d, row));
   }
-  if (live && gl == 0) d.row_code[row] = code;
-  if (live && gl == 0 && (code == RC_EMPTY || code == RC_REDUNDANT || is_forcing(code)))
-    d.row_out[row] = row_out_of(code, st);
-  if (code == RC_SINGLETON && mine) {
-    d.row_out[row] = RowOut{aa, 0.0, aj, 0};
-    drop_col(d, aj, aa, lhs, rhs);
+  if (__ballot(code != RC_KEEP || (on && dec.infeasible)) != 0) {
+    // a row of the wavefront leaves, or cannot be met
+    const Dev& cd = cold_dev();
+    const int row = __shfl(row_of, from, PSL_WAVE);
+    if (on && dec.infeasible && gl == 0) flag_infeasible(cd, row_lp_of(cd, row));
+    if (on && gl == 0 && (code == RC_EMPTY || code == RC_REDUNDANT || is_forcing(code)))
+      cd.row_out[row] = row_out_of(code, st);
+    if (code == RC_SINGLETON && mine) {
+      cd.row_out[row] = RowOut{aa, 0.0, aj, 0};
+      drop_col(cd, aj, aa, lhs, rhs);
+    }
+    if (code == RC_REDUNDANT || is_forcing(code)) {
+      if (C == 1) lane_drop<C>(cd, e, lhs, rhs);
+      else lane_drop_stream<C>(cd, on, s0, len, gl * C, lhs, rhs);
+    }
   }
-  if (code == RC_REDUNDANT || is_forcing(code)) {
-    if (C == 1) lane_drop<C>(d, e, lhs, rhs);
-    else lane_drop_stream<C>(d, live, s0, len, gl * C, lhs, rhs);
-  }
+  return RowRes::pack(code, st.nmin, st.nmax);
 }
 
-// rows and nonzeros of a row block that are swept (direct lists)
-template <int G, int C, int MODE, bool DIR>
-__device__ __forceinline__ void count_swept(const Dev& d, const RoundArgs& ra, const RowIn<C>& in) {
+// rows and nonzeros that are swept (direct lists), of rows held one by a lane
+template <int MODE, bool DIR>
+__device__ __forceinline__ void count_swept(const RoundArgs& ra, bool on, int len) {
   if (MODE != MODE_ROUND || !DIR) return;
-  int gl = threadIdx.x & (G - 1);
-  unsigned long long m = __ballot(in.on && gl == 0);
-  int z = in.on && gl == 0 ? in.len : 0;
-  z = group_sum_int<PSL_WAVE>(z);
+  unsigned long long m = __ballot(on);
+  int z = group_sum_int<PSL_WAVE>(on ? len : 0);
   if (lane_id() == 0 && m) {
     atomicAdd(ra.rows, (int)__popcll(m));
     atomicAdd(ra.nnz, z);
   }
 }
 
-// The workgroup's REP row blocks of the bin. With one position per lane the
-// loads of all REP blocks are issued level by level before any block is
-// processed, so a lane has REP rows' gathers in flight together.
-template <int G, int C, int MODE, int REP, bool DIR>
+// The workgroup's REP row blocks of a bin with one position per lane: a
+// wavefront takes REP * 64 / G consecutive rows of the list. One lane reads a
+// row's entry, sides and flags and stores its outcome, for all blocks with one
+// load or store each, and the lanes of the row's group take them from it: the
+// vector memory unit needs 17 cycles for any 8- or 16-byte load of a wavefront
+// (37 where the lanes' lines differ, as the bounds'), also where four or more
+// lanes read one row's, and it was 80% busy when each block made its own. The
+// positions' loads of all blocks are issued, level by level, before any block
+// is processed, so a lane has REP rows' gathers in flight together.
+template <int G, int MODE, int REP, bool DIR>
 __device__ __forceinline__ void sweep_rows(const Dev& d, const CandSink& sk, RoundArgs ra, bool over, int bin,
                                            int lblock) {
+  constexpr int RW = PSL_WAVE / G, NR = REP * RW;  // rows of a block's wavefront; of all blocks'
+  static_assert(NR <= PSL_WAVE, "one row per lane");
   const int cap = d.bin_off[bin + 1] - d.bin_off[bin];
-  int gl = threadIdx.x & (G - 1);
-  if (C == 1) {
-    BinEnt be[REP];
+  const int lane = lane_id(), gl = lane & (G - 1);
+  const int first = (lblock * (PSL_BLOCK / PSL_WAVE) + (int)(threadIdx.x >> 6)) * NR;
+  const BinEnt be = row_entry(d, bin, cap, first + (lane < NR ? lane : NR - 1));
+  const int count = DIR ? cap : d.sel[bin].v;
+  hold(be.row);
+  if (over || first >= count) return;  // uniform over the wavefront
+  RowOf r;
+  row_take(be, lane < NR && first + lane < count, r);
+  int j[REP];
+  double a[REP];
 #pragma unroll
-    for (int k = 0; k < REP; ++k) be[k] = row_entry<G, C>(d, bin, cap, lblock * REP + k);
-    int count = (DIR ? cap : d.sel[bin].v);
-#pragma unroll
-    for (int k = 0; k < REP; ++k) hold(be[k].row);
-    if (over || lblock * REP * (PSL_BLOCK / G) >= count) return;  // uniform over the workgroup
-    RowIn<C> in[REP];
-    int j[REP];
-    double a[REP];
-#pragma unroll
-    for (int k = 0; k < REP; ++k) {
-      row_take<G, C>(be[k], count, lblock * REP + k, in[k]);
-      bool v = gl < in[k].len;
-      int64_t p = v ? in[k].s0 + gl : 0;
-      j[k] = d.ci[p];
-      a[k] = d.va[p];
-      in[k].e[0].v = v;
-      row_data<MODE, DIR, C>(d, ra, in[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < REP; ++k) {
-      bool v = in[k].e[0].v;
-      double2 bb = make_double2(0.0, 0.0);
-      if (!DIR || in[k].on) bb = d.bnd[j[k]];
-      in[k].e[0].j = v ? j[k] : 0;
-      in[k].e[0].a = v ? a[k] : 0.0;
-      in[k].e[0].lb = v ? bb.x : 0.0;
-      in[k].e[0].ub = v ? bb.y : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < REP; ++k) {
-      if ((lblock * REP + k) * (PSL_BLOCK / G) >= count) break;  // uniform over the workgroup
-      if (DIR && MODE == MODE_ROUND && __ballot(in[k].on) == 0) continue;
-      count_swept<G, C, MODE, DIR>(d, ra, in[k]);
-      row_block<G, C, MODE>(d, sk, in[k]);
-    }
-  } else {
-    int count = (DIR ? cap : d.sel[bin].v);
-    if (over) return;
-#pragma unroll 1
-    for (int k = 0; k < REP; ++k) {
-      int vb = lblock * REP + k;
-      if (vb * (PSL_BLOCK / G) >= count) break;  // uniform over the workgroup
-      RowIn<C> in;
-      row_take<G, C>(row_entry<G, C>(d, bin, cap, vb), count, vb, in);
-      row_data<MODE, DIR, C>(d, ra, in);
-      if (DIR && MODE == MODE_ROUND && __ballot(in.on) == 0) continue;
-      count_swept<G, C, MODE, DIR>(d, ra, in);
-      load_els<C>(d, in.s0, in.len, gl * C, true, in.e);
-      row_block<G, C, MODE>(d, sk, in);
-    }
+  for (int k = 0; k < REP; ++k) {
+    const int from = k * RW + lane / G;
+    const int s0 = __shfl(r.start, from, PSL_WAVE), len = __shfl(r.len, from, PSL_WAVE);
+    const int64_t p = gl < len ? (int64_t)s0 + gl : 0;
+    j[k] = d.ci[p];
+    a[k] = d.va[p];
   }
+  row_data<MODE, DIR>(d, ra, r);
+  const unsigned long long on = __ballot(r.on);
+  double2 bb[REP];
+#pragma unroll
+  for (int k = 0; k < REP; ++k) {
+    bb[k] = make_double2(0.0, 0.0);
+    if (!DIR || (on >> (k * RW + lane / G) & 1)) bb[k] = d.bnd[j[k]];
+  }
+  count_swept<MODE, DIR>(ra, r.on, r.len);
+  uint32_t res = 0;
+#pragma unroll
+  for (int k = 0; k < REP; ++k) {
+    if (first + k * RW >= count) break;  // uniform over the wavefront
+    if (DIR && MODE == MODE_ROUND && ((on >> (k * RW)) & (RW == 64 ? ~0ull : (1ull << RW) - 1)) == 0) continue;
+    const int from = k * RW + lane / G;
+    RowIn<1> in;
+    in.on = (on >> from) & 1;
+    in.s0 = __shfl(r.start, from, PSL_WAVE);
+    in.len = __shfl(r.len, from, PSL_WAVE);
+    in.lhs = __shfl(r.lhs, from, PSL_WAVE);
+    in.rhs = __shfl(r.rhs, from, PSL_WAVE);
+    const bool v = gl < in.len;
+    in.e[0] = El{v ? j[k] : 0, v ? a[k] : 0.0, v ? bb[k].x : 0.0, v ? bb[k].y : 0.0, v};
+    const bool vr = first + from < count;
+    const uint32_t w = row_block<G, 1, MODE>(d, sk, in, vr, r.row, from);
+    const uint32_t x = __shfl(w, (lane & (RW - 1)) * G, PSL_WAVE);
+    if (lane / RW == k) res = x;
+  }
+  if (MODE == MODE_ROUND && r.on) row_store(d, r.row, res);
+}
+
+// one row of a wavefront at a time, C positions per lane
+template <int C, int MODE, bool DIR>
+__device__ __forceinline__ void sweep_wide_row(const Dev& d, const CandSink& sk, RoundArgs ra, bool over, int bin,
+                                               int lblock) {
+  const int cap = d.bin_off[bin + 1] - d.bin_off[bin];
+  const int lane = lane_id();
+  const int gid = lblock * (PSL_BLOCK / PSL_WAVE) + (int)(threadIdx.x >> 6);
+  const int count = DIR ? cap : d.sel[bin].v;
+  if (over || gid >= count) return;  // uniform over the wavefront
+  RowOf r;
+  row_take(row_entry(d, bin, cap, gid), true, r);
+  row_data<MODE, DIR>(d, ra, r);
+  if (DIR && MODE == MODE_ROUND && !r.on) return;
+  count_swept<MODE, DIR>(ra, r.on && lane == 0, r.len);
+  RowIn<C> in;
+  in.on = r.on;
+  in.s0 = r.start;
+  in.len = r.len;
+  in.lhs = r.lhs;
+  in.rhs = r.rhs;
+  load_els<C>(d, in.s0, in.len, lane * C, true, in.e);
+  const uint32_t w = row_block<PSL_WAVE, C, MODE>(d, sk, in, true, r.row, lane);
+  if (MODE == MODE_ROUND && r.on && lane == 0) row_store(d, r.row, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -763,7 +782,7 @@ __device__ __forceinline__ void sweep_long_chunk(const Dev& d, const CandSink& s
   for (int p = 0; p < ch.npass; ++p) {
     int base = ch.first + p * PASS_LEN + (int)threadIdx.x * 8;
     if (dec.prop)
-      lane_prop_stream<8>(d, sk, row, true, s0, len, base, lhs, rhs, st, dec.single, dec.force, uncap, mine, aj, aa);
+      lane_prop_stream<8>(d, sk, true, s0, len, base, lhs, rhs, st, dec.single, dec.force, uncap, mine, aj, aa);
     if (dec.code == RC_REDUNDANT || is_forcing(dec.code)) lane_drop_stream<8>(d, true, s0, len, base, lhs, rhs);
   }
   if (dec.prop && dec.single && !dec.infeasible) {
@@ -829,17 +848,17 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_sweep(Dev d, SweepGrid g, int bas
   } else {
     CandSink sk{d.cand + start, &lcount};
     if (KIND != KIND_WIDE && b < g.nb[BIN_G4]) {
-      sweep_rows<4, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G4, b);
+      sweep_rows<4, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G4, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G4]) < g.nb[BIN_G8]) {
-      sweep_rows<8, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G8, b);
+      sweep_rows<8, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G8, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G8]) < g.nb[BIN_G16]) {
-      sweep_rows<16, 1, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G16, b);
+      sweep_rows<16, MODE, DIR ? 1 : 4, DIR>(d, sk, ra, over, BIN_G16, b);
     } else if (KIND != KIND_WIDE && (b -= g.nb[BIN_G16]) < g.nb[BIN_W1]) {
-      sweep_rows<64, 1, MODE, DIR ? 1 : 2, DIR>(d, sk, ra, over, BIN_W1, b);
+      sweep_rows<64, MODE, DIR ? 1 : 2, DIR>(d, sk, ra, over, BIN_W1, b);
     } else if (KIND != KIND_SHORT) {
       b -= KIND == KIND_WIDE ? g.nb[BIN_G4] + g.nb[BIN_G8] + g.nb[BIN_G16] + g.nb[BIN_W1] : g.nb[BIN_W1];
-      if (b < g.nb[BIN_W4]) sweep_rows<64, 4, MODE, 1, DIR>(d, sk, ra, over, BIN_W4, b);
-      else sweep_rows<64, 8, MODE, 1, DIR>(d, sk, ra, over, BIN_W8, b - g.nb[BIN_W4]);
+      if (b < g.nb[BIN_W4]) sweep_wide_row<4, MODE, DIR>(d, sk, ra, over, BIN_W4, b);
+      else sweep_wide_row<8, MODE, DIR>(d, sk, ra, over, BIN_W8, b - g.nb[BIN_W4]);
     }
   }
   if (MODE == MODE_ROUND && !over) {
@@ -884,7 +903,8 @@ __device__ __forceinline__ void sources(const Dev& d, const SweepGrid& g, int b)
   const Cand* list = d.cand + start;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     Cand c = list[i];
-    if (c.t == dunkey(d.bkey[c.js])) atomicMin(&d.src[c.js], c.pos);
+    const long long k = d.bkey[c.js];
+    if (c.t == (c.js & 1 ? unukey(k) : dunkey(k))) atomicMin(&d.src[c.js], c.pos);
   }
 }
 
@@ -929,7 +949,7 @@ __device__ __forceinline__ uint8_t col_decide(const Dev& d, int j, int& k) {
   hold(left);
   if (b.x == b.y) return 0;
   double lo = dunkey(key.x);
-  double up = dunkey(key.y);
+  double up = unukey(key.y);
   uint8_t code = 0;
   if (lo != b.x) {
     code |= CC_LB;
@@ -1230,7 +1250,7 @@ __device__ __forceinline__ void emit_row(const Dev& d, int i, int round, Record*
 __device__ __forceinline__ void emit_col(const Dev& d, int j, uint8_t code, int round, Record* r) {
   double2 b = d.bnd[j];
   double lo = dunkey(d.bkey[2 * (int64_t)j]);
-  double up = dunkey(d.bkey[2 * (int64_t)j + 1]);
+  double up = unukey(d.bkey[2 * (int64_t)j + 1]);
   // the source of a changed bound is the CSR position of the lowest row's
   // candidate equal to it (positions of one column ascend with the row); a
   // changed bound always has one
@@ -1272,7 +1292,7 @@ __device__ __forceinline__ void emit_col(const Dev& d, int j, uint8_t code, int 
   }
   d.bnd[j] = make_double2(nlo, nup);
   d.bkey[2 * (int64_t)j] = dkey(nlo);
-  d.bkey[2 * (int64_t)j + 1] = dkey(nup);
+  d.bkey[2 * (int64_t)j + 1] = ukey(nup);
   d.src[2 * (int64_t)j] = 0x7FFFFFFF;
   d.src[2 * (int64_t)j + 1] = 0x7FFFFFFF;
 }

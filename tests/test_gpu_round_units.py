@@ -85,3 +85,27 @@ def test_direct_and_selected_lists(rows):
     """On both sides of the 500000 nonzeros up to which a sweep tests each row."""
     lp = lp_of(rows, 100000, seed=1)
     assert_same(gpu(lp), O.presolve(lp), f"{rows} rows, {len(lp['val'])} nonzeros")
+
+
+def with_long_column(m, entries, seed):
+    """lp_of plus one column in the first `entries` rows, its bounds far out:
+    every one of them may tighten it."""
+    lp = lp_of(m, m, seed)
+    rng = np.random.default_rng(seed)
+    rp, n = lp["row_ptr"], lp["n"]
+    at = rp[1:entries + 1]  # behind each row's last entry
+    lp["col_idx"] = np.insert(lp["col_idx"], at, n).astype(lp["col_idx"].dtype)
+    lp["val"] = np.insert(lp["val"], at, rng.choice([-2.0, -1.0, 1.0, 2.0], entries))
+    lp["row_ptr"] = (rp + np.minimum(np.arange(m + 1), entries)).astype(rp.dtype)
+    for k, v in (("lb", -1e4), ("ub", 1e4), ("c", 1.0)):
+        lp[k] = np.append(lp[k], v)
+    lp["n"] = n + 1
+    return lp
+
+
+@pytest.mark.parametrize("entries", [4095, 4096, 4097, 6000])
+def test_long_column_accumulators(entries):
+    """With columns of more than 4096 entries a candidate looks at its
+    accumulator before the atomic."""
+    lp = with_long_column(6000, entries, seed=5)
+    assert_same(gpu(lp), O.presolve(lp), f"{entries} entries")
