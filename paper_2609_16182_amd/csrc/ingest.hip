@@ -24,71 +24,249 @@ __device__ __forceinline__ double canon_inf(double v, double inf_value) {
   return pos0(v);
 }
 
-__global__ void k_check_rows(Dev d) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.m) return;
-  int32_t a = d.rp[i], b = d.rp[i + 1];
-  if ((i == 0 && a != 0) || a < 0 || b < a || (int64_t)b > d.nnz || (i == d.m - 1 && (int64_t)b != d.nnz))
-    report(d, ERR_ROWPTR, i);
-  double l = d.lhs[i], r = d.rhs[i];
-  double iv = d.cfg.inf_value;
-  if (__builtin_isnan(l) || __builtin_isnan(r) || l >= iv || r <= -iv) report(d, ERR_SIDE, i);
-  d.lhs[i] = canon_inf(l, iv);
-  d.rhs[i] = canon_inf(r, iv);
+// the arrays of an LP in device memory, one row of workgroups each
+__global__ void __launch_bounds__(PSL_BLOCK) k_copy_in(CopyIn c) {
+  const InSeg g = c.seg[blockIdx.y];
+  const int64_t t = (int64_t)blockIdx.x * PSL_BLOCK + threadIdx.x, step = (int64_t)gridDim.x * PSL_BLOCK;
+  int64_t done = 0;
+  if ((((uintptr_t)g.src | (uintptr_t)g.dst) & 15) == 0) {
+    done = g.words / 4;
+    const uint4* src = reinterpret_cast<const uint4*>(g.src);
+    uint4* dst = reinterpret_cast<uint4*>(g.dst);
+    for (int64_t i = t; i < done; i += step) dst[i] = src[i];
+    done *= 4;
+  }
+  for (int64_t i = done + t; i < g.words; i += step) g.dst[i] = g.src[i];
 }
 
-__global__ void k_check_cols(Dev d, const double* lb_in, const double* ub_in, double* c_mut) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d.n) return;
-  double l = lb_in[j], u = ub_in[j], c = c_mut[j];
-  double iv = d.cfg.inf_value;
-  if (__builtin_isnan(l) || __builtin_isnan(u) || l >= iv || u <= -iv) report(d, ERR_BOUND, j);
-  if (!__builtin_isfinite(c)) report(d, ERR_COST, j);
-  d.bnd[j] = make_double2(canon_inf(l, iv), canon_inf(u, iv));
-  c_mut[j] = pos0(c);
+void launch_copy_in(const CopyIn& c, hipStream_t s) {
+  int64_t w = 0;
+  for (const InSeg& g : c.seg) w = g.words > w ? g.words : w;
+  int64_t blocks = (w + 4 * PSL_BLOCK - 1) / (4 * PSL_BLOCK);
+  if (blocks == 0) return;
+  if (blocks > 2048) blocks = 2048;
+  hipLaunchKernelGGL(k_copy_in, dim3((unsigned)blocks, IN_SEGS), dim3(PSL_BLOCK), 0, s, c);
 }
 
-// rowid1[e] counts the rows ending at position e; its exclusive scan then
-// gives, at index p + 1, the row holding CSR position p.
-__global__ void k_row_ends(Dev d, int32_t* cnt) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.m) return;
-  atomicAdd(&cnt[d.rp[i + 1]], 1);
+// bin of a row of len entries
+__device__ __forceinline__ int bin_of_len(int len, int t_long, int t_g8) {
+  return len <= 4 ? BIN_G4 : len <= t_g8 ? BIN_G8 : len <= 16 ? BIN_G16 : len > t_long ? BIN_LONG
+       : len <= 64 ? BIN_W1 : len <= 256 ? BIN_W4 : BIN_W8;
 }
 
-__global__ void k_check_entries(Dev d, const int32_t* rowid1) {
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < d.nnz; p += (int64_t)gridDim.x * blockDim.x) {
-    int row = rowid1[p + 1];
-    int j = d.ci[p];
-    if (j < 0 || j >= d.n || (p > d.rp[row] && d.ci[p - 1] >= j)) report(d, ERR_COLIDX, p);
-    double a = d.va[p];
-    if (!__builtin_isfinite(a) || a == 0.0) report(d, ERR_COEF, p);
+// Rows and columns, in tiles of 1024 of each: the checks, the stored sides and
+// bounds, and each tile's rows per bin (hist[bin * tiles + tile], from whose
+// scan k_bin_fill lists them). The launches of the ingest are queued without a
+// look at the errors found, so each of them stays inside its arrays whatever
+// the input holds.
+#define ING_TILE 1024
+__global__ void __launch_bounds__(PSL_BLOCK) k_check(Dev d, const double* lb_in, const double* ub_in, double* c_mut,
+                                                     int32_t t_long, int32_t t_g8, int32_t* hist, int tiles) {
+  __shared__ int c[NBINS];
+  if (threadIdx.x < NBINS) c[threadIdx.x] = 0;
+  __syncthreads();
+  const double iv = d.cfg.inf_value;
+  const int64_t base = (int64_t)blockIdx.x * ING_TILE + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < ING_TILE / PSL_BLOCK; ++k) {
+    const int64_t i = base + k * PSL_BLOCK;
+    int bin = -1;
+    if (i < d.m) {
+      int32_t a = d.rp[i], b = d.rp[i + 1];
+      if ((i == 0 && a != 0) || a < 0 || b < a || (int64_t)b > d.nnz || (i == d.m - 1 && (int64_t)b != d.nnz))
+        report(d, ERR_ROWPTR, i);
+      double l = d.lhs[i], r = d.rhs[i];
+      if (__builtin_isnan(l) || __builtin_isnan(r) || l >= iv || r <= -iv) report(d, ERR_SIDE, i);
+      d.lhs[i] = canon_inf(l, iv);
+      d.rhs[i] = canon_inf(r, iv);
+      bin = bin_of_len(b - a, t_long, t_g8);
+    }
+#pragma unroll
+    for (int q = 0; q < NBINS; ++q) {
+      int cnt = __popcll(__ballot(bin == q));
+      if (lane_id() == 0 && cnt) atomicAdd(&c[q], cnt);
+    }
+    if (i < d.n) {
+      double l = lb_in[i], u = ub_in[i], cost = c_mut[i];
+      if (__builtin_isnan(l) || __builtin_isnan(u) || l >= iv || u <= -iv) report(d, ERR_BOUND, i);
+      if (!__builtin_isfinite(cost)) report(d, ERR_COST, i);
+      d.bnd[i] = make_double2(canon_inf(l, iv), canon_inf(u, iv));
+      c_mut[i] = pos0(cost);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < NBINS && (int)blockIdx.x < tiles) hist[threadIdx.x * tiles + blockIdx.x] = c[threadIdx.x];
+}
+
+// the bins' lists, rows ascending in each, and the bins' sizes
+__global__ void __launch_bounds__(PSL_BLOCK) k_bin_fill(Dev d, int32_t t_long, int32_t t_g8, const int32_t* off,
+                                                        int tiles, BinEnt* bins) {
+  __shared__ int at[NBINS], wcnt[PSL_BLOCK / PSL_WAVE][NBINS];
+  const int w = threadIdx.x >> 6;
+  if (threadIdx.x < NBINS) {
+    const int q = threadIdx.x;
+    at[q] = off[q * tiles + blockIdx.x];
+    if (blockIdx.x == 0) d.flags->bins[q] = (q + 1 < NBINS ? off[(q + 1) * tiles] : d.m) - off[q * tiles];
+  }
+  for (int k = 0; k < ING_TILE / PSL_BLOCK; ++k) {
+    const int64_t i = (int64_t)blockIdx.x * ING_TILE + k * PSL_BLOCK + threadIdx.x;
+    int a = 0, len = 0, bin = -1, below = 0;
+    if (i < d.m) {
+      a = d.rp[i];
+      len = d.rp[i + 1] - a;
+      bin = bin_of_len(len, t_long, t_g8);
+    }
+#pragma unroll
+    for (int q = 0; q < NBINS; ++q) {
+      unsigned long long m = __ballot(bin == q);
+      if (bin == q) below = __popcll(m & lanemask_lt());
+      if (lane_id() == 0) wcnt[w][q] = __popcll(m);
+    }
+    __syncthreads();
+    if (bin >= 0) {
+      int p = at[bin] + below;
+      for (int v = 0; v < w; ++v) p += wcnt[v][bin];
+      bins[p] = BinEnt{(int32_t)i, a, len, 0};
+    }
+    __syncthreads();
+    if (threadIdx.x < NBINS)
+      for (int v = 0; v < PSL_BLOCK / PSL_WAVE; ++v) at[threadIdx.x] += wcnt[v][threadIdx.x];
+    __syncthreads();
   }
 }
 
-void launch_check_rows(const Dev& d, hipStream_t s) {
-  if (d.m == 0) return;
-  hipLaunchKernelGGL(k_check_rows, dim3((d.m + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d);
+// last row i < m with rp[i] <= p, given rp[0] <= p < rp[m] (rp ascends), by the
+// wavefront: 64 probes a step
+__device__ __forceinline__ int row_of_pos(const int32_t* rp, int m, int p) {
+  int lo = 0, hi = m;
+  while (hi - lo > 1) {
+    const int step = (hi - lo + PSL_WAVE - 1) / PSL_WAVE;
+    const int64_t at = (int64_t)lo + (int64_t)(lane_id() + 1) * step;
+    const int c = __popcll(__ballot(at < hi && rp[at < hi ? at : lo] <= p));
+    lo += c * step;
+    hi = hi - lo > step ? lo + step : hi;
+  }
+  return lo;
 }
 
-void check_cols(const Dev& d, const double* lb_in, const double* ub_in, double* c_mut, hipStream_t s) {
-  if (d.n == 0) return;
-  hipLaunchKernelGGL(k_check_cols, dim3((d.n + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d, lb_in, ub_in,
-                     c_mut);
+// Per tile of 2048 positions: the rows of the positions (rowid1), the checks of
+// the entries, and the counts of the first transposition pass (digits of the
+// column under mask; 0: none). The tile's first and last rows are searched, the
+// rows' starts between them marked in LDS and carried over their positions by a
+// running maximum. Also sets cp to -1 for the transposition.
+// One launch where a fill, a count per row, a scan, the checks and the pass's
+// counts were up to seven (1e7 rows, 9.7e7 entries: 1.16 ms together, 0.65 now,
+// of it 0.25 for the 1.5 GB it reads and writes).
+#define POS_TILE RX_TILE
+#define POS_ITEMS (POS_TILE / PSL_BLOCK)
+__global__ void __launch_bounds__(PSL_BLOCK) k_positions(Dev d, int32_t* rowid1, int32_t* cp, uint32_t mask,
+                                                         int32_t* hist, int tiles) {
+  __shared__ int mk[POS_TILE];
+  __shared__ int digit[256];
+  __shared__ int ends[2], wmax[PSL_BLOCK / PSL_WAVE];
+  const int t = threadIdx.x, w = t >> 6;
+  for (int64_t j = (int64_t)blockIdx.x * PSL_BLOCK + t; j <= d.n; j += (int64_t)gridDim.x * PSL_BLOCK) cp[j] = -1;
+  if (blockIdx.x == 0 && t == 0) rowid1[0] = 0;
+  const int64_t p0 = (int64_t)blockIdx.x * POS_TILE;
+  if (p0 >= d.nnz) return;
+  const int cnt = (int)(d.nnz - p0 < POS_TILE ? d.nnz - p0 : POS_TILE);
+  // rows can be searched when their pointers passed the check
+  const bool rows_ok = d.m > 0 && !(d.flags->error & ERR_ROWPTR);
+  const bool check = !(d.flags->error & (ERR_ROWPTR | ERR_SIDE | ERR_BOUND | ERR_COST));
+  digit[t] = 0;
+#pragma unroll
+  for (int k = 0; k < POS_ITEMS; ++k) mk[k * PSL_BLOCK + t] = 0;
+  if (w < 2 && rows_ok) {
+    const int r = row_of_pos(d.rp, d.m, (int)(w == 0 ? p0 : p0 + cnt - 1));
+    if (lane_id() == 0) ends[w] = r;
+  }
+  __syncthreads();
+  const int r0 = rows_ok ? ends[0] : 0, r1 = rows_ok ? ends[1] : 0;
+  const bool whole = rows_ok && (int64_t)d.rp[r0] == p0;  // the tile starts with a row
+  // (a tile between which many empty rows lie is searched position by position)
+  const bool walk = r1 - r0 <= 16 * POS_TILE;
+  if (walk) {
+    for (int r = r0 + 1 + t; r <= r1; r += PSL_BLOCK) {
+      const int s = d.rp[r];
+      if (d.rp[r + 1] > s) mk[s - p0] = r;
+    }
+    if (t == 0) mk[0] = r0;
+    __syncthreads();
+    int v[POS_ITEMS], run = 0;
+#pragma unroll
+    for (int k = 0; k < POS_ITEMS; ++k) {
+      const int x = mk[t * POS_ITEMS + k];
+      run = x > run ? x : run;
+      v[k] = run;
+    }
+    int pre = run;
+#pragma unroll
+    for (int o = 1; o < PSL_WAVE; o <<= 1) {
+      const int x = __shfl_up(pre, o, PSL_WAVE);
+      if (lane_id() >= o && x > pre) pre = x;
+    }
+    if (lane_id() == PSL_WAVE - 1) wmax[w] = pre;
+    __syncthreads();
+    pre = __shfl_up(pre, 1, PSL_WAVE);
+    if (lane_id() == 0) pre = 0;
+    for (int q = 0; q < w; ++q) pre = wmax[q] > pre ? wmax[q] : pre;
+#pragma unroll
+    for (int k = 0; k < POS_ITEMS; ++k) mk[t * POS_ITEMS + k] = v[k] > pre ? v[k] : pre;
+  } else {
+    for (int k = t; k < cnt; k += PSL_BLOCK) {
+      int lo = r0, hi = r1 + 1;
+      while (hi - lo > 1) {
+        const int mid = lo + (hi - lo) / 2;
+        if ((int64_t)d.rp[mid] <= p0 + k) lo = mid;
+        else hi = mid;
+      }
+      mk[k] = lo;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < POS_ITEMS; ++k) {
+    const int q = k * PSL_BLOCK + t;
+    if (q >= cnt) continue;
+    const int64_t p = p0 + q;
+    const int row = mk[q], j = d.ci[p];
+    rowid1[p + 1] = row;
+    if (mask) atomicAdd(&digit[(uint32_t)j & mask], 1);
+    if (check) {
+      const bool first = q == 0 ? whole : mk[q - 1] != row;
+      if (j < 0 || j >= d.n || (!first && d.ci[p - 1] >= j)) report(d, ERR_COLIDX, p);
+      const double a = d.va[p];
+      if (!__builtin_isfinite(a) || a == 0.0) report(d, ERR_COEF, p);
+    }
+  }
+  __syncthreads();
+  if (mask && (uint32_t)t <= mask) hist[(int64_t)t * tiles + blockIdx.x] = digit[t];
 }
 
-void build_rowid(const Dev& d, IngestScratch& sc, hipStream_t s) {
-  fill_i32(sc.rowid1, 0, d.nnz + 1, s);
-  if (d.m > 0)
-    hipLaunchKernelGGL(k_row_ends, dim3((d.m + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d, sc.rowid1);
-  scan_excl(sc.rowid1, sc.rowid1, d.nnz + 1, nullptr, sc.ws, s);
+// column bits and passes of the transposition
+static int csc_bits(const Dev& d) {
+  int bits = 0;
+  while (bits < 31 && ((int64_t)1 << bits) < (int64_t)d.n) ++bits;
+  return bits;
 }
 
-void launch_check_entries(const Dev& d, const int32_t* rowid1, hipStream_t s) {
-  if (d.nnz == 0) return;
-  int64_t blocks = (d.nnz + PSL_BLOCK - 1) / PSL_BLOCK;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(k_check_entries, dim3((unsigned)blocks), dim3(PSL_BLOCK), 0, s, d, rowid1);
+void launch_checks(const Dev& d, const double* lb_in, const double* ub_in, double* c_mut, const int32_t* thresholds,
+                   BinEnt* bins, IngestScratch& sc, hipStream_t s) {
+  const int64_t t = d.m > d.n ? d.m : d.n;
+  const int tiles = (int)(((int64_t)d.m + ING_TILE - 1) / ING_TILE);
+  if (t > 0)
+    hipLaunchKernelGGL(k_check, dim3((unsigned)((t + ING_TILE - 1) / ING_TILE)), dim3(PSL_BLOCK), 0, s, d, lb_in,
+                       ub_in, c_mut, thresholds[0], thresholds[2], sc.ws, tiles);
+  if (tiles > 0) {
+    scan_excl(sc.ws, sc.ws, (int64_t)NBINS * tiles, nullptr, sc.ws + (int64_t)NBINS * tiles, s);
+    hipLaunchKernelGGL(k_bin_fill, dim3(tiles), dim3(PSL_BLOCK), 0, s, d, thresholds[0], thresholds[2],
+                       (const int32_t*)sc.ws, tiles, bins);
+  }
+  // the first pass's digits, as build_csc splits them
+  const int bits = csc_bits(d), passes = (bits + 7) / 8, per = passes ? (bits + passes - 1) / passes : 0;
+  const int64_t pt = (d.nnz + POS_TILE - 1) / POS_TILE;
+  hipLaunchKernelGGL(k_positions, dim3((unsigned)(pt > 0 ? pt : 1)), dim3(PSL_BLOCK), 0, s, d, sc.rowid1,
+                     (int32_t*)d.cp, passes ? (1u << per) - 1u : 0u, sc.ws, (int)pt);
 }
 
 // ---------------------------------------------------------------------------
@@ -111,10 +289,11 @@ __global__ void k_csc_gather(Dev d, const int32_t* perm, const int32_t* rowid1, 
 // in k_col_len, so no thread loops over a long run.
 #define COLPTR_RUN 64
 __global__ void k_col_ptr(Dev d, const uint32_t* keys, int32_t* cp) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *d.n_dense = 0;
   for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q <= d.nnz; q += (int64_t)gridDim.x * blockDim.x) {
     int64_t prev = q > 0 ? (int64_t)keys[q - 1] : -1;
     int64_t cur = q < d.nnz ? (int64_t)keys[q] : (int64_t)d.n;
-    // keys were validated (< n); clamped all the same so no store leaves cp
+    // valid keys are < n; clamped, so that no store leaves cp for others
     prev = prev < (int64_t)d.n ? prev : (int64_t)d.n;
     cur = cur < (int64_t)d.n ? cur : (int64_t)d.n;
     int64_t j0 = cur - prev > COLPTR_RUN ? cur - COLPTR_RUN : prev;
@@ -145,17 +324,21 @@ __global__ void k_col_len(Dev d, const uint32_t* keys, int32_t* cp, int32_t* col
   }
   if (b < 0) b = col_start(keys, d.nnz, j + 1);  // written by thread j + 1
   col_len[j] = b - a;
+  // the columns of more than MARK_DENSE entries (order irrelevant; of a valid
+  // input they fit the list)
+  if (b - a > MARK_DENSE && !d.flags->error) d.dense_cols[atomicAdd(d.n_dense, 1)] = (int32_t)j;
 }
 
 // Stable transpose by LSD radix passes over the column index (at most 8 bits
 // a pass, the bits split evenly), moving row and value with each key; the
 // last pass writes the transposed copy itself. vtmp: nnz doubles of scratch.
+// counted: k_positions left the first pass's counts in the workspace and cp
+// at -1.
 // Returns the column of every position of the transposed copy (the sorted
 // keys), which compaction uses.
 const uint32_t* build_csc(const Dev& d, int32_t* cp, int32_t* ri, double* cva, int32_t* col_len, IngestScratch& sc,
-                          double* vtmp, hipStream_t s) {
-  int bits = 0;
-  while (bits < 31 && ((int64_t)1 << bits) < (int64_t)d.n) ++bits;
+                          double* vtmp, bool counted, hipStream_t s) {
+  int bits = csc_bits(d);
   int passes = (bits + 7) / 8;
   const uint32_t* kin = (const uint32_t*)d.ci;
   if (passes == 0) {
@@ -179,13 +362,14 @@ const uint32_t* build_csc(const Dev& d, int32_t* cp, int32_t* ri, double* cva, i
       double* vout = ((passes - 1 - pass) % 2 == 0) ? cva : vtmp;
       int32_t* rout = last ? ri : rb[pass & 1];
       uint32_t* kout = kb[pass & 1];
-      radix_pass_payload(kin, rin, sc.rowid1, vin, kout, rout, vout, d.nnz, shift, b, sc.ws, s);
+      radix_pass_payload(kin, rin, sc.rowid1, vin, kout, rout, vout, d.nnz, shift, b, counted && pass == 0,
+                         sc.ws, s);
       kin = kout;
       rin = rout;
       vin = vout;
     }
   }
-  fill_i32(cp, -1, d.n + 1, s);
+  if (!counted) fill_i32(cp, -1, d.n + 1, s);
   {
     int64_t blocks = (d.nnz + 1 + PSL_BLOCK - 1) / PSL_BLOCK;
     if (blocks > 16384) blocks = 16384;
@@ -198,55 +382,7 @@ const uint32_t* build_csc(const Dev& d, int32_t* cp, int32_t* ri, double* cva, i
 }
 
 // ---------------------------------------------------------------------------
-// row bins by CSR length, and the chunk table of long rows
-// ---------------------------------------------------------------------------
-// bin of every row, and the bin sizes (counted per wavefront by ballots, per
-// workgroup in LDS, then one global add per workgroup and bin)
-__global__ void k_bin_keys(Dev d, int32_t t_long, int32_t t_g8, uint32_t* keys, int32_t* counts) {
-  __shared__ int c[NBINS];
-  if (threadIdx.x < NBINS) c[threadIdx.x] = 0;
-  __syncthreads();
-  int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < d.m; i0 += stride) {
-    int64_t i = i0 + threadIdx.x;
-    int b = -1;
-    if (i < d.m) {
-      int len = d.rp[i + 1] - d.rp[i];
-      b = len <= 4 ? BIN_G4 : len <= t_g8 ? BIN_G8 : len <= 16 ? BIN_G16 : len > t_long ? BIN_LONG
-        : len <= 64 ? BIN_W1 : len <= 256 ? BIN_W4 : BIN_W8;
-      keys[i] = (uint32_t)b;
-    }
-#pragma unroll
-    for (int k = 0; k < NBINS; ++k) {
-      int cnt = __popcll(__ballot(b == k));
-      if (lane_id() == 0 && cnt) atomicAdd(&c[k], cnt);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < NBINS && c[threadIdx.x]) atomicAdd(&counts[threadIdx.x], c[threadIdx.x]);
-}
-
-__global__ void k_bin_fill(Dev d, const int32_t* rows, BinEnt* bins) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= d.m) return;
-  int row = rows[k];
-  int a = d.rp[row], b = d.rp[row + 1];
-  bins[k] = BinEnt{row, a, b - a, 0};
-}
-
-void build_bins(const Dev& d, const int32_t* thresholds, BinEnt* bins, int32_t* counts, IngestScratch& sc,
-                hipStream_t s) {
-  fill_i32(counts, 0, NBINS, s);
-  if (d.m == 0) return;
-  unsigned blocks = (unsigned)((d.m + PSL_BLOCK - 1) / PSL_BLOCK);
-  unsigned kb = blocks < 1024 ? blocks : 1024;
-  hipLaunchKernelGGL(k_bin_keys, dim3(kb), dim3(PSL_BLOCK), 0, s, d, thresholds[0], thresholds[2], sc.k0, counts);
-  radix_pass(sc.k0, nullptr, sc.k1, sc.v0, d.m, 0, 3, sc.ws, s);
-  hipLaunchKernelGGL(k_bin_fill, dim3(blocks), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)sc.v0, bins);
-}
-
-// ---------------------------------------------------------------------------
-// filtering of the bin lists and the chunk list down to the active rows
+// the chunk table of long rows
 // ---------------------------------------------------------------------------
 // passes per chunk: the requested size, doubled until the row has at most
 // LONG_MAX_CHUNKS chunks (chunk sizes stay powers of two times PASS_LEN)
@@ -281,10 +417,6 @@ __global__ void k_long_fill(Dev d, const int32_t* off, const int32_t* uoff, Long
 
 void build_long_chunks(const Dev& d, int npass0, LongChunk* chunks, int32_t* cnt, int32_t* cnt2, int32_t* totals,
                        int32_t* ws, hipStream_t s) {
-  if (d.nlong == 0) {
-    fill_i32(totals, 0, 2, s);
-    return;
-  }
   unsigned blocks = (unsigned)((d.nlong + PSL_BLOCK - 1) / PSL_BLOCK);
   hipLaunchKernelGGL(k_long_count, dim3(blocks), dim3(PSL_BLOCK), 0, s, d, npass0, cnt, cnt2);
   scan_excl(cnt, cnt, d.nlong, totals, ws, s);
@@ -313,12 +445,6 @@ struct SelArgs {
   int t_long, t_g8;     // bin thresholds of the ingest
   int seq;              // launch number of the round before
 };
-
-// bin of a row of len entries (the bins of the ingest)
-__device__ __forceinline__ int bin_of_len(int len, int t_long, int t_g8) {
-  return len <= 4 ? BIN_G4 : len <= t_g8 ? BIN_G8 : len <= 16 ? BIN_G16 : len > t_long ? BIN_LONG
-       : len <= 64 ? BIN_W1 : len <= 256 ? BIN_W4 : BIN_W8;
-}
 
 // index of long row `row` in d.lrow (ascending rows; the row is long)
 __device__ __forceinline__ int long_row_index(const Dev& d, int row) {
@@ -466,23 +592,12 @@ void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStrea
                      rec_cap);
 }
 
-// the columns of more than MARK_DENSE entries (order irrelevant)
-__global__ void k_dense_cols(Dev d) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d.n) return;
-  if (d.cp[j + 1] - d.cp[j] > MARK_DENSE) d.dense_cols[atomicAdd(d.n_dense, 1)] = (int32_t)j;
-}
-
-void list_dense_cols(const Dev& d, hipStream_t s) {
-  fill_i32(d.n_dense, 0, 1, s);
-  if (d.n > 0)
-    hipLaunchKernelGGL(k_dense_cols, dim3((unsigned)((d.n + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d);
-}
-
 // ---------------------------------------------------------------------------
 // state initialisation and round 0 (input fixings, crossed bounds / sides)
 // ---------------------------------------------------------------------------
-__global__ void k_init_state(Dev d, int64_t supers) {
+// (the run's start also copies the costs: it works on a copy, since
+// free-singleton substitutions change it and postsolve wants the input's)
+__global__ void k_init_state(Dev d, int64_t supers, const double* c_in, double* c_run) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < d.m) {
     d.row_on[t] = 1;
@@ -493,6 +608,7 @@ __global__ void k_init_state(Dev d, int64_t supers) {
   if (t <= d.m / 1024) d.dirty_tile[t] = 0;
   if (t < d.n) {
     double2 b = d.bnd[t];
+    if (c_run) c_run[t] = c_in[t];
     d.touch[t] = 1;    // the first round decides every column
     d.fs_flag[t] = 1;  // and checks every column for a free singleton
     d.owner[t] = ~0ull;
@@ -506,6 +622,8 @@ __global__ void k_init_state(Dev d, int64_t supers) {
   }
   if (t == 0) {
     Flags f;
+    f.n_dense = d.flags->n_dense;  // of the ingest
+    for (int b = 0; b < NBINS; ++b) f.bins[b] = d.flags->bins[b];
     f.infeasible = f.unbounded = f.error = f.merged = 0;
     f.cand_count = f.round_total = f.vlist_count = f.rows_removed = 0;
     f.fin_cols = f.mode = f.lead_count = f.fs_total = f.fs_rows = f.fs_claims = 0;
@@ -562,11 +680,12 @@ void init_locks(const Dev& d, int32_t* dn, int32_t* up, int32_t* ws, hipStream_t
                      (const int32_t*)dn, (const int32_t*)up);
 }
 
-void launch_init_state(const Dev& d, hipStream_t s) {
+void launch_init_state(const Dev& d, const double* c_in, double* c_run, hipStream_t s) {
   int64_t t = d.m > d.n ? d.m : d.n;
   int64_t supers = (int64_t)decide_supers(d.m, d.n);
   if (t < supers) t = supers;
-  hipLaunchKernelGGL(k_init_state, dim3((unsigned)((t + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d, supers);
+  hipLaunchKernelGGL(k_init_state, dim3((unsigned)((t + PSL_BLOCK - 1) / PSL_BLOCK)), dim3(PSL_BLOCK), 0, s, d, supers,
+                     c_in, c_run);
 }
 
 __global__ void k_round0_count(Dev d) {

@@ -157,7 +157,7 @@ void scan_excl(const int32_t* in, int32_t* out, int64_t n, int32_t* total, int32
 // ---------------------------------------------------------------------------
 
 #define RX_ROUNDS 8
-#define RX_TILE (PSL_BLOCK * RX_ROUNDS)
+static_assert(RX_TILE == PSL_BLOCK * RX_ROUNDS, "a tile is RX_ROUNDS keys a thread");
 
 __global__ void __launch_bounds__(PSL_BLOCK) k_rx_count(const uint32_t* keys, int64_t n, int shift, uint32_t mask,
                                                         int32_t* hist, int ntiles) {
@@ -343,13 +343,14 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_tx_scatter(const uint32_t* kin, c
 
 void radix_pass_payload(const uint32_t* keys_in, const int32_t* rows_in, const int32_t* rowid1,
                         const double* vals_in, uint32_t* keys_out, int32_t* rows_out, double* vals_out, int64_t n,
-                        int shift, int bits, int32_t* ws, hipStream_t s) {
+                        int shift, int bits, bool counted, int32_t* ws, hipStream_t s) {
   if (n <= 0) return;
   int ntiles = (int)((n + RX_TILE - 1) / RX_TILE);
   uint32_t mask = (1u << bits) - 1u;
   int32_t* hist = ws;
   int32_t* sws = ws + 256 * (int64_t)ntiles;
-  hipLaunchKernelGGL(k_rx_count, dim3(ntiles), dim3(PSL_BLOCK), 0, s, keys_in, n, shift, mask, hist, ntiles);
+  if (!counted)
+    hipLaunchKernelGGL(k_rx_count, dim3(ntiles), dim3(PSL_BLOCK), 0, s, keys_in, n, shift, mask, hist, ntiles);
   scan_excl(hist, hist, (int64_t)(mask + 1) * ntiles, nullptr, sws, s);
   hipLaunchKernelGGL(k_tx_scatter, dim3(ntiles), dim3(PSL_BLOCK), 0, s, keys_in, rows_in, rowid1, vals_in, keys_out,
                      rows_out, vals_out, n, shift, mask, (const int32_t*)hist, ntiles);

@@ -131,6 +131,7 @@ struct Flags {
   int32_t fs_claims;       // chunks of long substituting rows listed
   int32_t dbl_count;       // doubleton-equality candidates listed
   int32_t dbl_applied;     // a doubleton substitution was applied this pass
+  int32_t n_dense, bins[NBINS];  // ingest: columns in dense_cols; rows of each bin
   // rounds queued ahead of the host: a round's kernels do nothing when its
   // number is above stop_at, which the last round's control sets
   int32_t stop_at, rounds_done;

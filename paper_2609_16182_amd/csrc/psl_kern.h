@@ -13,6 +13,8 @@ namespace psl {
 size_t scan_ws_ints(int64_t n);
 void scan_excl(const int32_t* in, int32_t* out, int64_t n, int32_t* total, int32_t* ws, hipStream_t s);
 
+#define RX_TILE 2048  // keys a workgroup counts and moves
+
 // One stable counting-sort pass by the digit (key >> shift) & (2^bits - 1),
 // bits <= 8. vals_in == nullptr means value = index. ws: radix_ws_ints(n).
 size_t radix_ws_ints(int64_t n);
@@ -21,10 +23,11 @@ void radix_pass(const uint32_t* keys_in, const int32_t* vals_in, uint32_t* keys_
 
 // The same pass moving a payload of a row index and a value with each key;
 // rows_in == nullptr takes row rowid1[p + 1] for item p. Buffers must not
-// alias. ws: radix_ws_ints(n).
+// alias. ws: radix_ws_ints(n); counted: it holds the tiles' counts of the
+// pass's digits already (count of digit d in tile t at d * tiles + t).
 void radix_pass_payload(const uint32_t* keys_in, const int32_t* rows_in, const int32_t* rowid1,
                         const double* vals_in, uint32_t* keys_out, int32_t* rows_out, double* vals_out, int64_t n,
-                        int shift, int bits, int32_t* ws, hipStream_t s);
+                        int shift, int bits, bool counted, int32_t* ws, hipStream_t s);
 
 // out[i] = v (32-bit words)
 void fill_i32(int32_t* out, int32_t v, int64_t n, hipStream_t s);

@@ -70,17 +70,27 @@ struct IngestScratch {
   int32_t* v1;       // [nnz]
   int32_t* ws;       // scan / radix workspace
 };
-void launch_check_rows(const Dev& d, hipStream_t s);
-void check_cols(const Dev& d, const double* lb_in, const double* ub_in, double* c_mut, hipStream_t s);
-void launch_check_entries(const Dev& d, const int32_t* rowid1, hipStream_t s);
-void build_rowid(const Dev& d, IngestScratch& sc, hipStream_t s);
-// transposed copy (vtmp: nnz doubles of scratch); returns the column of each
-// of its positions
+// arrays (32-bit words, 4-byte aligned) copied by one launch
+#define IN_SEGS 8
+struct InSeg {
+  const uint32_t* src;
+  uint32_t* dst;
+  int64_t words;
+};
+struct CopyIn {
+  InSeg seg[IN_SEGS];
+};
+void launch_copy_in(const CopyIn& c, hipStream_t s);
+// input checks (d.flags->error), stored sides and bounds, the bins' lists and
+// sizes (d.flags->bins), the rows of the positions (sc.rowid1); sc.ws is left
+// with the counts that build_csc takes
+void launch_checks(const Dev& d, const double* lb_in, const double* ub_in, double* c_mut, const int32_t* thresholds,
+                   BinEnt* bins, IngestScratch& sc, hipStream_t s);
+// transposed copy (vtmp: nnz doubles of scratch; counted: right after
+// launch_checks) and its long columns (d.dense_cols, d.n_dense); returns the
+// column of each of its positions
 const uint32_t* build_csc(const Dev& d, int32_t* cp, int32_t* ri, double* cva, int32_t* col_len, IngestScratch& sc,
-                          double* vtmp, hipStream_t s);
-// bins: writes the bin lists and per-bin counts (device counts[NBINS])
-void build_bins(const Dev& d, const int32_t* thresholds, BinEnt* bins, int32_t* counts, IngestScratch& sc,
-                hipStream_t s);
+                          double* vtmp, bool counted, hipStream_t s);
 // The rows a launch takes: every active row of an LP still presolving, as bin
 // lists in out (bin b's from d.bin_off[b]), the kept long rows' chunks (from
 // d.chunks0) in cout and the counts in cnt (cleared before). A bin's rows
@@ -93,15 +103,13 @@ void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cou
 // before rounds are queued: the record buffer's state, no stop, and (K > 1)
 // the LPs' flags cleared
 void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStream_t s);
-// d.dense_cols / d.n_dense from the transposed copy (after build_csc)
-void list_dense_cols(const Dev& d, hipStream_t s);
 // chunk table of the long rows (d.nlong set); total chunks to *total (device)
 // totals[0] = chunks, totals[1] = candidate units of all chunks
 void build_long_chunks(const Dev& d, int npass0, LongChunk* chunks, int32_t* cnt, int32_t* cnt2, int32_t* totals,
                        int32_t* ws, hipStream_t s);
 void launch_round0_count(const Dev& d, hipStream_t s);
 void launch_round0_emit(const Dev& d, int64_t base, hipStream_t s);
-void launch_init_state(const Dev& d, hipStream_t s);
+void launch_init_state(const Dev& d, const double* c_in, double* c_run, hipStream_t s);
 // d.locks of every column from the alive rows (dual fixing); dn, up: nnz + 1
 // ints of scratch each, ws: scan workspace for nnz + 1 items
 void init_locks(const Dev& d, int32_t* dn, int32_t* up, int32_t* ws, hipStream_t s);
