@@ -15,16 +15,24 @@ __device__ __forceinline__ bool bit_of(const uint64_t* bits, int64_t j) { return
 // scan over the words): one 16-byte lookup gives a flag and its rank.
 struct RankWord {
   uint64_t bits;
-  int32_t pre;
-  int32_t pad;
+  int32_t pre;  // set flags before the word, in its tile
+  int32_t all;  // ... and in all
 };
 
 __device__ __forceinline__ bool bit_of(const RankWord* rw, int64_t j) { return (rw[j >> 6].bits >> (j & 63)) & 1ull; }
 
-// j's rank among the set flags (the index of a kept j after compaction)
+// j's rank among the set flags of its tile, and of all (the index of a kept j
+// after compaction)
+__device__ __forceinline__ int32_t set_below(const RankWord& w, int64_t j) {
+  return (int32_t)__popcll(w.bits & ((1ull << (j & 63)) - 1ull));
+}
+__device__ __forceinline__ int32_t tile_rank_of(const RankWord* rw, int64_t j) {
+  RankWord w = rw[j >> 6];
+  return w.pre + set_below(w, j);
+}
 __device__ __forceinline__ int32_t rank_of(const RankWord* rw, int64_t j) {
   RankWord w = rw[j >> 6];
-  return w.pre + (int32_t)__popcll(w.bits & ((1ull << (j & 63)) - 1ull));
+  return w.all + set_below(w, j);
 }
 
 __device__ __forceinline__ void set_word(uint64_t& w, uint64_t v) { w = v; }

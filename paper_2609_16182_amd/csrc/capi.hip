@@ -237,6 +237,7 @@ static psl_status setup_arena(psl_presolver* p) {
   ALLOC(p->isc.v0, big);
   ALLOC(p->isc.v1, big);
   size_t wsn = std::max<size_t>(scan_ws_ints(N + 1), radix_ws_ints(std::max<int64_t>(N, m)));
+  wsn = std::max(wsn, scan_ws_ints(compact_tiles(m, n, N) + 1));
   wsn = std::max<size_t>(wsn, scan_ws_ints(m + n + 1));
   wsn = std::max<size_t>(wsn, par_cols_ws_ints(n)) + 64;
   ALLOC(p->ws, wsn);
@@ -322,9 +323,7 @@ static psl_status setup_arena(psl_presolver* p) {
   }
 
   // compaction
-  ALLOC(p->cmp.row_new, m + 1);
-  ALLOC(p->cmp.col_new, n + 1);
-  ALLOC(p->cmp.col_keep, n);
+  ALLOC(p->cmp.tile_off, compact_tiles(m, n, N) + 1);
   ALLOC(p->cmp.rbits, m / 64 + 1);
   ALLOC(p->cmp.cbits, n / 64 + 1);
   ALLOC(p->cmp.terms, n);
@@ -333,8 +332,8 @@ static psl_status setup_arena(psl_presolver* p) {
   ALLOC(p->cmp.offset, K);
   ALLOC(p->lpr, K + 1);
   p->cmp.ws = p->ws;
-  p->cmp.eflag = p->isc.v0;
-  p->cmp.qflag = p->isc.v1;
+  p->cmp.ebits = (RankWord*)p->isc.v0;  // 16 B for each 64 positions
+  p->cmp.qbits = (RankWord*)p->isc.v1;
   p->cmp.rowid1 = p->isc.rowid1;
   p->cmp.lpr = p->lpr;
   p->cmp.seg = nullptr;
@@ -1261,7 +1260,6 @@ static psl_status launch_pass(psl_presolver* p) {
     launch_par_count(d, p->par, st);
     scan_excl(d.cnt, d.off, m, &d.flags->round_total, p->ws, st);
     launch_par_emit(d, p->par, p->rec_count - p->rec_flushed, R.round, st);
-    launch_par_drop(d, p->par, st);
   } else {
     fill_i32(&d.flags->round_total, 0, 1, st);
   }
@@ -1350,8 +1348,7 @@ static psl_status launch_compact(psl_presolver* p) {
     launch_long_stats(d, MODE_COMPACT, d.nchunks, RoundSeq{0, 1}, st);
     launch_sweep(d, p->grid, MODE_COMPACT, RoundSeq{0, 1}, st);
   }
-  compact_flags(d, p->cmp, st);
-  compact_write(d, p->cmp, p->red, p->obj_offset, st);
+  compact(d, p->cmp, p->red, p->obj_offset, st);
   HIPCHK(p, hipEventRecord(p->ev[5], st));
   HIPCHK(p, hipMemcpyAsync(p->htot, p->cmp.totals, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIPCHK(p, hipMemcpyAsync(p->h_lpr, p->lpr, (K + 1) * sizeof(LpRed), hipMemcpyDeviceToHost, st));

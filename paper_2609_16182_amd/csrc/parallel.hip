@@ -150,7 +150,12 @@ __device__ __forceinline__ void par_insert_n(const Dev& d, const ParScratch& P, 
   }
 }
 
+// the pass's state cleared, and the active columns as bits
 __global__ void k_par_reset(Dev d, ParScratch P) {
+  write_bits(P.abits, d.n, [&](int64_t j) {
+    double2 b = d.bnd[j];
+    return b.x != b.y;
+  });
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < P.cap; t += stride) {
     HashSlot z;
@@ -606,8 +611,32 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_par_locks(Dev d, ParScratch P) {
   }
 }
 
-__global__ void k_par_emit(Dev d, ParScratch P, int64_t base, int round) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// column lengths lose the merged rows: one wavefront per listed row
+__device__ __forceinline__ void par_drop(const Dev& d, const ParScratch& P, int block, int blocks) {
+  int nv = d.flags->vlist_count;
+  int wstride = blocks * (PSL_BLOCK / PSL_WAVE);
+  for (int k = block * (PSL_BLOCK / PSL_WAVE) + (threadIdx.x >> 6); k < nv; k += wstride) {
+    int r = P.vlist[k];
+    if (P.lead[r] < 0) continue;
+    double lhs = d.lhs[r], rhs = d.rhs[r];  // a removed row is no leader: its own sides
+    for (int p = d.rp[r] + lane_id(); p < d.rp[r + 1]; p += PSL_WAVE) {
+      int j = d.ci[p];
+      double2 b = d.bnd[j];
+      if (b.x != b.y) drop_col(d, j, d.va[p], lhs, rhs);
+    }
+  }
+}
+
+// The records, new sides and removals of the rows, and (by the first
+// drop_blocks workgroups) the columns' lengths: these read the sides of removed
+// rows, which no record changes.
+__global__ void __launch_bounds__(PSL_BLOCK) k_par_emit(Dev d, ParScratch P, int64_t base, int round,
+                                                        int drop_blocks) {
+  if ((int)blockIdx.x < drop_blocks) {
+    par_drop(d, P, blockIdx.x, drop_blocks);
+    return;
+  }
+  int64_t t = (int64_t)(blockIdx.x - drop_blocks) * blockDim.x + threadIdx.x;
   if (t >= d.m) return;
   int i = (int)t;
   Record r;
@@ -646,41 +675,14 @@ __global__ void k_par_emit(Dev d, ParScratch P, int64_t base, int round) {
 // ---------------------------------------------------------------------------
 void launch_par_reset(const Dev& d, const ParScratch& p, hipStream_t s) {
   int64_t t = p.cap > d.m ? p.cap : d.m;
+  if (d.n > t) t = d.n;
   int64_t blocks = (t + PSL_BLOCK - 1) / PSL_BLOCK;
   if (blocks > 8192) blocks = 8192;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(k_par_reset, dim3((unsigned)blocks), dim3(PSL_BLOCK), 0, s, d, p);
 }
 
-// column lengths lose the merged rows: one wavefront per listed row
-__global__ void __launch_bounds__(PSL_BLOCK) k_par_drop(Dev d, ParScratch P) {
-  int nv = d.flags->vlist_count;
-  int wstride = gridDim.x * (PSL_BLOCK / PSL_WAVE);
-  for (int k = blockIdx.x * (PSL_BLOCK / PSL_WAVE) + (threadIdx.x >> 6); k < nv; k += wstride) {
-    int r = P.vlist[k];
-    if (P.lead[r] < 0) continue;
-    double lhs = d.lhs[r], rhs = d.rhs[r];  // a removed row is no leader: its own sides
-    for (int p = d.rp[r] + lane_id(); p < d.rp[r + 1]; p += PSL_WAVE) {
-      int j = d.ci[p];
-      double2 b = d.bnd[j];
-      if (b.x != b.y) drop_col(d, j, d.va[p], lhs, rhs);
-    }
-  }
-}
-
-__global__ void k_par_bits(Dev d, ParScratch P) {
-  write_bits(P.abits, d.n, [&](int64_t j) {
-    double2 b = d.bnd[j];
-    return b.x != b.y;
-  });
-}
-
 void launch_par_hash(const Dev& d, const ParScratch& p, const SweepGrid& g, hipStream_t s) {
-  if (d.n > 0) {
-    int64_t b = (d.n + PSL_BLOCK - 1) / PSL_BLOCK;
-    if (b > 16384) b = 16384;
-    hipLaunchKernelGGL(k_par_bits, dim3((unsigned)b), dim3(PSL_BLOCK), 0, s, d, p);
-  }
   int total = 0;
   for (int b = 0; b < NBINS; ++b) total += g.nb[b];
   if (d.nlong > 0)
@@ -692,13 +694,15 @@ void launch_par_hash(const Dev& d, const ParScratch& p, const SweepGrid& g, hipS
   if (d.m > 0) hipLaunchKernelGGL(k_par_vlist, dim3((d.m + VLIST_BLOCK - 1) / VLIST_BLOCK), dim3(VLIST_BLOCK), 0, s, d, p);
 }
 
-void launch_par_drop(const Dev& d, const ParScratch& p, hipStream_t s) {
-  hipLaunchKernelGGL(k_par_drop, dim3(1024), dim3(PSL_BLOCK), 0, s, d, p);
+// workgroups for the listed rows (at most every row), per_wg of them at a time
+static unsigned list_blocks(const Dev& d, int per_wg, int64_t most) {
+  return (unsigned)std::min<int64_t>(most, ((int64_t)d.m + per_wg - 1) / per_wg);
 }
 
 void launch_par_verify(const Dev& d, const ParScratch& p, hipStream_t s) {
-  hipLaunchKernelGGL(k_par_verify, dim3(2048), dim3(PSL_BLOCK), 0, s, d, p);
-  hipLaunchKernelGGL(k_par_src, dim3(1024), dim3(PSL_BLOCK), 0, s, d, p);
+  if (d.m == 0) return;
+  hipLaunchKernelGGL(k_par_verify, dim3(list_blocks(d, PSL_BLOCK / PSL_WAVE, 2048)), dim3(PSL_BLOCK), 0, s, d, p);
+  hipLaunchKernelGGL(k_par_src, dim3(list_blocks(d, PSL_BLOCK, 1024)), dim3(PSL_BLOCK), 0, s, d, p);
 }
 
 void launch_par_count(const Dev& d, const ParScratch& p, hipStream_t s) {
@@ -709,7 +713,8 @@ void launch_par_count(const Dev& d, const ParScratch& p, hipStream_t s) {
 
 void launch_par_emit(const Dev& d, const ParScratch& p, int64_t base, int round, hipStream_t s) {
   if (d.m == 0) return;
-  hipLaunchKernelGGL(k_par_emit, dim3((d.m + PSL_BLOCK - 1) / PSL_BLOCK), dim3(PSL_BLOCK), 0, s, d, p, base, round);
+  const unsigned rows = (d.m + PSL_BLOCK - 1) / PSL_BLOCK, drop = list_blocks(d, PSL_BLOCK / PSL_WAVE, 1024);
+  hipLaunchKernelGGL(k_par_emit, dim3(drop + rows), dim3(PSL_BLOCK), 0, s, d, p, base, round, (int)drop);
 }
 
 }  // namespace psl

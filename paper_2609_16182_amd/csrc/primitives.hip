@@ -360,27 +360,6 @@ void radix_pass_payload(const uint32_t* keys_in, const int32_t* rows_in, const i
 // canonical pairwise sum of an array
 // ---------------------------------------------------------------------------
 
-#define PW_TILE 2048
-
-// Sum of one aligned tile x[0..2048) (elements at or beyond lim read as 0) by
-// the whole block: eight contiguous leaves per thread (tree of 8), a butterfly
-// over the wave (tree of 64 such groups), then the four wave sums as
-// (w0 + w1) + (w2 + w3). Every thread returns the sum.
-__device__ __forceinline__ double tile_sum(const double* x, int64_t lim) {
-  __shared__ double ws[PSL_BLOCK / PSL_WAVE];
-  int64_t base = (int64_t)threadIdx.x * 8;
-  double v[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = base + k < lim ? x[base + k] : 0.0;
-  double s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-  s = group_sum<PSL_WAVE>(s);
-  if (lane_id() == 0) ws[threadIdx.x >> 6] = s;
-  __syncthreads();
-  double t = (ws[0] + ws[1]) + (ws[2] + ws[3]);
-  __syncthreads();
-  return t;
-}
-
 // Each block sums the aligned chunk [2048 b, 2048 b + 2048).
 __global__ void __launch_bounds__(PSL_BLOCK) k_pw_chunks(const double* x, int64_t n, double* out) {
   int64_t base = (int64_t)blockIdx.x * PW_TILE;

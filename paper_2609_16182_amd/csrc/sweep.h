@@ -160,7 +160,6 @@ void launch_par_hash(const Dev& d, const ParScratch& p, const SweepGrid& g, hipS
 void launch_par_verify(const Dev& d, const ParScratch& p, hipStream_t s);
 void launch_par_count(const Dev& d, const ParScratch& p, hipStream_t s);
 void launch_par_emit(const Dev& d, const ParScratch& p, int64_t base, int round, hipStream_t s);
-void launch_par_drop(const Dev& d, const ParScratch& p, hipStream_t s);
 
 // doubleton.hip: doubleton-equality substitution (allocated when enabled)
 // a rewrite of a long row that inserts the kept column (entries move by one
@@ -208,18 +207,17 @@ struct LpRed {           // bases of an LP's reduced problem in the batch's arra
   int32_t eb, qb;        // first position in the reduced CSR / transposed copy
 };
 struct CompactScratch {
-  int32_t* row_new;       // [m]     kept flags -> new row ids
-  int32_t* col_new;       // [n]     kept flags -> new column ids
-  uint8_t* col_keep;      // [n]     kept columns (bytes)
-  RankWord* rbits;        // [m/64+1] kept rows, one bit each, with ranks
-  RankWord* cbits;        // [n/64+1] kept columns, one bit each, with ranks
-  double* terms;          // [n]     cost terms of removed columns
+  RankWord* rbits;        // [m/64+1] kept rows, one bit each, with ranks in their tile
+  RankWord* cbits;        // [n/64+1] kept columns
+  RankWord* ebits;        // [nnz/64+1] kept positions of the CSR
+  RankWord* qbits;        // [nnz/64+1] kept positions of the transposed copy
+  int32_t* tile_off;      // [compact_tiles+1] kept items before each tile
+  int t_col, t_csr, t_csc, tiles;  // first tiles of the columns, CSR, transposed copy; all
+  double* terms;          // [n]     cost terms of removed columns (K = 1: of their tiles)
   double* pws;            // pairwise-sum workspace; pws[0] = the sum
   int32_t* totals;        // [4]     m', n', nnz' (CSR), nnz' (transposed)
   double* offset;         // [1]     reduced objective offset
   int32_t* ws;            // scan workspace
-  int32_t* eflag;         // [nnz+1] CSR keep flags -> output positions
-  int32_t* qflag;         // [nnz+1] transposed keep flags -> output positions
   const int32_t* rowid1;  // row of CSR position p at index p + 1
   const uint32_t* colid;  // column of each position of the transposed copy
   LpRed* lpr;             // [K+1] per-LP bases (lpr[K] = totals)
@@ -227,11 +225,10 @@ struct CompactScratch {
   const int32_t* seg_host;//        the same on the host
   const double* lp_off_in;// [K] input objective offsets (K > 1)
 };
-// flags and scans (totals written to c.totals)
-void compact_flags(const Dev& d, const CompactScratch& c, hipStream_t s);
-// offset(s), gather of both layouts, vectors, maps and classes; with K > 1 the
-// offsets go to c.offset[0..K)
-void compact_write(const Dev& d, const CompactScratch& c, const Reduced& r, double obj_offset, hipStream_t s);
+int64_t compact_tiles(int64_t m, int64_t n, int64_t nnz);
+// the reduced problem: both layouts, vectors, maps and classes, c.totals and
+// the offset(s) (with K > 1 in c.offset[0..K))
+void compact(const Dev& d, const CompactScratch& c, const Reduced& r, double obj_offset, hipStream_t s);
 
 // batch.hip
 struct LpDesc {        // one LP of a batch, as given (device pointers)

@@ -79,3 +79,15 @@ def test_first_invalid_entry(at, what):
     with pytest.raises(psl.PslError) as e:
         psl.presolve(lp)
     assert str(at) in str(e.value)
+
+
+@pytest.mark.parametrize("m,n", [(2047, 2049), (2048, 2048), (4096, 63), (64, 4097)])
+def test_reduced_problem_tiles(m, n):
+    """Kept rows, columns and entries are ranked in tiles of 2048, 64 to a word."""
+    rng = np.random.default_rng(m)
+    lp = lp_of_lengths(rng.integers(0, 5, m), n, seed=n)
+    fixed = rng.random(n) < 0.3
+    lp["ub"] = np.where(fixed & np.isfinite(lp["lb"]), lp["lb"], lp["ub"])
+    out, p = psl.presolve(lp, max_rounds=1, max_outer=1)
+    p.close()
+    assert_same(out, O.presolve(lp, max_rounds=1, max_outer=1), f"{m} x {n}")
