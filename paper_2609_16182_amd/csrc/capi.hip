@@ -1161,8 +1161,9 @@ static psl_status launch_round(psl_presolver* p) {
     launch_decide(d, p->grid, rm, ctl, p->dense, round, seq, d.cnt, st);
     // (the candidate regions are free until the next sweep)
     if (s.enable_free_singletons) {
-      launch_free_singletons(d, reinterpret_cast<int32_t*>(d.cand), round, seq, p->ws, st);
-      launch_control(d, ctl, seq, st);
+      int32_t* fs_list = reinterpret_cast<int32_t*>(d.cand);
+      launch_free_singletons(d, fs_list, round, seq, st);
+      launch_control(d, ctl, fs_list, seq, st);
     }
     if (!d.direct)
       select_next(d, p->thresholds[0], p->thresholds[2], p->bins_s, p->chunks_s, d.flags->sel[1], seq, st);

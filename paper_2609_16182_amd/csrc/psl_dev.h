@@ -126,7 +126,7 @@ struct Flags {
                            // only, bit 1: inert rows skipped), set with the decisions
   int64_t error_pos;
   int32_t lead_count;      // parallel pass: leaders whose merged sides add locks
-  int32_t fs_total;        // free singleton eliminations of the round
+  int32_t fs_picks;        // the last round with a free singleton candidate
   int32_t fs_rows;         // chunks of long eliminated rows listed
   int32_t fs_claims;       // chunks of long substituting rows listed
   int32_t dbl_count;       // doubleton-equality candidates listed

@@ -26,8 +26,14 @@
 
 namespace psl {
 
+// Most rounds have no candidate. A round that has marks flags->fs_picks with
+// its number, and without the mark the launches after the first return at once;
+// those of the chunk lists have one workgroup a CU at most. (1e6 rows with every
+// option: 12 launches of 55 us together a round, 8 of 36 now.)
 #define FS_SHORT 32
 #define FS_CHUNK PSL_BLOCK
+#define FS_LIST_BLOCKS 256
+#define FS_SUPER 64  // tiles whose counts are added up for the offsets
 #define FS_NONE 0x7FFFFFFF
 
 // the LP stopped (infeasible or unbounded, this round or before) or is done
@@ -35,6 +41,12 @@ namespace psl {
 __device__ __forceinline__ bool lp_stopped(const Dev& d, int lp) {
   if (d.K > 1) return d.lp_ok[lp] == 0;
   return (d.flags->infeasible | d.flags->unbounded) != 0;
+}
+
+// round seq is not run, or has no candidate
+__device__ __forceinline__ bool fs_idle(const Dev& d, int seq) {
+  const bool none = d.flags->fs_picks != seq;
+  return round_over(d, seq) || none;
 }
 
 // the column's one alive row i takes the column when each bound side is
@@ -54,13 +66,15 @@ __device__ __forceinline__ void fs_offer(const Dev& d, int j, int i) {
 __global__ void __launch_bounds__(PSL_BLOCK) k_fs_pick(Dev d, int seq) {
   if (round_over(d, seq)) return;
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j == 0) d.flags->fs_claims = 0;
+  if (j == 0) d.flags->fs_claims = d.flags->fs_rows = 0;
   bool want = false;
   if (j < d.n && d.fs_flag[j]) {
     d.fs_flag[j] = 0;
     double2 b = d.bnd[j];
     want = b.x != b.y && d.col_len[j] == 1 && !lp_stopped(d, col_lp_of(d, (int)j));
   }
+  if (__ballot(want) == 0) return;
+  if (lane_id() == 0) d.flags->fs_picks = seq;
   int q0 = 0, q1 = 0;
   if (want) {
     q0 = d.cp[j];
@@ -122,9 +136,10 @@ __device__ __forceinline__ unsigned long long fs_key(int round, int i) {
 // rows whose column has a cost: an infinite preferred side stops the LP;
 // otherwise they claim their columns (long rows through the claim list)
 __global__ void k_fs_claim(Dev d, int32_t* clist, int round, int seq) {
-  if (round_over(d, seq)) return;
+  if (fs_idle(d, seq)) return;
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= d.m) return;
+  if (t <= d.m / (PSL_BLOCK * FS_SUPER)) d.off[t] = 0;  // for the count
   int i = (int)t;
   int j = d.fs_pick[i];
   if (j == FS_NONE) return;
@@ -149,7 +164,7 @@ __global__ void k_fs_claim(Dev d, int32_t* clist, int round, int seq) {
 // row when a lower row holds one of them
 template <int MODE>
 __global__ void __launch_bounds__(PSL_BLOCK) k_fs_claim_long(Dev d, const int32_t* clist, int round, int seq) {
-  if (round_over(d, seq)) return;
+  if (fs_idle(d, seq)) return;
   int nc = d.flags->fs_claims;
   for (int k = blockIdx.x; k < nc; k += gridDim.x) {
     int p0 = clist[k];
@@ -176,11 +191,10 @@ __device__ __forceinline__ bool fs_applies(const Dev& d, int i, int j, int round
 }
 
 // applying rows keep their pick, the others drop it; d.cnt gets the count
-// of each tile of PSL_BLOCK rows
+// of each tile of PSL_BLOCK rows, d.off that of each FS_SUPER tiles
 __global__ void __launch_bounds__(PSL_BLOCK) k_fs_count(Dev d, int round, int seq) {
-  if (round_over(d, seq)) return;
+  if (fs_idle(d, seq)) return;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) d.flags->fs_rows = 0;
   int k = 0;
   if (i < d.m) {
     int j = d.fs_pick[i];
@@ -195,7 +209,10 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_count(Dev d, int round, int se
   }
   int tot;
   block_excl_scan(k, &tot);
-  if (threadIdx.x == 0) d.cnt[blockIdx.x] = tot;
+  if (threadIdx.x == 0) {
+    d.cnt[blockIdx.x] = tot;
+    if (tot) atomicAdd(&d.off[blockIdx.x / FS_SUPER], tot);
+  }
 }
 
 // the other columns of an applying row: a new cost (with a substitution) and
@@ -209,14 +226,24 @@ __device__ __forceinline__ void fs_entry(const Dev& d, int jj, double a, double2
   if (b.x != b.y) drop_col(d, jj, a, lhs, rhs);
 }
 
-// records after the round's decision records, in row order (tile offsets
-// from the scanned tile counts, a block scan inside the tile); the row
+// records after the round's decision records, in row order (the counts of the
+// tiles before added up by the workgroup, a block scan inside the tile); the row
 // leaves, its column is set to s / a_ij (0 without a cost); a short row
 // updates and leaves its other columns here, a long one is listed in chunks
 // (and keeps its pick for them)
 __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int round, int seq) {
-  if (round_over(d, seq)) return;
+  if (fs_idle(d, seq)) return;
   if (d.cnt[blockIdx.x] == 0) return;  // no row of the tile applies
+  int before = 0;
+  {
+    const int sup = blockIdx.x / FS_SUPER;
+    for (int k = threadIdx.x; k < sup; k += PSL_BLOCK) before += d.off[k];
+    const int b = sup * FS_SUPER + threadIdx.x;
+    if (threadIdx.x < FS_SUPER && b < (int)blockIdx.x) before += d.cnt[b];
+    int all;
+    block_excl_scan(before, &all);
+    before = all;
+  }
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int j = t < d.m ? d.fs_pick[t] : FS_NONE;
   int tot;
@@ -240,7 +267,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
   rec.v[1] = lhs;
   rec.v[2] = rhs;
   rec.v[3] = cj;
-  d.rec[d.flags->rec_base + d.flags->round_total + d.off[blockIdx.x] + pre] = rec;
+  d.rec[d.flags->rec_base + d.flags->round_total + before + pre] = rec;
   d.row_on[i] = 0;
   d.bnd[j] = make_double2(v, v);
   d.bkey[2 * (int64_t)j] = dkey(v);
@@ -273,13 +300,19 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_emit(Dev d, int32_t* list, int
 }
 
 // the listed chunks of long applying rows: one workgroup per chunk, a
-// position a thread (the row's own column was set at its emission)
+// position a thread (the row's own column was set at its emission); adds the
+// round's eliminations to its totals
 __global__ void __launch_bounds__(PSL_BLOCK) k_fs_drop(Dev d, const int32_t* list, int seq) {
-  if (round_over(d, seq)) return;
+  if (fs_idle(d, seq)) return;
   int nc = d.flags->fs_rows;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    d.flags->round_total += d.flags->fs_total;
-    d.flags->rows_removed += d.flags->fs_total;
+  if (blockIdx.x == 0) {
+    int own = 0, all;
+    for (int k = threadIdx.x; k <= d.m / (PSL_BLOCK * FS_SUPER); k += PSL_BLOCK) own += d.off[k];
+    block_excl_scan(own, &all);
+    if (threadIdx.x == 0) {
+      d.flags->round_total += all;
+      d.flags->rows_removed += all;
+    }
   }
   for (int k = blockIdx.x; k < nc; k += gridDim.x) {
     int p0 = list[k];
@@ -295,18 +328,7 @@ __global__ void __launch_bounds__(PSL_BLOCK) k_fs_drop(Dev d, const int32_t* lis
   }
 }
 
-// the long rows' picks, once all their chunks are done
-__global__ void k_fs_reset(Dev d, const int32_t* list, int seq) {
-  if (round_over(d, seq)) return;
-  int nc = d.flags->fs_rows;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nc; k += gridDim.x * blockDim.x) {
-    int p0 = list[k];
-    int i = d.rowid1[p0 + 1];
-    if (p0 == d.rp[i]) d.fs_pick[i] = FS_NONE;  // the row's first chunk
-  }
-}
-
-void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, int32_t* ws, hipStream_t s) {
+void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, hipStream_t s) {
   if (d.m == 0 || d.n == 0) return;
   // the claim chunks follow the room of the drop chunks (at most nnz / FS_SHORT
   // + m of each)
@@ -315,14 +337,11 @@ void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, int
   unsigned rb = (unsigned)((d.m + PSL_BLOCK - 1) / PSL_BLOCK);
   hipLaunchKernelGGL(k_fs_pick, dim3(cb), dim3(PSL_BLOCK), 0, s, d, seq);
   hipLaunchKernelGGL(k_fs_claim, dim3(rb), dim3(PSL_BLOCK), 0, s, d, clist, round, seq);
-  hipLaunchKernelGGL((k_fs_claim_long<0>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
-  hipLaunchKernelGGL((k_fs_claim_long<1>), dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
+  hipLaunchKernelGGL((k_fs_claim_long<0>), dim3(FS_LIST_BLOCKS), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
+  hipLaunchKernelGGL((k_fs_claim_long<1>), dim3(FS_LIST_BLOCKS), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)clist, round, seq);
   hipLaunchKernelGGL(k_fs_count, dim3(rb), dim3(PSL_BLOCK), 0, s, d, round, seq);
-  // tile counts (rb <= m entries of d.cnt) scanned
-  scan_excl(d.cnt, d.off, rb, &d.flags->fs_total, ws, s);
   hipLaunchKernelGGL(k_fs_emit, dim3(rb), dim3(PSL_BLOCK), 0, s, d, list, round, seq);
-  hipLaunchKernelGGL(k_fs_drop, dim3(1024), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list, seq);
-  hipLaunchKernelGGL(k_fs_reset, dim3(64), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list, seq);
+  hipLaunchKernelGGL(k_fs_drop, dim3(FS_LIST_BLOCKS), dim3(PSL_BLOCK), 0, s, d, (const int32_t*)list, seq);
 }
 
 }  // namespace psl

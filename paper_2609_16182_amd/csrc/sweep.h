@@ -58,7 +58,7 @@ int64_t decide_tiles(int64_t m, int64_t n);
 size_t decide_supers(int64_t m, int64_t n);
 void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, const RoundCtl& ctl, bool dense, int round,
                    int seq, int32_t* tile_sum, hipStream_t s);
-void launch_control(const Dev& d, const RoundCtl& ctl, int seq, hipStream_t s);
+void launch_control(const Dev& d, const RoundCtl& ctl, const int32_t* fs_list, int seq, hipStream_t s);
 int long_max_passes();
 
 // ingest.hip
@@ -134,7 +134,7 @@ void launch_par_cols(const Dev& d, const ColScratch& P, int64_t base, int round,
 // (records after the round's others; list: nnz / 32 + m ints of
 // scratch; adds its records to d.flags->round_total and its rows to
 // rows_removed)
-void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, int32_t* ws, hipStream_t s);
+void launch_free_singletons(const Dev& d, int32_t* list, int round, int seq, hipStream_t s);
 
 // parallel.hip
 struct LpTab {        // an LP's slice of the parallel-row table

@@ -1472,8 +1472,18 @@ __device__ __forceinline__ void round_control(const Dev& d, const RoundCtl& ctl,
   if (!go_on || (!ctl.last && f.rec_at + ctl.need > f.rec_cap)) f.stop_at = seq;
 }
 
-__global__ void __launch_bounds__(PSL_BLOCK) k_round_control(Dev d, RoundCtl ctl, int seq) {
-  round_control(d, ctl, round_over(d, seq), seq);
+// Rounds with free singletons: the control after them (the first workgroup), and
+// the picks of the long rows they took (the chunks listed), all of whose chunks
+// are done.
+__global__ void __launch_bounds__(PSL_BLOCK) k_round_control(Dev d, RoundCtl ctl, const int32_t* list, int seq) {
+  const bool over = round_over(d, seq);
+  const int nc = over || d.flags->fs_picks != seq ? 0 : d.flags->fs_rows;
+  for (int k = blockIdx.x * PSL_BLOCK + threadIdx.x; k < nc; k += gridDim.x * PSL_BLOCK) {
+    int p0 = list[k];
+    int i = d.rowid1[p0 + 1];
+    if (p0 == d.rp[i]) d.fs_pick[i] = 0x7FFFFFFF;  // the row's first chunk
+  }
+  if (blockIdx.x == 0) round_control(d, ctl, over, seq);
 }
 
 // Records of the round in index order: a tile's offset is the sum of the tiles
@@ -1614,11 +1624,11 @@ void launch_decide(const Dev& d, const SweepGrid& g, const RoundMode& rm, const 
   hipLaunchKernelGGL(k_decide, dim3((unsigned)(tg.nsrc + nt)), dim3(DEC_BLOCK), 0, s, d, g, tg, rm, seq, tile_sum);
   hipLaunchKernelGGL(k_decide_emit, dim3((unsigned)(nt + 1)), dim3(DEC_BLOCK), 0, s, d, (const int32_t*)tile_sum, tg,
                      ctl, round, seq);
-  if (dense) hipLaunchKernelGGL(k_mark_dense, dim3(1024), dim3(PSL_BLOCK), 0, s, d, seq);
+  if (dense) hipLaunchKernelGGL(k_mark_dense, dim3(512), dim3(PSL_BLOCK), 0, s, d, seq);
 }
 
-void launch_control(const Dev& d, const RoundCtl& ctl, int seq, hipStream_t s) {
-  hipLaunchKernelGGL(k_round_control, dim3(1), dim3(PSL_BLOCK), 0, s, d, ctl, seq);
+void launch_control(const Dev& d, const RoundCtl& ctl, const int32_t* fs_list, int seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_round_control, dim3(32), dim3(PSL_BLOCK), 0, s, d, ctl, fs_list, seq);
 }
 
 int long_max_passes() { return LONG_MAX_PASSES; }

@@ -109,3 +109,10 @@ def test_long_column_accumulators(entries):
     accumulator before the atomic."""
     lp = with_long_column(6000, entries, seed=5)
     assert_same(gpu(lp), O.presolve(lp), f"{entries} entries")
+
+
+@pytest.mark.parametrize("m", [255, 257, 16384, 16385, 33000])
+def test_free_singleton_tiles(m):
+    """Eliminations are counted in tiles of 256 rows, 64 tiles to a sum."""
+    lp = lp_of(m, m + m // 4, seed=m)
+    assert_same(gpu(lp, enable_free_singletons=1), O.presolve(lp, enable_free_singletons=1), f"{m} rows")
