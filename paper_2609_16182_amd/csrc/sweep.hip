@@ -1579,7 +1579,11 @@ static void sweep_launches(const Dev& d, const SweepGrid& g, bool split, RoundSe
   int n_wide = g.nb[BIN_W4] + g.nb[BIN_W8];
   int n_long = MODE == MODE_ROUND ? g.nb[BIN_LONG] : 0;
   dim3 blk(PSL_BLOCK);
-  if (!split) {
+  // Without wide and long rows the short kind's kernel alone: it holds none of
+  // their code, and its pointers stay in scalar registers (a presolve of 523 rows
+  // 1.28 ms with the kernel of all kinds, 1.24 with this; 31337 rows 1.06 and
+  // 1.04; a 4096-LP batch 71.4 and 70.6). With such rows they run beside each other.
+  if (!split && n_wide + n_long > 0) {
     int total = n_short + n_wide + n_long;
     if (total) hipLaunchKernelGGL((k_sweep<MODE, KIND_ALL, DIR>), dim3(total), blk, 0, s, d, g, 0, rs);
     return;
