@@ -383,6 +383,7 @@ static psl_status setup_arena(psl_presolver* p) {
     ALLOC(p->lp_round, K);
     ALLOC(p->lp_round_b, K);
     ALLOC(p->lp_ok, K);
+    ALLOC(p->lp_run, K);
     ALLOC(p->lpf, K);
     ALLOC(p->lpo, K);
     ALLOC(p->lpt, K);
@@ -450,6 +451,7 @@ static psl_status setup_arena(psl_presolver* p) {
   d.lp_row0 = p->lp_row0;
   d.lp_col0 = p->lp_col0;
   d.lp_ok = p->lp_ok;
+  d.lp_run = p->lp_run;
   d.lp_round = p->lp_round;
   d.lp_round_next = p->lp_round_b;
   d.lpf = p->lpf;
@@ -467,7 +469,7 @@ static psl_status setup_arena(psl_presolver* p) {
   for (const void* q : ptrs)
     if (!q) return fail(p, PSL_ERR_DEVICE, "internal: a device array was not set up");
   if (K > 1) {
-    const void* bp[] = {d.row_lp, d.col_lp, d.lp_row0, d.lp_col0, d.lp_ok, d.lp_round, d.lpf, d.lpo, p->lpt,
+    const void* bp[] = {d.row_lp, d.col_lp, d.lp_row0, d.lp_col0, d.lp_ok, d.lp_run, d.lp_round, d.lpf, d.lpo, p->lpt,
                         p->lp_z0, p->descs, p->lp_off_in, p->rec_off, p->bins_0};
     for (const void* q : bp)
       if (!q) return fail(p, PSL_ERR_DEVICE, "internal: a batch array was not set up");

@@ -76,7 +76,7 @@ struct psl_presolver {
   // batch (K > 1): device maps and per-LP arrays, pinned host mirrors
   int32_t K = 1;
   int32_t *row_lp = nullptr, *col_lp = nullptr, *lp_row0 = nullptr, *lp_col0 = nullptr, *lp_round = nullptr, *lp_round_b = nullptr;
-  uint8_t* lp_ok = nullptr;
+  uint8_t *lp_ok = nullptr, *lp_run = nullptr;
   LpFlags* lpf = nullptr;
   LpOut* lpo = nullptr;
   LpTab* lpt = nullptr;

@@ -585,6 +585,7 @@ __global__ void k_rounds_begin(Dev d, int64_t rec_at, int64_t rec_cap) {
   if (d.K > 1 && k < d.K) {
     d.lpf[k] = LpFlags{0, 0, 0, 0};
     d.lpo[k] = LpOut{0, 0};
+    d.lp_run[k] = d.lp_ok[k];
   }
 }
 

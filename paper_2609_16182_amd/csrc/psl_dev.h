@@ -224,6 +224,7 @@ struct Dev {
   const int32_t *lp_row0, *lp_col0;   // [K+1] first row / column of each LP
   uint8_t *lp_ok;                     // [K] LP still presolving (its rows stay in the bins;
                                       // cleared here when the LP stops)
+  uint8_t *lp_run;                    // [K] lp_ok at the start of the round, kept through it
   const int32_t *lp_round;            // [K] the LP's own number of the current round
   int32_t *lp_round_next;             // the same after the round, written by its control
   LpFlags *lpf;                       // [K]
@@ -247,9 +248,16 @@ __device__ __forceinline__ int bin_rows_listed(const Dev& d, int b) {
   return d.direct ? d.bin_off[b + 1] - d.bin_off[b] : d.sel[b].v;
 }
 __device__ __forceinline__ int chunks_listed(const Dev& d) { return d.direct ? d.nchunks : d.sel[SEL_CHUNKS].v; }
-// (direct lists hold rows of every LP) the row's LP is still presolving
+// (direct lists hold rows of every LP) the row's LP is still presolving; for
+// kernels beside which none stops an LP
 __device__ __forceinline__ bool row_lp_on(const Dev& d, int i) {
   return !d.direct || d.K == 1 || d.lp_ok[d.row_lp[i]] != 0;
+}
+// ... was presolving when the round began: for the sweep, whose workgroups stop
+// LPs while others still read their rows. All rows of an LP take part in the
+// round that stops it, as where the LP is alone.
+__device__ __forceinline__ bool row_lp_swept(const Dev& d, int i) {
+  return !d.direct || d.K == 1 || d.lp_run[d.row_lp[i]] != 0;
 }
 
 // A value the compiler has to have loaded here: loads written before it are

@@ -101,7 +101,7 @@ void select_all(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout
 void select_next(const Dev& d, int t_long, int t_g8, BinEnt* out, LongChunk* cout, SelCnt* cnt, int seq,
                  hipStream_t s);
 // before rounds are queued: the record buffer's state, no stop, and (K > 1)
-// the LPs' flags cleared
+// the LPs' flags cleared and those still presolving noted
 void launch_rounds_begin(const Dev& d, int64_t rec_at, int64_t rec_cap, hipStream_t s);
 // chunk table of the long rows (d.nlong set); total chunks to *total (device)
 // totals[0] = chunks, totals[1] = candidate units of all chunks

@@ -407,8 +407,8 @@ __device__ __forceinline__ void row_take(const BinEnt& be, bool vr, RowOf& r) {
 
 // Second level: the row's sides and flags, beside the positions (columns and
 // coefficients); the third level, the bounds, is issued by load_els or by the
-// caller. A row of the direct lists is swept when it is active, of an LP still
-// presolving and, by the mode, marked / not inert.
+// caller. A row of the direct lists is swept when it is active, of an LP that was
+// presolving when the round began and, by the mode, marked / not inert.
 template <int MODE, bool DIR>
 __device__ __forceinline__ void row_data(const Dev& d, const RoundArgs& ra, RowOf& r) {
   r.lhs = d.lhs[r.row];
@@ -418,7 +418,7 @@ __device__ __forceinline__ void row_data(const Dev& d, const RoundArgs& ra, RowO
   } else if (DIR) {
     uint8_t on = d.row_on[r.row], dt = d.dirty[r.row];
     int2 rf = d.rinf[r.row];
-    r.on = r.vr && on != 0 && (!(ra.mode & 1) || dt == ra.mark) && row_lp_on(d, r.row) &&
+    r.on = r.vr && on != 0 && (!(ra.mode & 1) || dt == ra.mark) && row_lp_swept(d, r.row) &&
            (!(ra.mode & 2) || !row_inert(rf, r.lhs, r.rhs));
   } else {
     r.on = r.vr;  // selected
@@ -652,10 +652,11 @@ __device__ __forceinline__ void pass_stats(const Dev& d, int64_t s0, int len, in
 
 // Is long row `row` (active) swept this round, from the direct lists? Every
 // workgroup of the row's chunks takes the same answer: the counts its inert
-// test reads are rewritten by the sweep with the values they have.
+// test reads are rewritten by the sweep with the values they have, and the
+// LP's state is the one at the round's start.
 __device__ __forceinline__ bool long_swept(const Dev& d, int row, RoundSeq rs) {
   int mode = rs.full ? 0 : d.flags->mode;
-  return (!(mode & 1) || d.dirty[row] == round_mark(rs.seq)) && row_lp_on(d, row) &&
+  return (!(mode & 1) || d.dirty[row] == round_mark(rs.seq)) && row_lp_swept(d, row) &&
          (!(mode & 2) || !row_inert(d.rinf[row], d.lhs[row], d.rhs[row]));
 }
 
@@ -1447,6 +1448,7 @@ __device__ __forceinline__ void round_control(const Dev& d, const RoundCtl& ctl,
         any = any || more;
       }
       d.lp_round_next[k] = r;
+      d.lp_run[k] = d.lp_ok[k];
     }
     if (any) go_on = 1;
   }
