@@ -505,7 +505,10 @@ const char *psl_batch_last_error(const psl_batch *b);
  * in the device-memory budget, and presolves them as one batch. Several slots
  * run at once, each with its own stream, host thread and device arena, so LPs
  * that arrive while others are on the device start as soon as a slot and
- * memory are free and their work overlaps on the device. Reduced problems
+ * memory are free and their work overlaps on the device. While small LPs come
+ * quickly and beside each other, a free slot's thread lets the queue grow for up
+ * to 0.4 ms first; a request that follows the answer to the one before, or a
+ * pause, does not wait. Reduced problems
  * stay on the device until released. Each request's outcome, records and
  * reduced problem are exactly those psl_presolve_run gives for its LP alone.
  * The server's functions may be called from any thread. */
