@@ -1127,7 +1127,8 @@ static psl_status launch_round(psl_presolver* p) {
     HIPCHK(p, hipMemcpyAsync(const_cast<int32_t*>(p->d.lp_round), p->h_round, p->K * sizeof(int32_t), hipMemcpyHostToDevice, st));
   }
   launch_rounds_begin(d, p->rec_count - p->rec_flushed, p->rec_cap, st);
-  const bool ahead = p->nnz <= RUN_AHEAD_NNZ && !p->step_rounds;
+  // (the trace has a line for each round, from the reads after it)
+  const bool ahead = p->nnz <= RUN_AHEAD_NNZ && !p->step_rounds && !p->trace;
   R.queued = std::min(ahead ? RUN_AHEAD : 1, s.max_rounds - R.r);
   for (int q = 0; q < R.queued; ++q) {
     const int seq = ++R.seq, round = R.round + 1 + q;
@@ -1197,10 +1198,7 @@ static psl_status complete_round(psl_presolver* p) {
   const double sb = 12.0 * f.sum_nnz + 48.0 * f.sum_rows + 32.0 * f.sum_cols;
   // the decisions over every row and column, and the rounds' records
   S.alg_bytes += sb - S.sweep_bytes + 40.0 * done * ((double)p->m + p->n) + 48.0 * recs;
-  if (p->trace)
-    std::fprintf(stderr, "[psl] rounds to %d: swept rows %lld nnz %lld, records %lld, last round: %d, rows removed %d, "
-                 "bounds made finite %d\n", R.round + done, (long long)(f.sum_rows - R.rows_before),
-                 (long long)(f.sum_nnz - S.sweep_nnz), (long long)recs, f.round_total, f.rows_removed, f.fin_cols);
+  const long long swept_rows = f.sum_rows - R.rows_before, swept_nnz = f.sum_nnz - S.sweep_nnz;
   R.rows_before = f.sum_rows;
   S.sweep_bytes = sb;
   S.sweep_nnz = f.sum_nnz;
@@ -1226,6 +1224,10 @@ static psl_status complete_round(psl_presolver* p) {
       ++nprop;
     }
   }
+  if (p->trace)
+    std::fprintf(stderr, "[psl] round %d: swept rows %lld nnz %lld, records %d, rows removed %d, "
+                 "bounds made finite %d, LPs propagating %d\n", R.round, swept_rows, swept_nnz, f.round_total,
+                 f.rows_removed, f.fin_cols, nprop);
   // (an LP found infeasible or unbounded has left lp_ok on the device)
   if (nprop > 0 && R.r < p->s.max_rounds) R.unit = U_ROUND;
   else rounds_end(p);
