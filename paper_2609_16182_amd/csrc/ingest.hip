@@ -4,6 +4,8 @@
 // The paper keeps A together with its transpose (section 3.2, "Internal data
 // structures"). The transpose is built here by a stable radix sort of the CSR
 // positions by column, so the rows of every column come out ascending.
+#include <algorithm>
+
 #include "psl_kern.h"
 #include "sweep.h"
 
@@ -265,7 +267,10 @@ void launch_checks(const Dev& d, const double* lb_in, const double* ub_in, doubl
   // the first pass's digits, as build_csc splits them
   const int bits = csc_bits(d), passes = (bits + 7) / 8, per = passes ? (bits + passes - 1) / passes : 0;
   const int64_t pt = (d.nnz + POS_TILE - 1) / POS_TILE;
-  hipLaunchKernelGGL(k_positions, dim3((unsigned)(pt > 0 ? pt : 1)), dim3(PSL_BLOCK), 0, s, d, sc.rowid1,
+  // and enough workgroups for cp where the columns are many and the positions few
+  // (1.5e7 columns, 2000 entries: 2.13 ms an ingest with the one of the positions)
+  const int64_t ct = std::min<int64_t>(((int64_t)d.n + POS_TILE) / POS_TILE, 2048);
+  hipLaunchKernelGGL(k_positions, dim3((unsigned)std::max(pt, ct)), dim3(PSL_BLOCK), 0, s, d, sc.rowid1,
                      (int32_t*)d.cp, passes ? (1u << per) - 1u : 0u, sc.ws, (int)pt);
 }
 
