@@ -675,14 +675,19 @@ static void set_sizes(psl_presolver* p, int32_t K, int32_t m, int32_t n, int64_t
   p->d.nnz = nnz;
 }
 
-// 4-byte aligned device memory of device dev
-static bool on_device(const void* q, int dev) {
+// 4-byte aligned device memory of device dev, bytes of it in one allocation (a
+// kernel's reads beyond that would fault, where hipMemcpy returns an error)
+static bool on_device(const void* q, size_t bytes, int dev) {
   hipPointerAttribute_t a;
-  if (((uintptr_t)q & 3) != 0 || hipPointerGetAttributes(&a, q) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (((uintptr_t)q & 3) != 0 || hipPointerGetAttributes(&a, q) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)q) != hipSuccess) {
     (void)hipGetLastError();  // not an error of the caller's
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == dev;
+  const size_t at = (size_t)((const char*)q - (const char*)base);
+  return a.type == hipMemoryTypeDevice && a.device == dev && at <= size && bytes <= size - at;
 }
 
 // copy + validate + transpose + bins of one LP whose shape equals the handle's
@@ -701,7 +706,7 @@ static psl_status ingest(psl_presolver* p, const psl_lp* lp) {
   // what else the pointers may be is left to hipMemcpy
   int dev = -1;
   bool here = lp->mem == PSL_MEM_DEVICE && hipGetDevice(&dev) == hipSuccess;
-  for (const InSeg& g : in.seg) here = here && (g.words == 0 || on_device(g.src, dev));
+  for (const InSeg& g : in.seg) here = here && (g.words == 0 || on_device(g.src, g.words * 4, dev));
   if (here) {
     launch_copy_in(in, st);
   } else {
