@@ -98,6 +98,35 @@ def test_infeasible_members_with_options(stop):
     check(lps, f"options {stop}", enable_dual_fix=1, enable_free_singletons=1, enable_forcing_rows=1)
 
 
+def few_rows(seed):
+    """An LP of one to three rows over a few columns; a third of them cannot be met."""
+    rng = np.random.default_rng(seed)
+    m, n = 1 + seed % 3, 4
+    return dict(m=m, n=n, row_ptr=np.arange(0, 3 * m + 1, 3).astype(np.int32),
+                col_idx=np.concatenate([np.sort(rng.choice(n, 3, replace=False)) for _ in range(m)]).astype(np.int32),
+                val=rng.choice([-1.0, 1.0, 2.0], 3 * m), lhs=np.where(rng.random(m) < 0.3, 9.0, -INF),
+                rhs=np.full(m, 9.0), lb=np.zeros(n), ub=rng.integers(1, 6, n).astype(float), c=np.ones(n),
+                obj_offset=0.0)
+
+
+@pytest.mark.parametrize("K", [255, 257, 2047, 2048, 2049, 4097])
+def test_many_lps(K):
+    """The control goes over the LPs in steps of 2048, 256 at a time."""
+    lps = [few_rows(s) for s in range(K)]
+    refs = [O.presolve(lp) for lp in lps]
+    b = psl.Batch(lps)
+    names = b.run()
+    assert names == [ref.result_name for ref in refs]
+    assert "INFEASIBLE" in names[K - 200:] and "REDUCED" in names[K - 200:]
+    for k, ref in enumerate(refs):
+        assert b.lp_stats(k)["rounds"] == ref.rounds, k
+    for k in list(range(8)) + list(range(max(0, K - 8), K)):
+        got = {"result_name": names[k], "records": b.records(k),
+               "reduced": b.reduced(k) if names[k] in ("REDUCED", "UNCHANGED") else None}
+        assert_same(got, refs[k], f"LP {k} of {K}")
+    b.close()
+
+
 @pytest.mark.parametrize("rows,direct", [(96000, True), (98000, False)])
 def test_both_lists_are_reached(rows, direct):
     """The LPs of the two-sided test of the rounds lie on either side."""
