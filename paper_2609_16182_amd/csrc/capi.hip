@@ -566,8 +566,12 @@ static std::string error_message(psl_presolver* p, int32_t bits, int64_t pos) {
 // rows to sweep selected, so that a late round's sweep is as small as they
 // are. A pass, direct and selected: 2000 rows 1.64 and 1.81 ms, 31337 rows
 // (3.6e5 nonzeros) 1.31 and 1.44, 48 LPs of 1.1e6 nonzeros 3.77 and 3.40, the
-// power-law LP (1e7) 6.11 and 5.12.
+// power-law LP (1e7) 6.11 and 5.12. Testing every row pays while the rows are not
+// many more than the entries: with most rows empty, 5e5 of them (40000 and 300000
+// entries) 0.78 and 0.86 ms a run direct, 0.87 and 0.93 selected; 1e6 (480000) 1.19
+// and 1.08, 2e6 3.16 and 2.64, 4e6 2.78 and 2.10.
 static const int64_t DIRECT_NNZ = 500000;
+static const int64_t DIRECT_ROWS = 700000;
 
 // the LP (or union of LPs) of the handle is in d.rp .. p->c_mut; validate,
 // transpose, bin
@@ -587,7 +591,7 @@ static psl_status ingest_rest(psl_presolver* p) {
   LongChunk* chunks0 = p->chunks_0;  // kept intact: the row selections copy from it
   d.bins = bins0;
   d.lchunk = chunks0;
-  d.direct = p->nnz <= DIRECT_NNZ;
+  d.direct = p->nnz <= DIRECT_NNZ && p->m <= DIRECT_ROWS;
   launch_checks(d, p->lb_in, p->ub_in, p->c_mut, p->thresholds, bins0, p->isc, st);
   // the reduced problem's value array is free until compaction
   d.colid = nullptr;
@@ -1114,8 +1118,12 @@ static psl_status complete_round0(psl_presolver* p) {
 // power-law LP (1e7) and on one of 9.6e6 they change nothing (5.39 ms; 19.4
 // against 19.9). Units of 4, 8 and 16 rounds give 2.00, 1.88 and 1.92 ms on an
 // LP of 2000 rows (34 rounds) and 1.52, 1.51, 1.60 on one of 31337 (17 rounds,
-// where the rounds queued past the last are launches that return).
+// where the rounds queued past the last are launches that return). Nor with rows
+// far beyond the entries, whose grids are of the rows: with most rows empty, 2e6 of
+// them 2.64 ms a run queued ahead and 2.79 round by round, 4e6 2.10 and 2.04, 1e7
+// 8.07 and 7.24, 3e7 20.0 and 15.6.
 static const int64_t RUN_AHEAD_NNZ = 4000000;
+static const int64_t RUN_AHEAD_ROWS = 3000000;
 static const int RUN_AHEAD = 8;
 
 static psl_status launch_round(psl_presolver* p) {
@@ -1133,7 +1141,7 @@ static psl_status launch_round(psl_presolver* p) {
   }
   launch_rounds_begin(d, p->rec_count - p->rec_flushed, p->rec_cap, st);
   // (the trace has a line for each round, from the reads after it)
-  const bool ahead = p->nnz <= RUN_AHEAD_NNZ && !p->step_rounds && !p->trace;
+  const bool ahead = p->nnz <= RUN_AHEAD_NNZ && p->m <= RUN_AHEAD_ROWS && !p->step_rounds && !p->trace;
   R.queued = std::min(ahead ? RUN_AHEAD : 1, s.max_rounds - R.r);
   for (int q = 0; q < R.queued; ++q) {
     const int seq = ++R.seq, round = R.round + 1 + q;
