@@ -27,12 +27,14 @@
 namespace psl {
 
 // Most rounds have no candidate. A round that has marks flags->fs_picks with
-// its number, and without the mark the launches after the first return at once;
-// those of the chunk lists have one workgroup a CU at most. (1e6 rows with every
-// option: 12 launches of 55 us together a round, 8 of 36 now.)
+// its number, and without the mark the launches after the first return at once.
+// (1e6 rows with every option: 12 launches of 55 us together a round, 8 of 36 now.)
+// The launches over the chunk lists have four workgroups a CU: with one, a run
+// over 40000 rows of 65 entries, each with a free singleton of its own, took 7.2 ms
+// instead of 5.0, and an LP without such rows no less than with four.
 #define FS_SHORT 32
 #define FS_CHUNK PSL_BLOCK
-#define FS_LIST_BLOCKS 256
+#define FS_LIST_BLOCKS 1024
 #define FS_SUPER 64  // tiles whose counts are added up for the offsets
 #define FS_NONE 0x7FFFFFFF
 
