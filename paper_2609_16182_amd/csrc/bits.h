@@ -35,20 +35,17 @@ __device__ __forceinline__ int32_t rank_of(const RankWord* rw, int64_t j) {
   return w.all + set_below(w, j);
 }
 
-__device__ __forceinline__ void set_word(uint64_t& w, uint64_t v) { w = v; }
-__device__ __forceinline__ void set_word(RankWord& w, uint64_t v) { w.bits = v; }
-
 // Word w of flag f over [0, n): each wavefront takes 64 consecutive indices
 // (an aligned word), its ballot is the word. Launched with one thread per
 // index (grid-strided in multiples of 64), every lane of a word present.
-template <typename W, typename F>
-__device__ __forceinline__ void write_bits(W* words, int64_t n, F f) {
+template <typename F>
+__device__ __forceinline__ void write_bits(uint64_t* words, int64_t n, F f) {
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < n; t0 += stride) {
     int64_t t = t0 + threadIdx.x;
     bool v = t < n && f(t);
     unsigned long long w = __ballot(v);
-    if ((threadIdx.x & 63) == 0 && t < n) set_word(words[t >> 6], w);
+    if ((threadIdx.x & 63) == 0 && t < n) words[t >> 6] = w;
   }
 }
 

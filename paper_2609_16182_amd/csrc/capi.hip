@@ -3,14 +3,16 @@
 // rows, section 3.2; repeated for a few outer cycles), compaction and the
 // host postsolve (section 3.3).
 //
-// Control crosses to the host once per round: a 64-byte flag block (records
-// emitted, infeasible / unbounded) is read back to decide whether to go on.
+// Control crosses to the host once per unit, which is a round or, in smaller
+// LPs, up to eight rounds that the device ends itself: a flag block of 2.4 KB (records
+// emitted, rows swept, the next selection's counts, infeasible / unbounded) is read
+// back to decide whether to go on.
 //
 // One engine serves a single LP (K = 1) and batches of K LPs laid out as the
 // blocks of one block-diagonal LP. In a batch every LP has its own state
 // machine on the host (propagating / converged / done, its round count and
-// outer cycles); the per-round readback then also holds each LP's record
-// count and flags, and LPs that stopped are filtered out of the bin lists.
+// outer cycles); the readback then also holds each LP's flags and its round number
+// (negative once it has converged), and rows of LPs that stopped are not swept.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -564,9 +566,11 @@ static std::string error_message(psl_presolver* p, int32_t bits, int64_t pos) {
 // row tests ride along with the row's entries, and the selection (a launch of
 // 8 us beside a sweep of 17 on an LP of 2000 rows) goes. Larger LPs have the
 // rows to sweep selected, so that a late round's sweep is as small as they
-// are. A pass, direct and selected: 2000 rows 1.64 and 1.81 ms, 31337 rows
-// (3.6e5 nonzeros) 1.31 and 1.44, 48 LPs of 1.1e6 nonzeros 3.77 and 3.40, the
-// power-law LP (1e7) 6.11 and 5.12. Testing every row pays while the rows are not
+// are. A pass, direct and selected: 2000 rows 1.64 and 1.81 ms; rows of 8 with
+// planted reductions, 2e5 nonzeros 1.25 and 1.59, 4.5e5 1.53 and 1.76, 5.5e5 1.59
+// and 1.80, 9e5 1.97 and 2.00, 1.5e6 2.53 and 2.37; rows of 9 without, 4.5e5 0.71
+// and 0.80, 9e5 0.85 both, 1.5e6 1.02 and 0.94; 48 LPs of 1.1e6 nonzeros 3.77 and
+// 3.40, the power-law LP (1e7) 6.11 and 5.12. Testing every row pays while the rows are not
 // many more than the entries: with most rows empty, 5e5 of them (40000 and 300000
 // entries) 0.78 and 0.86 ms a run direct, 0.87 and 0.93 selected; 1e6 (480000) 1.19
 // and 1.08, 2e6 3.16 and 2.64, 4e6 2.78 and 2.10.

@@ -632,7 +632,7 @@ __global__ void k_init_state(Dev d, int64_t supers, const double* c_in, double* 
     f.n_dense = d.flags->n_dense;  // of the ingest
     for (int b = 0; b < NBINS; ++b) f.bins[b] = d.flags->bins[b];
     f.infeasible = f.unbounded = f.error = f.merged = 0;
-    f.cand_count = f.round_total = f.vlist_count = f.rows_removed = 0;
+    f.round_total = f.vlist_count = f.rows_removed = 0;
     f.fin_cols = f.mode = f.lead_count = f.fs_picks = f.fs_rows = f.fs_claims = 0;
     f.error_pos = 0x7FFFFFFFFFFFFFFFLL;
     f.dbl_count = f.dbl_applied = 0;

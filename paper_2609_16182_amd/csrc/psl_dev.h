@@ -6,8 +6,9 @@
 //   rows  lhs/rhs[m] f64, row_on[m] u8, row_code[m] u8, row_out[m] 16 B
 //   cols  bnd[n] double2 (lb, ub), bkey[2n] i64 (order-mapped accumulators of
 //         the round's best lb / ub, both largest key first), src[2n] i32, col_len[n] i32, c[n] f64
-//   bins  bins[m] {row, start, len} (active rows grouped by CSR length,
-//         ascending within a bin; filtered as rows are removed)
+//   bins  bins[m] {row, start, len} (rows grouped by CSR length: those of the
+//         ingest all rows, ascending within a bin; a selection's the rows to
+//         sweep, ascending within a tile of rows, the tiles in any order)
 // A column is removed exactly when lb == ub: a fixed column keeps lb = ub = v,
 // and every active column has ub - lb > fix_tol * max(1, |lb|) >= 0 once a
 // round has run, so the sweep learns a column's state from its bounds alone.
@@ -120,7 +121,7 @@ struct Swept {
 
 struct Flags {
   int32_t infeasible, unbounded, error, merged;
-  int32_t cand_count, round_total, vlist_count, rows_removed;
+  int32_t round_total, vlist_count, rows_removed;
   int32_t fin_cols;        // columns of the round with a bound that became finite
   int32_t mode;            // the next round's selection mode (bit 0: touched rows
                            // only, bit 1: inert rows skipped), set with the decisions

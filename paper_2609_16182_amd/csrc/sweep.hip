@@ -11,7 +11,7 @@
 // butterfly over G lanes, four wavefronts, chunk partials -- gives the same
 // bits, whatever bin a row falls in.
 //
-// Bins (by CSR length; rows are listed per bin, ascending):
+// Bins (by CSR length; the order of the rows in a bin is of no consequence):
 //   G4  <= 4     4-lane groups, 1 position per lane
 //   G8  <= 8     8-lane groups, 1 position per lane
 //   G16 <= 16    16-lane groups, 1 position per lane
@@ -235,10 +235,12 @@ struct CandSink {  // this workgroup's candidate region and its LDS counter
 // Fold qualifying candidates into the round's accumulators and list them; a
 // candidate that another one beats is found not to be the final bound when the
 // sources are taken. Nothing is read back, so no wavefront waits for memory
-// here; with long columns (d.look_first) their accumulators are read first,
-// since a beaten candidate's atomic waits for all others on that address (a
-// presolve of 1e6 power-law rows 4.84 ms, 5.33 without the look; a 4096-LP
-// batch, without long columns, 74.9 and 73.5 ms).
+// here; in an LP with long columns (d.look_first) the accumulators are read first,
+// since a beaten candidate's atomic waits for all others on that address. The
+// look is the whole LP's: 1e6 power-law rows, with many long columns, take 4.41
+// ms a presolve with it and 4.77 without; 1e7 rows with 20 long columns of 1.5e7
+// 72.7 and 72.0, so a few of them pay for it; a 4096-LP batch without any, which
+// has no look, 71.4 with one and 70.7.
 // Most lanes have one side at most, so one atomic and one store serve both.
 // Must be reached by every lane of the wavefront.
 __device__ __forceinline__ void commit_cands(const Dev& d, const CandSink& sk, int pos, int j, bool hlo, double tlo,

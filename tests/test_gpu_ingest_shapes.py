@@ -55,3 +55,22 @@ def test_many_columns(m, n):
     out, p = psl.presolve(lp)
     p.close()
     assert_same(out, O.presolve(lp), f"{m} x {n}")
+
+
+@pytest.mark.parametrize("at", [1, 2047, 2048, 5000])
+@pytest.mark.parametrize("what", ["column", "order", "value"])
+def test_lowest_invalid_entry_is_named(at, what):
+    """Of two invalid entries the message names the lower one, in full."""
+    lp = lp_of(1000, 1000, length=7)
+    for p in (at, 6001):
+        if what == "column":
+            lp["col_idx"][p] = 1000
+        elif what == "order":
+            assert p % 7  # not a row's first entry
+            lp["col_idx"][p] = lp["col_idx"][p - 1]
+        else:
+            lp["val"][p] = np.inf
+    with pytest.raises(psl.PslError) as e:
+        psl.presolve(lp)
+    assert e.value.status == psl.PSL_ERR_INVALID
+    assert f"(first at index {at})" in str(e.value)
